@@ -1187,6 +1187,9 @@ tc_status count_graphs(tc_context* ctx, uint32_t k, tc_graph* const* graphs, uin
     H->hub_words = hub_words;
     const uint32_t pf[tc::kBins] = {1u, 1u, 1u, p.light_chunk, 4u * p.light_chunk};
     for (uint32_t b = 0; b < tc::kBins; ++b) H->per_fetch[b] = pf[b];
+    int per_cu = 0;
+    if (tc_status e = occupancy(ctx, p, pv, false, &per_cu, true)) return e;
+    H->waves = p.wg_waves * (p.grid_wgs ? p.grid_wgs : (uint32_t)(per_cu * ctx->cu_count));
     tc::MultiDesc* D = reinterpret_cast<tc::MultiDesc*>(h + hdr_bytes);
     uint64_t tv0 = 0, t0 = 0;
     for (uint32_t g = 0; g < k; ++g) {

@@ -871,6 +871,46 @@ __device__ __forceinline__ uint32_t bin_base(const GraphMeta* m, uint32_t bin) {
     return b;
 }
 
+// Guided fetches of a wavefront bin (largest work first): the first `waves` fetches take `unit` items
+// each, the next `waves` twice as many, and so on up to `cap` items per fetch.  With `cap` from the start
+// one wavefront took the 16 (packed: 64) heaviest vertices of the bin one after another: R-MAT scale 16
+// spent 1.57 ms in a chain of 16 vertices of 3e4 probes, Barabasi-Albert with 1000 vertices ran on 16
+// wavefronts.
+struct Guided {
+    uint32_t n, waves, unit, cap, levels, level0;  // level0: items the doubling levels take
+    __device__ __forceinline__ Guided(uint32_t n_, uint32_t waves_, uint32_t unit_, uint32_t cap_)
+        : n(n_), waves(waves_ < 65536u ? waves_ : 65536u), unit(unit_), cap(cap_), levels(0) {
+        while ((unit << levels) < cap) ++levels;  // sizes unit << l below cap
+        level0 = unit * waves * ((1u << levels) - 1u);
+    }
+    __device__ __forceinline__ Guided(uint32_t n_, uint32_t waves_, uint32_t unit_, uint32_t cap_, uint32_t levels_)
+        : n(n_), waves(waves_ < 65536u ? waves_ : 65536u), unit(unit_), cap(cap_), levels(levels_) {
+        level0 = unit * waves * ((1u << levels) - 1u);
+    }
+    __device__ __forceinline__ uint32_t fetches() const {
+        if (n > level0) return levels * waves + (n - level0 + cap - 1) / cap;
+        uint32_t f = 0, left = n;
+        for (uint32_t l = 0; left; ++l) {
+            const uint32_t size = unit << l, most = (left + size - 1) / size;
+            const uint32_t take = most < waves ? most : waves;
+            f += take;
+            left = most <= waves ? 0u : left - waves * size;
+        }
+        return f;
+    }
+    __device__ __forceinline__ void range(uint32_t f, uint32_t& j0, uint32_t& j1) const {
+        const uint32_t l = f / waves;
+        uint32_t size = cap;
+        if (l < levels) {
+            size = unit << l;
+            j0 = unit * waves * ((1u << l) - 1u) + (f - l * waves) * size;
+        } else {
+            j0 = level0 + (f - levels * waves) * cap;
+        }
+        j1 = j0 + size < n ? j0 + size : n;
+    }
+};
+
 // Wavefront total of a multi-graph launch: hits of single graphs accumulate in `acc` while they
 // belong to the same graph and go to that graph's total when the wavefront moves to another one.
 struct AccSink {
@@ -1003,7 +1043,8 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
     __shared__ uint32_t s_wsum[kMaxWaves];
     __shared__ unsigned long long s_acc[kMaxWaves];
     __shared__ uint32_t s_item;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+    __shared__ uint32_t s_fetch[kMaxWaves][4];  // a wavefront bin's fetches (in LDS: the kernel is short of scalar registers)
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
     unsigned long long acc = 0;
     AccSink sink;
     uint32_t n_before, n_wg, n_wave, n_pack;
@@ -1021,13 +1062,9 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
 
     uint32_t* const queue = lds + a.table_words + (size_t)wave * kQueueWords;  // this wavefront's probe queue
     // Workgroup bin: the table fills the workgroup's table region.
+    // (Workgroup b starts with vertex b; the queue holds the others.)
     if (n_wg) {
-        for (;;) {
-            if (tid == 0) s_item = atomicAdd(&a.heads[2 * kHeadStride], 1u);
-            __syncthreads();
-            const uint32_t j = s_item;
-            __syncthreads();
-            if (j >= n_wg) break;
+        for (uint32_t j = blockIdx.x; j < n_wg;) {
             if constexpr (MULTI) {
                 const MultiHeader* H = a.multi;
                 const uint32_t* pre = H->pre + 2u * (H->k + 1);
@@ -1041,54 +1078,99 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
                 process_wg<S, PV, HK, true, SW>(a, a.items[n_before + j], lds, a.table_words, tid, wave, nw, lane,
                                                 s_wsum, acc, queue);
             }
+            if (n_wg <= gridDim.x) break;
+            if (tid == 0) s_item = gridDim.x + atomicAdd(&a.heads[2 * kHeadStride], 1u);
+            __syncthreads();
+            j = s_item;
+            __syncthreads();
         }
     }
-    // Wavefront bins: each wavefront owns a slice of the LDS and takes `per_fetch` vertices at a time.
-    // Chunk c of a bin belongs to sub-queue c % kWaveQueues (interleaved, so every sub-queue keeps the
+    // Wavefront bins: each wavefront owns a slice of the LDS and takes up to `per_fetch` vertices at a
+    // time (Guided; in multi-graph mode what the set-up kernel chose).  When no earlier bin has work,
+    // wavefront w of the launch starts with chunk w (its number counts workgroups first, so the largest
+    // chunks go to different CUs) and the queue holds the rest; with workgroup-bin vertices every chunk is
+    // in the queue, since a wavefront of a busy workgroup would start its large chunk late.  Chunk c of
+    // the queue belongs to sub-queue c % kWaveQueues (interleaved, so every sub-queue keeps the
     // largest-work-first order); each sub-queue counter has a cache line of its own, which spreads
     // the fetch atomics of a launch with millions of light vertices over kWaveQueues addresses.  A
-    // wavefront starts on sub-queue blockIdx % kWaveQueues (one per XCD with round-robin dispatch),
-    // moves on when its sub-queue is drained, and requests its next chunk before working on the
-    // current one.  `work(args, base, j0, j1)` processes items base + [j0, j1) of the bin with the
+    // wavefront starts on sub-queue blockIdx % kWaveQueues (one per XCD with round-robin dispatch) and
+    // requests its next chunk before working on the current one; when its sub-queue is drained it reads
+    // all counters at once and moves to one that is not.  (Moving on by an atomic on each of the other
+    // sub-queues in turn kept even an empty launch of 6144 wavefronts busy for 0.1 ms.)
+    // `work(args, base, j0, j1)` processes items base + [j0, j1) of the bin with the
     // arguments of their graph (in multi-graph mode a chunk never spans two graphs).
     // The wavefront's own region (after the workgroup bin): a table slice and its probe queue, or
     // four packed-vertex tables.
     uint32_t* slice = lds + (size_t)wave * (a.slice_words + kQueueWords);
     uint32_t* const slice_queue = slice + a.slice_words;
+    bool busy = n_wg != 0;  // an earlier bin has work
     auto drain = [&](uint32_t bin, uint32_t n_bin, uint32_t base1, uint32_t per_fetch, uint32_t head0,
                      auto&& work) {
-        const uint32_t nchunks = MULTI ? a.multi->fetch_tot[bin] : (n_bin + per_fetch - 1) / per_fetch;
-        uint32_t q = blockIdx.x % kWaveQueues, drained = 0;
+        uint32_t* const st = s_fetch[wave];
+        {
+            const uint32_t waves = gridDim.x * (uint32_t)nw;
+            const Guided guided(MULTI ? 0u : n_bin, waves, bin == 4u ? 4u : 1u, per_fetch);
+            const uint32_t nchunks = MULTI ? a.multi->fetch_tot[bin] : guided.fetches();
+            if (nchunks == 0) return;
+            if (lane == 0) {
+                st[0] = nchunks;
+                st[1] = busy ? 0u : waves;  // chunks outside the queue
+                st[2] = n_bin;
+                st[3] = guided.levels;
+            }
+            wave_sync();
+        }
+        busy = true;
+        auto state = [&](int i) -> uint32_t { return __builtin_amdgcn_readfirstlane(st[i]); };
+        uint32_t q = blockIdx.x % kWaveQueues;
         auto request = [&]() -> uint32_t {
             uint32_t c = 0;
             if (lane == 0) c = atomicAdd(&a.heads[(head0 + q) * kHeadStride], 1u);
             return c;
         };
-        // Chunk index from a sub-queue ticket, moving on through drained sub-queues (nchunks: all done).
+        // Chunk index from a sub-queue ticket, moving on from drained sub-queues (kNone: all done).
+        // Counters only grow, so each round either returns or finds a sub-queue drained for good.
+        constexpr uint32_t kNone = 0xFFFFFFFFu;
         auto settle = [&](uint32_t ticket) -> uint32_t {
+            const uint32_t nchunks = state(0), fixed = state(1);
+            if (nchunks <= fixed) return kNone;
             for (;;) {
-                const uint32_t g = __builtin_amdgcn_readfirstlane(ticket) * kWaveQueues + q;
+                const uint32_t g = fixed + __builtin_amdgcn_readfirstlane(ticket) * kWaveQueues + q;
                 if (g < nchunks) return g;
-                if (++drained >= kWaveQueues) return nchunks;
-                q = (q + 1) % kWaveQueues;
+                uint32_t seen = 0;
+                if (lane < (int)kWaveQueues)
+                    seen = __hip_atomic_load(&a.heads[(head0 + (uint32_t)lane) * kHeadStride], __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t left = (uint32_t)__ballot(
+                    lane < (int)kWaveQueues && fixed + (uint64_t)seen * kWaveQueues + (uint32_t)lane < nchunks);
+                if (!left) return kNone;
+                const uint32_t above = left >> q;  // the next one at or after q, else the lowest
+                q = above ? q + (uint32_t)__builtin_ctz(above) : (uint32_t)__builtin_ctz(left);
                 ticket = request();
             }
         };
-        uint32_t cur = settle(request());
-        while (cur < nchunks) {
-            const uint32_t ticket = request();  // next chunk, settled after this one
+        uint32_t cur;
+        if (state(1)) {
+            cur = (uint32_t)wave * gridDim.x + blockIdx.x;
+            if (cur >= state(0)) cur = kNone;
+        } else {
+            cur = settle(request());
+        }
+        while (cur != kNone) {
+            const uint32_t ticket = state(0) > state(1) ? request() : 0u;  // next chunk, settled after this one
             if constexpr (MULTI) {
                 const MultiHeader* H = a.multi;
                 const uint32_t* pre = H->pre + (size_t)bin * (H->k + 1);
                 const uint32_t g = find_graph(pre, H->k, cur, lane);
                 const MultiDesc& d = H->desc[g];
-                const uint32_t nb = d.meta->bins[bin];
-                const uint32_t j0 = (cur - pre[g]) * per_fetch;
+                const uint32_t nb = d.meta->bins[bin], size = H->fetch_size[bin];
+                const uint32_t j0 = (cur - pre[g]) * size;
                 sink.to(d.totals, acc, lane);
-                work(graph_view(a, d), bin_base(d.meta, bin), j0, (j0 + per_fetch < nb) ? j0 + per_fetch : nb);
+                work(graph_view(a, d), bin_base(d.meta, bin), j0, (j0 + size < nb) ? j0 + size : nb);
             } else {
-                const uint32_t j0 = cur * per_fetch;
-                work(a, base1, j0, (j0 + per_fetch < n_bin) ? j0 + per_fetch : n_bin);
+                uint32_t j0, j1;
+                Guided(state(2), gridDim.x * (uint32_t)nw, bin == 4u ? 4u : 1u, per_fetch, state(3)).range(cur, j0, j1);
+                work(a, base1, j0, j1);
             }
             cur = settle(ticket);
         }
@@ -1268,8 +1350,11 @@ hipError_t count_launch_multi(bool hub, uint32_t S, bool pv, uint32_t hash_kind,
 namespace {
 
 // Multi-graph set-up: every workgroup clears a grid-stride share of the totals and (per-vertex mode)
-// of the staging; workgroup 0 clears the queue heads and forms, for every bin, the exclusive prefix
-// over the handles of their fetch counts (ceil(bin size / per_fetch)) and the bin totals.
+// of the staging; workgroup 0 clears the queue heads, chooses the vertices per fetch of every bin (at
+// most per_fetch, and so few that the bin makes two fetches per wavefront of the launch where it can:
+// 256 graphs of up to 20,000 vertices counted in 0.61 ms with the full 16 and 64 per fetch) and forms
+// the exclusive prefix over the handles of their fetch counts (ceil(bin size / fetch size)) and the bin
+// totals.
 __global__ void __launch_bounds__(1024) k_multi_prepare(MultiHeader* H) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, nw = blockDim.x >> 6;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -1278,7 +1363,7 @@ __global__ void __launch_bounds__(1024) k_multi_prepare(MultiHeader* H) {
         for (size_t i = (size_t)blockIdx.x * blockDim.x + tid; i < H->n_total; i += stride) H->tv[i] = 0;
     if (blockIdx.x != 0) return;
     __shared__ uint32_t s_wave[kBins][kMaxWaves];
-    __shared__ uint32_t s_carry[kBins], s_items[kBins];
+    __shared__ uint32_t s_carry[kBins], s_items[kBins], s_size[kBins];
     for (uint32_t i = tid; i < kHeadWords; i += blockDim.x) H->heads[i] = 0;
     if (tid < kBins) {
         s_carry[tid] = 0;
@@ -1286,16 +1371,27 @@ __global__ void __launch_bounds__(1024) k_multi_prepare(MultiHeader* H) {
     }
     __syncthreads();
     const uint32_t k = H->k;
+    for (uint32_t g = tid; g < k; g += blockDim.x) {
+        const GraphMeta* m = H->desc[g].meta;
+#pragma unroll
+        for (uint32_t b = 0; b < kBins; ++b) {
+            const uint32_t nb = m ? m->bins[b] : 0u;
+            if (nb) atomicAdd(&s_items[b], nb);
+        }
+    }
+    __syncthreads();
+    if (tid < kBins) {
+        const uint32_t unit = tid == 4u ? 4u : 1u, cap = H->per_fetch[tid];
+        const uint32_t even = s_items[tid] / (2u * H->waves) / unit * unit;
+        s_size[tid] = even < unit ? (unit < cap ? unit : cap) : even < cap ? even : cap;
+    }
+    __syncthreads();
     for (uint32_t g0 = 0; g0 < k; g0 += blockDim.x) {
         const uint32_t g = g0 + tid;
         uint32_t f[kBins];
         const GraphMeta* m = g < k ? H->desc[g].meta : nullptr;
 #pragma unroll
-        for (uint32_t b = 0; b < kBins; ++b) {
-            const uint32_t nb = m ? m->bins[b] : 0u;
-            if (nb) atomicAdd(&s_items[b], nb);
-            f[b] = (nb + H->per_fetch[b] - 1) / H->per_fetch[b];
-        }
+        for (uint32_t b = 0; b < kBins; ++b) f[b] = ((m ? m->bins[b] : 0u) + s_size[b] - 1) / s_size[b];
         uint32_t incl[kBins];
 #pragma unroll
         for (uint32_t b = 0; b < kBins; ++b) {
@@ -1321,6 +1417,7 @@ __global__ void __launch_bounds__(1024) k_multi_prepare(MultiHeader* H) {
         H->pre[tid * (k + 1) + k] = s_carry[tid];
         H->fetch_tot[tid] = s_carry[tid];
         H->items_tot[tid] = s_items[tid];
+        H->fetch_size[tid] = s_size[tid];
     }
 }
 

@@ -280,10 +280,12 @@ struct MultiHeader {
     uint32_t* heads;                 // [kHeadWords] queue heads
     uint32_t* hub;                   // global-memory tables: hub_wgs regions of hub_words words
     unsigned long long hub_words;
-    uint32_t per_fetch[kBins];       // vertices per queue fetch of each bin (host-written)
+    uint32_t per_fetch[kBins];       // most vertices per queue fetch of each bin (host-written)
     uint32_t items_tot[kBins];       // scheduled vertices of each bin over all handles (device-written)
     uint32_t fetch_tot[kBins];       // fetches of each bin over all handles (device-written)
-    uint32_t pad[29];
+    uint32_t fetch_size[kBins];      // vertices per queue fetch of each bin (device-written)
+    uint32_t waves;                  // wavefronts of the main launch
+    uint32_t pad[23];
 };
 static_assert(sizeof(MultiHeader) == 256, "header is one 256-byte block");
 
