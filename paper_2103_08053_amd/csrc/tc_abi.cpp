@@ -102,6 +102,9 @@ namespace {
 
 using tc::Layout;
 
+constexpr uint64_t kCoreMinSamples = 1u << 17;  // core path: fewest edge samples
+constexpr uint32_t kCoreWideRanks = 1u << 24;   // and the vertices from which its core is the larger one
+
 constexpr size_t kAlign = 256;
 constexpr size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -238,6 +241,35 @@ bool records_on(const tc_params& p, uint32_t n, uint64_t m_in) {
            tc::record_words(n, m_in) < (1ull << 31);
 }
 
+// Layout of the core path (tc_core.hip) for a graph of n vertices and m_in samples built with p.  Ids per
+// block word: the most whose 2^(32 - S) blocks hold every rank; where n is larger, 21 (an 8 KB table in the
+// count's and the build's LDS; R-MAT 22: blocks built in 1.1 ms against 2.0 ms with 20 and 16 KB, and the
+// same count), but 20 from 2^24 vertices on, where a core of 43,008 ranks leaves too many probes to the
+// bucket kernels (R-MAT 26 per-vertex count 388 ms against 397).  A word's index must also be able
+// to name every member of the list of an owner that the path takes.  For default flags (each of them asks
+// for a bin, a probe or an order of its own), single graphs, and enough samples that the few launches more
+// do not show.
+void core_shape(const tc_context* ctx, const tc_params& p, const tc::BinCaps& caps, uint32_t n, uint64_t m_in,
+                bool batch, Layout& L) {
+    L.core_bits = L.core_first = 0;
+    L.core_big_all = false;
+    if (!ctx || batch || p.flags != 0 || m_in < kCoreMinSamples || n > m_in) return;
+    // the launches' tables hold out-degrees up to 128 (wavefront bin), 1024 and 4096
+    if (caps.wave_cap > 128 || caps.wg_cap > 1024 || caps.big_cap > 4096) return;
+    const uint32_t most = std::min(dplus_bound(n, m_in), caps.big_cap);  // out-degrees of bins 1 and 2
+    const uint32_t named = std::min(most, std::max(caps.wg_cap, caps.mid_cap));
+    uint32_t S = 22;
+    while (S > 20 && ((uint64_t)S << (32 - S)) < n) --S;
+    if (n >= kCoreWideRanks) S = 20;
+    else if (S == 20 && ((uint64_t)S << (32 - S)) < n) S = 21;
+    while (S > tc::kCoreMinBits && (1u << (32 - S)) < named) --S;
+    if ((1u << (32 - S)) < named) return;
+    const uint64_t ranks = (uint64_t)S << (32 - S);
+    L.core_bits = S;
+    L.core_first = n > ranks ? (uint32_t)(n - ranks) : 0u;
+    L.core_big_all = (1u << (32 - S)) >= most;
+}
+
 Layout layout(const tc_context* ctx, const tc_params& p, uint32_t n, uint64_t m_in, bool batch = false) {
     Layout L{};
     L.records = records_on(p, n, m_in);
@@ -251,6 +283,13 @@ Layout layout(const tc_context* ctx, const tc_params& p, uint32_t n, uint64_t m_
     L.s_gid = o;   o = align_up(o + (batch ? sizeof(uint32_t) * (size_t)n : 0));
     L.s_rec = o;   o = align_up(o + (L.records ? sizeof(uint32_t) * tc::record_words(n, m_in) : 0));
     L.s_place = o; o = align_up(o + (L.records ? 8 * ((size_t)n + 1) : 0));
+    core_shape(ctx, p, bin_caps(ctx, p), n, m_in, batch, L);
+    const bool core = L.core_bits != 0;
+    L.s_blk = o;    o = align_up(o + (core ? 16 * (tc::core_start((uint32_t)m_in, n) + 1) : 0));
+    L.s_bl = o;     o = align_up(o + (core ? 8 * (size_t)n : 0));
+    L.s_rend = o;   o = align_up(o + (core ? 4 * (size_t)n : 0));
+    L.s_rmeta = o;  o = align_up(o + (core ? sizeof(tc::GraphMeta) : 0));
+    L.s_ritems = o; o = align_up(o + (core ? 4 * (size_t)n : 0));
     L.storage = o;
 
     o = 0;
@@ -302,6 +341,12 @@ tc::GraphDev graph_ptrs(void* storage, const Layout& L) {
     g.gid = nullptr;
     g.rec = L.records ? reinterpret_cast<uint32_t*>(b + L.s_rec) : nullptr;
     g.place = L.records ? reinterpret_cast<uint32_t*>(b + L.s_place) : nullptr;
+    const bool core = L.core_bits != 0;
+    g.blk = core ? reinterpret_cast<uint4*>(b + L.s_blk) : nullptr;
+    g.bl = core ? reinterpret_cast<uint2*>(b + L.s_bl) : nullptr;
+    g.rend = core ? reinterpret_cast<uint32_t*>(b + L.s_rend) : nullptr;
+    g.rest_meta = core ? reinterpret_cast<tc::GraphMeta*>(b + L.s_rmeta) : nullptr;
+    g.rest_items = core ? reinterpret_cast<uint32_t*>(b + L.s_ritems) : nullptr;
     return g;
 }
 
@@ -347,6 +392,9 @@ tc_status build_into(tc_context* ctx, tc_graph* g, uint32_t n, uint64_t m_in, co
     g->p = ctx->p;
     g->caps = bin_caps(ctx, ctx->p);
     g->caps.records = L.records;
+    g->caps.core_bits = L.core_bits;
+    g->caps.core_first = L.core_first;
+    g->caps.core_big_all = L.core_big_all;
     g->empty = (n == 0 || m_in == 0);
     if (g->empty) {
         g->dev = tc::GraphDev{};
@@ -361,7 +409,8 @@ tc_status build_into(tc_context* ctx, tc_graph* g, uint32_t n, uint64_t m_in, co
     g->dev = graph_ptrs(storage, L);
     if (batch) g->dev.gid = reinterpret_cast<uint32_t*>(static_cast<char*>(storage) + L.s_gid);
     if (ctx->timing) HIP_TRY(ctx, hipEventRecord(ctx->ev[0], s));
-    HIP_TRY(ctx, tc::prep_build(n, m_in, src, dst, g->dev, temp_ptrs(temp, L), g->caps, batch, s));
+    HIP_TRY(ctx, tc::prep_build(n, m_in, src, dst, g->dev, temp_ptrs(temp, L), g->caps, batch, ctx->cu_count,
+                                s));
     if (ctx->timing) {
         HIP_TRY(ctx, hipEventRecord(ctx->ev[1], s));
         ctx->have_build = true;
@@ -410,9 +459,55 @@ tc_status occupancy(tc_context* ctx, const tc_params& p, bool pv, bool hub, int*
     return TC_OK;
 }
 
+tc_status core_occupancy(tc_context* ctx, int part, bool pv, uint32_t S, int* per_cu) {
+    const uint32_t key = 2u + (uint32_t)part;  // beside the count kernels' 0 and 1
+    for (const auto& o : ctx->occ)
+        if (o.hub == key && o.pv == (uint32_t)pv && o.S == S) {
+            *per_cu = o.per_cu;
+            return TC_OK;
+        }
+    int q = 0;
+    HIP_TRY(ctx, tc::core_info(part, pv, S, &q));
+    if (q < 1) return fail(ctx, TC_E_INVALID, "core kernel %d does not fit", part);
+    ctx->occ.push_back({key, 0, 0, S, (uint32_t)pv, 0, 0, 0, q});
+    *per_cu = q;
+    return TC_OK;
+}
+
 // Whether any vertex can land in bins 0 or 1 (those need the large-vertex launch).
 bool needs_hub_launch(const tc_graph* g) {
     return g->caps.force_hub || g->caps.force_big || dplus_bound(g->n, g->m_in) > g->caps.wg_cap;
+}
+
+// Grid sizes of a count's launches (resolving them may set kernel attributes: not while capturing).
+struct Shapes {
+    uint32_t grid = 0, grid_hub = 0, grid_mid = 0;
+    uint32_t grid_core[3] = {0, 0, 0};  // 0: no owner can be of that size
+};
+
+tc_status launch_shapes(tc_context* ctx, const tc_graph* g, bool pv, Shapes* out) {
+    const tc_params& p = g->p;
+    auto grid = [&](int per_cu) { return p.grid_wgs ? p.grid_wgs : (uint32_t)(per_cu * ctx->cu_count); };
+    int q = 0;
+    if (tc_status st = occupancy(ctx, p, pv, false, &q)) return st;
+    out->grid = grid(q);
+    if (needs_hub_launch(g)) {
+        if (tc_status st = occupancy(ctx, p, pv, true, &q)) return st;
+        out->grid_hub = grid(q);
+        if (g->caps.mid_cap) {
+            if (tc_status st = occupancy(ctx, p, pv, true, &q, false, ctx->mid_lds_bytes, 64 * tc::kMidWaves)) return st;
+            out->grid_mid = grid(q);
+        }
+    }
+    if (g->caps.core_bits) {
+        const uint32_t dmax = dplus_bound(g->n, g->m_in);
+        for (int part = 0; part < 3; ++part) {
+            if (part && dmax <= (part == 1 ? g->caps.wave_cap : g->caps.wg_cap)) continue;
+            if (tc_status st = core_occupancy(ctx, part, pv, g->caps.core_bits, &q)) return st;
+            out->grid_core[part] = grid(q);
+        }
+    }
+    return TC_OK;
 }
 
 // The count: clears, the persistent kernel and (per-vertex mode) the gather.
@@ -457,17 +552,11 @@ tc_status count_into(tc_context* ctx, const tc_graph* g, uint64_t* d_totals, uin
     a.subwave = subwave_lanes(p.flags);
     a.pack_region = pack_region(p);
     const bool hub = needs_hub_launch(g);
-    int per_cu = 0, per_cu_hub = 0, per_cu_mid = 0;
-    if (tc_status st = occupancy(ctx, p, pv, false, &per_cu)) return st;
-    if (hub)
-        if (tc_status st = occupancy(ctx, p, pv, true, &per_cu_hub)) return st;
-    if (hub && g->caps.mid_cap)
-        if (tc_status st = occupancy(ctx, p, pv, true, &per_cu_mid, false, ctx->mid_lds_bytes, 64 * tc::kMidWaves))
-            return st;
-    const uint32_t grid = p.grid_wgs ? p.grid_wgs : (uint32_t)(per_cu * ctx->cu_count);
-    const uint32_t grid_hub = p.grid_wgs ? p.grid_wgs : (uint32_t)(per_cu_hub * ctx->cu_count);
-    const uint32_t grid_mid = p.grid_wgs ? p.grid_wgs : (uint32_t)(per_cu_mid * ctx->cu_count);
-    if (grid_hub < a.hub_wgs) a.hub_wgs = grid_hub;
+    const bool core = g->caps.core_bits != 0;
+    Shapes sh;
+    if (tc_status st = launch_shapes(ctx, g, pv, &sh)) return st;
+    if (sh.grid_hub < a.hub_wgs) a.hub_wgs = sh.grid_hub;
+    a.end = a.off + 1;
     HIP_TRY(ctx, tc::fill_u32(a.heads, 0, tc::kHeadWords, s));
     HIP_TRY(ctx, tc::fill_u32(d_totals, 0, 2 * (size_t)g->k, s));
     if (pv) {
@@ -476,23 +565,57 @@ tc_status count_into(tc_context* ctx, const tc_graph* g, uint64_t* d_totals, uin
     }
     const bool rec = record && ctx->timing;
     if (rec) HIP_TRY(ctx, hipEventRecord(ctx->ev[2], s));
-    if (hub) {
-        a.table_words = big_table_words(ctx);
-        a.hub_part = 0;
-        HIP_TRY(ctx, tc::count_launch(true, false, p.slots_per_bucket, pv, p.hash_kind, grid_hub, launch_threads(p, true),
-                                      launch_lds(ctx, p, true), a, s));
-        if (g->caps.mid_cap) {
-            a.table_words = mid_table_words(ctx);
-            a.hub_part = 1;
-            HIP_TRY(ctx, tc::count_launch(true, false, p.slots_per_bucket, pv, p.hash_kind, grid_mid,
-                                          64 * tc::kMidWaves, ctx->mid_lds_bytes, a, s));
+    // The bucket kernels over one set of bins.
+    auto buckets = [&]() -> tc_status {
+        if (hub) {
+            a.table_words = big_table_words(ctx);
             a.hub_part = 0;
+            HIP_TRY(ctx, tc::count_launch(true, false, p.slots_per_bucket, pv, p.hash_kind, sh.grid_hub,
+                                          launch_threads(p, true), launch_lds(ctx, p, true), a, s));
+            if (g->caps.mid_cap) {
+                a.table_words = mid_table_words(ctx);
+                a.hub_part = 1;
+                HIP_TRY(ctx, tc::count_launch(true, false, p.slots_per_bucket, pv, p.hash_kind, sh.grid_mid,
+                                              64 * tc::kMidWaves, ctx->mid_lds_bytes, a, s));
+                a.hub_part = 0;
+            }
         }
+        a.table_words = wg_table_words(p);
+        HIP_TRY(ctx, tc::count_launch(false, a.subwave != 0, p.slots_per_bucket, pv, p.hash_kind, sh.grid,
+                                      launch_threads(p, false), p.wg_lds_bytes, a, s));
+        return TC_OK;
+    };
+    if (core) {
+        tc::CoreArgs c{};
+        c.meta = a.meta;
+        c.off = a.off;
+        c.col = a.col;
+        c.items = a.items;
+        c.blk = g->dev.blk;
+        c.bl = g->dev.bl;
+        c.heads = a.heads;
+        c.total = a.total;
+        c.tv = a.tv;
+        c.n = g->n;
+        c.S = g->caps.core_bits;
+        c.c0 = g->caps.core_first;
+        c.magic = tc::core_magic(c.S);
+        c.big_all = g->caps.core_big_all ? 1u : 0u;
+        c.shard = shard;
+        c.shards = shards;
+        a.core = c.big_all ? 1u : 2u;
+        for (int part = 2; part >= 0; --part)
+            if (sh.grid_core[part]) HIP_TRY(ctx, tc::core_launch(part, pv, sh.grid_core[part], c, s));
     }
-    a.table_words = wg_table_words(p);
-    HIP_TRY(ctx, tc::count_launch(false, a.subwave != 0, p.slots_per_bucket, pv, p.hash_kind, grid,
-                                  launch_threads(p, false),
-                                  p.wg_lds_bytes, a, s));
+    if (tc_status st = buckets()) return st;
+    if (core && g->caps.core_first) {  // the core owners' triangles outside the core
+        a.core = 0;
+        a.meta = g->dev.rest_meta;
+        a.items = g->dev.rest_items;
+        a.end = g->dev.rend;
+        a.heads += 1;  // other words of the same lines
+        if (tc_status st = buckets()) return st;
+    }
     if (rec) {
         HIP_TRY(ctx, hipEventRecord(ctx->ev[3], s));
         ctx->have_count = true;
@@ -1082,11 +1205,9 @@ tc_status tc_graph_count_replay(tc_context* ctx, tc_graph* g, uint64_t* d_totals
     if (!g->exec || std::memcmp(key, g->key, sizeof(key)) != 0) {
         drop_capture(g);
         if (!ctx->capture_stream) HIP_TRY(ctx, hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
-        int per_cu = 0;  // resolve launch shapes before capture (no attribute calls while capturing)
-        if (!g->empty) {
-            if (tc_status st = occupancy(ctx, g->p, d_per_vertex != nullptr, false, &per_cu)) return st;
-            if (needs_hub_launch(g))
-                if (tc_status st = occupancy(ctx, g->p, d_per_vertex != nullptr, true, &per_cu)) return st;
+        if (!g->empty) {  // resolve launch shapes before capture (no attribute calls while capturing)
+            Shapes sh;
+            if (tc_status st = launch_shapes(ctx, g, d_per_vertex != nullptr, &sh)) return st;
         }
         HIP_TRY(ctx, hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
         tc_status st = count_into(ctx, g, d_totals, d_per_vertex, d_scratch, L, ctx->capture_stream, false);

@@ -45,26 +45,18 @@
 // non-zero tallies go to the per-vertex array with one global atomic each.
 #include <type_traits>
 
+#include "tc_fetch.h"
 #include "tc_internal.h"
 #include "tc_wave.h"
 
 namespace tc {
 namespace {
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <bool WG>
 __device__ __forceinline__ void group_sync() {
     if constexpr (WG) __syncthreads();
     else wave_sync();
 }
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int S>
 struct Bucket {
@@ -105,12 +97,6 @@ __device__ __forceinline__ unsigned long long ballot_has(const Bucket<S>& v, uin
 #pragma unroll
     for (int j = 1; j < S; ++j) m |= __ballot(v.v[j] == w);
     return m;
-}
-
-// This lane's bit of a wave mask, as a lane predicate (the mask itself is the predicate: no vector
-// shift, and, or compare of the 64-bit value).
-__device__ __forceinline__ bool lane_in(unsigned long long mask) {
-    return __builtin_amdgcn_inverse_ballot_w64(mask);
 }
 
 // Byte offset of w within a bucket that contains it (j * 4).
@@ -177,11 +163,6 @@ struct Probe {
     uint32_t flog;         // log2 of the filter's words
     uint32_t* queue;       // this wavefront's queue: entries {id, k}, kQueueEntries then 64 dummies
 };
-
-// This lane's position among the set lanes of a wave mask (number of set lanes below it).
-__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 
 template <int S, bool PV>
 __device__ __forceinline__ void tally_hit(const Probe& pr, uint32_t s, uint32_t k) {
@@ -538,7 +519,7 @@ __device__ __forceinline__ void list_of(const CountArgs& a, uint32_t w, uint32_t
         start = p + 1u;
     } else {
         start = a.off[w];
-        len = a.off[w + 1] - start;
+        len = a.end[w] - start;
     }
 }
 
@@ -854,6 +835,7 @@ __device__ __forceinline__ CountArgs graph_view(const CountArgs& a, const MultiD
     CountArgs v = a;
     v.meta = d.meta;
     v.off = d.off;
+    v.end = d.off + 1;
     v.col = d.col;
     v.items = d.items;
     v.gid = d.gid;
@@ -870,46 +852,6 @@ __device__ __forceinline__ uint32_t bin_base(const GraphMeta* m, uint32_t bin) {
     for (uint32_t i = 0; i < bin; ++i) b += m->bins[i];
     return b;
 }
-
-// Guided fetches of a wavefront bin (largest work first): the first `waves` fetches take `unit` items
-// each, the next `waves` twice as many, and so on up to `cap` items per fetch.  With `cap` from the start
-// one wavefront took the 16 (packed: 64) heaviest vertices of the bin one after another: R-MAT scale 16
-// spent 1.57 ms in a chain of 16 vertices of 3e4 probes, Barabasi-Albert with 1000 vertices ran on 16
-// wavefronts.
-struct Guided {
-    uint32_t n, waves, unit, cap, levels, level0;  // level0: items the doubling levels take
-    __device__ __forceinline__ Guided(uint32_t n_, uint32_t waves_, uint32_t unit_, uint32_t cap_)
-        : n(n_), waves(waves_ < 65536u ? waves_ : 65536u), unit(unit_), cap(cap_), levels(0) {
-        while ((unit << levels) < cap) ++levels;  // sizes unit << l below cap
-        level0 = unit * waves * ((1u << levels) - 1u);
-    }
-    __device__ __forceinline__ Guided(uint32_t n_, uint32_t waves_, uint32_t unit_, uint32_t cap_, uint32_t levels_)
-        : n(n_), waves(waves_ < 65536u ? waves_ : 65536u), unit(unit_), cap(cap_), levels(levels_) {
-        level0 = unit * waves * ((1u << levels) - 1u);
-    }
-    __device__ __forceinline__ uint32_t fetches() const {
-        if (n > level0) return levels * waves + (n - level0 + cap - 1) / cap;
-        uint32_t f = 0, left = n;
-        for (uint32_t l = 0; left; ++l) {
-            const uint32_t size = unit << l, most = (left + size - 1) / size;
-            const uint32_t take = most < waves ? most : waves;
-            f += take;
-            left = most <= waves ? 0u : left - waves * size;
-        }
-        return f;
-    }
-    __device__ __forceinline__ void range(uint32_t f, uint32_t& j0, uint32_t& j1) const {
-        const uint32_t l = f / waves;
-        uint32_t size = cap;
-        if (l < levels) {
-            size = unit << l;
-            j0 = unit * waves * ((1u << l) - 1u) + (f - l * waves) * size;
-        } else {
-            j0 = level0 + (f - levels * waves) * cap;
-        }
-        j1 = j0 + size < n ? j0 + size : n;
-    }
-};
 
 // Wavefront total of a multi-graph launch: hits of single graphs accumulate in `acc` while they
 // belong to the same graph and go to that graph's total when the wavefront moves to another one.
@@ -930,7 +872,7 @@ __device__ __forceinline__ void process_wg(const CountArgs& a, uint32_t u, uint3
     u = __builtin_amdgcn_readfirstlane(u);
     if (!in_shard(a, u)) return;
     const int64_t beg = own_start(a, u);
-    const uint32_t d = __builtin_amdgcn_readfirstlane(a.off[u + 1] - a.off[u]);
+    const uint32_t d = __builtin_amdgcn_readfirstlane(a.end[u] - a.off[u]);
     process<S, PV, HK, true, DEFER, NoMid, SW>(a, u, beg, d, tbl, avail, tid, blockDim.x, wave, nw, lane, s_wsum, acc,
                                                queue, false, 0u, 0u, 0u, NoMid{}, part, parts);
 }
@@ -980,7 +922,10 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
         n_hub = a.meta->bins[0];
         base1 = n_hub;  // bin 1 follows bin 0 in the item order
         hi1 = a.meta->big_full;
+        const bool core = a.core && core_on(*a.meta);  // bin 1, or its half-LDS part, goes to the core launches
+        if (core && a.core == 1) hi1 = 0;
         if (a.hub_part) {
+            if (core) return;
             n_hub = 0;
             lo1 = hi1;
             hi1 = a.meta->bins[1];
@@ -1058,6 +1003,11 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
         n_wg = a.meta->bins[2];
         n_wave = a.meta->bins[3];
         n_pack = a.meta->bins[4];
+        if (a.core && core_on(*a.meta)) {  // those go to the core launches
+            n_before += n_wg + a.meta->heavy3;
+            n_wg = 0;
+            n_wave -= a.meta->heavy3;
+        }
     }
 
     uint32_t* const queue = lds + a.table_words + (size_t)wave * kQueueWords;  // this wavefront's probe queue
@@ -1185,7 +1135,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
             if ((uint32_t)lane < cnt) {
                 vu = v.items[base + b0 + lane];
                 vb = own_start(v, vu);
-                vd = v.off[vu + 1] - v.off[vu];
+                vd = v.end[vu] - v.off[vu];
             }
             // Two-stage prefetch for lists of at most 64: the next vertex's list is loaded while
             // this one's table is built, and its elements' list bounds while this one is probed.
@@ -1237,7 +1187,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) 
                 if ((uint32_t)lane < cnt) {
                     vu = v.items[base + b0 + lane];
                     vb = own_start(v, vu);
-                    vd = v.off[vu + 1] - v.off[vu];
+                    vd = v.end[vu] - v.off[vu];
                 }
                 for (uint32_t i = 0; i < cnt;) {
                     uint32_t n16 = 0;

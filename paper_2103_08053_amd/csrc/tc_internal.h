@@ -40,9 +40,26 @@ struct GraphMeta {
     unsigned int bins[6];
     unsigned int wave_cands, pack_cands;  // census before binning: wavefront-size tables, and packable ones
     unsigned long long bin_work[6];       // sum of W(u) over the vertices of each bin
-    unsigned int pad[36];
+    // core path (0 when the graph is not laid out for it): owners of the wavefront bin with W(u) at least
+    // kCoreMinWork (the first of the bin), work of all owners the path would take, edges into the core
+    unsigned int heavy3, pad0;
+    unsigned long long heavy_work, core_edges;
+    unsigned int pad[30];
 };
 static_assert(sizeof(GraphMeta) == 256, "meta is one 256-byte block");
+
+// Core path (tc_core.hip): lists' ids among the last ranks as words of a block index above a mask of S
+// ids.  It takes the owners of the workgroup bin, those of the large-LDS bin whose out-degree a table
+// entry can index, and those of the wavefront bin with W(u) >= kCoreMinWork; the core is the last
+// S << (32 - S) ranks (all of them where n is smaller).
+constexpr uint32_t kCoreMinBits = 20;
+constexpr uint64_t kCoreMinWork = 1024;
+__host__ __device__ inline bool core_on(const GraphMeta& m) {
+    return m.heavy_work > 0 && 2 * m.heavy_work >= m.wplus && 4 * m.core_edges >= m.m;
+}
+// First quad (16 bytes) of row r's block words when its list starts at col[off]: rows in order, each
+// with room for one word per id padded to whole quads (ceil4(d) <= d + 3).
+__host__ __device__ inline uint64_t core_start(uint32_t off, uint32_t r) { return ((uint64_t)off + 3ull * r + 3) / 4; }
 
 // Hash-table geometry for a vertex with d out-neighbours, shared by the host
 // (capacity per bin) and the kernels (layout in LDS or in global memory).
@@ -185,6 +202,12 @@ struct GraphDev {
                         // r's record at p(r) holds d+(r), then rec_id(p(v)) of each out-neighbour v
     uint32_t* place;    // [2 (n + 1)] record layout: {p(r), d+(r)} of every rank r; entry n holds the
                         // records' extent (words up to the end of the last one)
+    // core path only, else null
+    uint4* blk;         // [core_start(m_in, n)] block words of every list
+    uint2* bl;          // [n] {first quad, quads} of each list's block words
+    uint32_t* rend;     // [n] end of each list's ids outside the core (they come first)
+    GraphMeta* rest_meta;  // bins of the lists cut at rend
+    uint32_t* rest_items;  // [n]
 };
 
 // Batch description for the build (device arrays of k + 1 offsets).
@@ -218,6 +241,10 @@ struct BinCaps {
     uint32_t pack_cap;  // out-degree limit of the packed bin (0: no packing)
     bool force_wg, force_hub, force_big, lpt, scatter_csr;
     bool records;       // build the record layout (GraphDev::rec)
+    // core path: ids per block word (0: not laid out), first rank of the core, and whether every owner of
+    // the large-LDS bin takes it (else only those counted with half a CU's LDS)
+    uint32_t core_bits, core_first;
+    bool core_big_all;
     uint32_t order;  // hash-id order: 0 (degree, id) rank, 1 in-degree, 2 collective degree
 };
 
@@ -236,13 +263,16 @@ __host__ __device__ inline uint32_t rec_id(uint32_t p) { return p ^ ((p >> 5) & 
 struct Layout {
     size_t storage, temp, scratch;
     // storage offsets
-    size_t s_meta, s_off, s_off32, s_col, s_rank, s_items, s_gid, s_rec, s_place;
+    size_t s_meta, s_off, s_off32, s_col, s_rank, s_items, s_gid, s_rec, s_place, s_blk, s_bl, s_rend, s_rmeta,
+        s_ritems;
     // temp offsets
     size_t t_keys_a, t_keys_b, t_aux, t_deg, t_dplus, t_order, t_skey_a, t_skey_b, t_rk_a, t_rk_b, t_off2, t_place,
         t_sort;
     size_t sort_tmp_bytes;
     bool relabel;  // temp holds the relabelling arrays
     bool records;  // storage holds the record layout, per-vertex scratch is indexed by record id
+    uint32_t core_bits, core_first;  // storage holds the core path's layout (BinCaps)
+    bool core_big_all;
     // scratch offsets
     size_t c_tv, c_heads, c_total, c_hub;
     uint64_t hub_words;
@@ -293,8 +323,11 @@ struct CountArgs {
     const MultiHeader* multi;        // several graphs (per-graph fields below come from its descriptors)
     const GraphMeta* meta;
     const uint32_t* off;  // [n + 1] 32-bit CSR offsets (half the cache footprint of the 64-bit ones)
+    const uint32_t* end;  // [n] ends of the lists (off + 1, or where they are cut)
     const uint32_t* col;
     const uint32_t* items;
+    uint32_t core;                   // core launches count the owners they take (when core_on): 1 all of
+                                     // bin 1, 2 its half-LDS part; 0 no such launches
     uint32_t* heads;                 // [kHeadWords] queue heads (zeroed before the launches)
     unsigned long long* total;       // [1] (zeroed before launch); single-graph mode
     const uint32_t* gid;             // [n] graph of each rank (batch mode), or null
@@ -325,7 +358,7 @@ struct CountArgs {
 size_t prep_sort_tmp_bytes(uint32_t n, uint64_t m_in);
 hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint32_t* dst,
                       const GraphDev& g, const BuildTemp& t, const BinCaps& caps, const BatchIn* batch,
-                      hipStream_t stream);
+                      int cu_count, hipStream_t stream);
 hipError_t fill_u32(void* p, uint32_t value, size_t words, hipStream_t stream);
 // out[x] = tv[id(rank[x])] with id(r) = r, or the record id rec_id(place[2r]) when place is given.
 hipError_t gather_per_vertex(const unsigned long long* tv, const uint32_t* rank, uint32_t n, const uint32_t* place,
@@ -333,6 +366,42 @@ hipError_t gather_per_vertex(const unsigned long long* tv, const uint32_t* rank,
 // Zeroes the record layout's per-vertex staging at every record's start (place[2r], r < n): the only
 // entries a count adds to.
 hipError_t clear_record_staging(unsigned long long* tv, const uint32_t* place, uint32_t n, hipStream_t stream);
+
+// tc_core.hip
+struct CoreBuild {
+    const GraphMeta* meta;
+    const uint32_t* off;                 // [n + 1]
+    const unsigned long long* okeys;     // sorted oriented keys (head in the bits of mask)
+    unsigned long long mask;
+    uint32_t* col;
+    uint32_t* blk;
+    uint2* bl;
+    uint32_t* rend;
+    const uint32_t* items;
+    GraphMeta* rest_meta;
+    uint32_t* rest_items;
+    uint32_t* cls;                       // [n] temporary
+    uint32_t* hist;                      // [320] temporary
+    uint32_t n, S, c0, magic;
+    bool big_all;
+    BinCaps caps;
+};
+struct CoreArgs {
+    const GraphMeta* meta;
+    const uint32_t* off;
+    const uint32_t* col;
+    const uint32_t* items;
+    const uint4* blk;
+    const uint2* bl;
+    uint32_t* heads;
+    unsigned long long* total;
+    unsigned long long* tv;
+    uint32_t n, S, c0, magic, dcap, big_all, shard, shards;
+};
+inline uint32_t core_magic(uint32_t S) { return (uint32_t)(((1ull << 32) + S - 1) / S); }  // x / S = umulhi(x, magic), x < 2^26
+hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream);
+hipError_t core_info(int part, bool pv, uint32_t S, int* blocks_per_cu);
+hipError_t core_launch(int part, bool pv, uint32_t grid, CoreArgs a, hipStream_t stream);
 
 // tc_diag.hip: per-table collision statistics of a built graph (the cost model of Equation 2) for
 // the tables the count kernels build; avail[bin] = table words of bins 0-4.  stats = {phi,

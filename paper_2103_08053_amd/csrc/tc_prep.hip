@@ -21,6 +21,7 @@
 //     rec_id(p(v)) of each out-neighbour v; records go in rank order, a short one moved to the next
 //     128-byte line where it would straddle one (placed first, written during the scan of step 6,
 //     which gathers d+(v) anyway);
+//  7. the core path's block words and the schedule of the lists cut before the core (tc_core.hip).
 //  6. scheduling (Section 4.3): out-degree d+ and collective work
 //     W(u) = sum of d+(v) over out-neighbours v (the collective degree of
 //     Equation 2); vertices with d+ < 2 or W = 0 are skipped, the rest go by
@@ -450,8 +451,10 @@ __global__ void k_pack_census(const int64_t* __restrict__ off, const unsigned lo
 // the vertices whose tables need more than half a CU's LDS (counted by one workgroup per CU), then
 // those up to caps.mid_cap (two workgroups per CU); the work field there takes 23 bits.
 __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long long* __restrict__ wscan, uint32_t n,
-                           BinCaps caps, GraphMeta* meta, uint32_t* __restrict__ skey, uint32_t* __restrict__ rec,
+                           BinCaps caps, GraphMeta* meta, uint32_t* skey, uint32_t* __restrict__ rec,
                            const uint32_t* __restrict__ place) {
+    __shared__ unsigned long long s_hw, s_ce;
+    __shared__ unsigned int s_h3;
     __shared__ unsigned long long s_w;
     __shared__ unsigned int s_max, s_bins[6], s_full;
     __shared__ unsigned long long s_bw[6];
@@ -459,7 +462,7 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
         s_bins[threadIdx.x] = 0;
         s_bw[threadIdx.x] = 0;
     }
-    if (threadIdx.x == 0) { s_w = 0; s_max = 0; s_full = 0; }
+    if (threadIdx.x == 0) { s_w = 0; s_max = 0; s_full = 0; s_hw = 0; s_ce = 0; s_h3 = 0; }
     __syncthreads();
     const unsigned long long kWorkMax = (1ull << 24) - 1;  // larger work ties: LPT order is a heuristic
     const unsigned long long kWorkMax1 = (1ull << 23) - 1;  // bin 1: below the part bit
@@ -468,6 +471,8 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
     unsigned long long wsum = 0;
     uint32_t dmax = 0, nb0 = 0, nb1 = 0, nb2 = 0, nb3 = 0, nb4 = 0, nb5 = 0, nfull = 0;
     unsigned long long bw[6] = {0, 0, 0, 0, 0, 0};
+    unsigned long long hw = 0, ce = 0;
+    uint32_t h3 = 0;
     for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
         const int64_t b = off[r], e = off[r + 1];
         const uint32_t d = (uint32_t)(e - b);
@@ -480,6 +485,12 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
         else if (caps.force_wg || d > caps.wave_cap) bin = 2;
         else if (d <= pack_cap && w <= kPackMaxWork) bin = 4;
         else bin = 3;
+        if (caps.core_bits) {  // skey[r] still holds r's degree: deg - d+ edges end in r
+            if (r >= caps.core_first) ce += skey[r] - d;
+            const bool h = bin == 3 && w >= kCoreMinWork;
+            h3 += h;
+            if (h || bin == 2 || (bin == 1 && (caps.core_big_all || d <= caps.mid_cap))) hw += w;
+        }
         if (bin == 1) {
             const uint32_t half = d <= caps.mid_cap ? 1u : 0u;
             const unsigned long long wk = w > kWorkMax1 ? kWorkMax1 : w;
@@ -513,8 +524,16 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
         nb4 += __shfl_xor(nb4, o);
         nb5 += __shfl_xor(nb5, o);
         nfull += __shfl_xor(nfull, o);
+        if (caps.core_bits) {
+            hw += __shfl_xor(hw, o);
+            ce += __shfl_xor(ce, o);
+            h3 += __shfl_xor(h3, o);
+        }
     }
     if ((threadIdx.x & 63) == 0) {
+        if (hw) atomicAdd(&s_hw, hw);
+        if (ce) atomicAdd(&s_ce, ce);
+        if (h3) atomicAdd(&s_h3, h3);
         atomicAdd(&s_w, wsum);
         atomicMax(&s_max, dmax);
         atomicAdd(&s_bins[0], nb0);
@@ -533,6 +552,9 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
         atomicAdd(&meta->wplus, s_w);
         atomicMax(&meta->max_dplus, s_max);
         if (s_full) atomicAdd(&meta->big_full, s_full);
+        if (s_hw) atomicAdd(&meta->heavy_work, s_hw);
+        if (s_ce) atomicAdd(&meta->core_edges, s_ce);
+        if (s_h3) atomicAdd(&meta->heavy3, s_h3);
         for (int i = 0; i < 6; ++i) atomicAdd(&meta->bins[i], s_bins[i]);
         for (int i = 0; i < 6; ++i)
             if (s_bw[i]) atomicAdd(&meta->bin_work[i], s_bw[i]);
@@ -764,7 +786,8 @@ hipError_t relabel(uint32_t n, const GraphDev& g, const BuildTemp& t, const Batc
 }
 
 hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint32_t* dst, const GraphDev& g,
-                      const BuildTemp& t, const BinCaps& caps, const BatchIn* batch, hipStream_t stream) {
+                      const BuildTemp& t, const BinCaps& caps, const BatchIn* batch, int cu_count,
+                      hipStream_t stream) {
     const uint32_t nb = id_bits(n);
     const unsigned long long sentinel = (2 * nb >= 64) ? ~0ull : ((1ull << (2 * nb)) - 1);
     size_t tmp = t.sort_tmp_bytes;
@@ -897,6 +920,30 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
     tmp = t.sort_tmp_bytes;
     TC_TRY(sort_pairs(t.sort_tmp, tmp, skey, reinterpret_cast<uint32_t*>(t.skey_b), g.items, (size_t)n, kScheduleBits,
                       stream));
+    // 7: block words of the core path and the schedule of the lists cut before the core.
+    if (caps.core_bits) {
+        CoreBuild c{};
+        c.meta = g.meta;
+        c.off = g.off32;
+        c.okeys = reinterpret_cast<const unsigned long long*>(t.aux);
+        c.mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
+        c.col = g.col;
+        c.blk = reinterpret_cast<uint32_t*>(g.blk);
+        c.bl = g.bl;
+        c.rend = g.rend;
+        c.items = g.items;
+        c.rest_meta = g.rest_meta;
+        c.rest_items = g.rest_items;
+        c.cls = t.order;
+        c.hist = t.deg;
+        c.n = n;
+        c.S = caps.core_bits;
+        c.c0 = caps.core_first;
+        c.magic = core_magic(c.S);
+        c.big_all = caps.core_big_all;
+        c.caps = caps;
+        TC_TRY(core_build(c, cu_count, stream));
+    }
     return hipSuccess;
 }
 

@@ -1,4 +1,5 @@
-// Wavefront-wide integer scan and sum on gfx9 DPP lane moves (no LDS traffic).
+// Wavefront-wide helpers: integer scan and sum on gfx9 DPP lane moves (no LDS traffic), lane masks, and
+// the ordering of a wavefront's own LDS accesses.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,6 +29,27 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
 // Sum over the 64 lanes (every lane active), as a uniform value.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Orders this wavefront's LDS accesses (its lanes run in lock step: no barrier is needed).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// This lane's bit of a wave mask, as a lane predicate (the mask itself is the predicate: no vector
+// shift, and, or compare of the 64-bit value).
+__device__ __forceinline__ bool lane_in(unsigned long long mask) {
+    return __builtin_amdgcn_inverse_ballot_w64(mask);
+}
+
+// This lane's position among the set lanes of a wave mask (number of set lanes below it).
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 }  // namespace tc
