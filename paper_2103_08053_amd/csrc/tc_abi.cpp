@@ -296,18 +296,20 @@ Layout layout(const tc_context* ctx, const tc_params& p, uint32_t n, uint64_t m_
     L.t_keys_a = o; o = align_up(o + 8 * (size_t)m_in);
     L.t_keys_b = o; o = align_up(o + 8 * (size_t)m_in);
     L.t_aux = o;    o = align_up(o + 8 * (size_t)m_in);
-    L.t_deg = o;    o = align_up(o + 4 * ((size_t)n + 1));
-    L.t_dplus = o;  o = align_up(o + 4 * ((size_t)n + 1));
+    L.zero = tc::prep_zero(n, m_in);
+    L.t_zero = o;   o = align_up(o + 4 * L.zero.words);
+    const bool scatter = (p.flags & TC_F_SCATTER_CSR) != 0;
     L.t_order = o;  o = align_up(o + 4 * (size_t)n);
     L.t_skey_a = o; o = align_up(o + 8 * (size_t)n);
     L.t_skey_b = o; o = align_up(o + 8 * (size_t)n);
     const bool relabel = (p.flags & (TC_F_ORDER_INDEGREE | TC_F_ORDER_COLLECTIVE)) != 0;
     L.relabel = relabel;
+    L.t_dplus = o;  o = align_up(o + (relabel || scatter ? 4 * ((size_t)n + 1) : 0));
     L.t_rk_a = o;   o = align_up(o + (relabel ? 8 * (size_t)n : 0));
     L.t_rk_b = o;   o = align_up(o + (relabel ? 8 * (size_t)n : 0));
     L.t_off2 = o;   o = align_up(o + (relabel ? 8 * ((size_t)n + 1) : 0));
     L.t_place = o;  o = align_up(o + (L.records ? 16 * (tc::place_chunks(n) + 1) : 0));
-    L.sort_tmp_bytes = align_up(tc::prep_sort_tmp_bytes(n, m_in));
+    L.sort_tmp_bytes = align_up(tc::prep_sort_tmp_bytes(n, relabel, scatter));
     L.t_sort = o;   o = align_up(o + L.sort_tmp_bytes);
     L.temp = o;
 
@@ -356,7 +358,11 @@ tc::BuildTemp temp_ptrs(void* temp, const Layout& L) {
     t.keys_a = reinterpret_cast<unsigned long long*>(b + L.t_keys_a);
     t.keys_b = reinterpret_cast<unsigned long long*>(b + L.t_keys_b);
     t.aux = reinterpret_cast<uint32_t*>(b + L.t_aux);
-    t.deg = reinterpret_cast<uint32_t*>(b + L.t_deg);
+    t.zero = reinterpret_cast<uint32_t*>(b + L.t_zero);
+    t.zero_words = L.zero.words;
+    t.deg = t.zero + L.zero.deg;
+    t.first = reinterpret_cast<unsigned long long*>(t.zero + L.zero.first);
+    t.status = reinterpret_cast<unsigned long long*>(t.zero + L.zero.status);
     t.dplus = reinterpret_cast<uint32_t*>(b + L.t_dplus);
     t.order = reinterpret_cast<uint32_t*>(b + L.t_order);
     t.skey_a = reinterpret_cast<unsigned long long*>(b + L.t_skey_a);
@@ -768,7 +774,8 @@ tc_status tc_create(int hip_device, const tc_params* p, tc_context** out) {
         c->lds_per_block_max = std::min(c->lds_per_block_max, prop.maxSharedMemoryPerMultiProcessor);
     {
         uint32_t static_lds = 0;
-        if (hipSetDevice(hip_device) != hipSuccess || tc::count_kernel_static_lds(&static_lds) != hipSuccess) {
+        if (hipSetDevice(hip_device) != hipSuccess || tc::prep_init() != hipSuccess ||
+            tc::count_kernel_static_lds(&static_lds) != hipSuccess) {
             delete c;
             return TC_E_DEVICE;
         }

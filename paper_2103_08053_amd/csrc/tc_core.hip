@@ -19,6 +19,8 @@
 //
 // Whether a graph takes this path is decided on the device (core_on): the owners with enough work must
 // hold at least half of W+, and a quarter of the edges must end in the core.
+#include <algorithm>
+
 #include "tc_fetch.h"
 #include "tc_internal.h"
 #include "tc_wave.h"
@@ -30,150 +32,206 @@ namespace {
 
 __device__ __forceinline__ uint32_t block_of(uint32_t x, uint32_t magic) { return __umulhi(x, magic); }
 
-constexpr uint32_t kBlockRows = 32;  // consecutive rows a wavefront takes at a time
+// Rows that lie within a tile of 2048 consecutive edges: an LDS hash table of (row in the tile, block)
+// collects the block masks, and the edge that brought a block writes its word once the masks are
+// complete; positions in the row come from prefix counts over one bit per edge.  No row waits for another:
+// one wavefront per row, each with a table of its own, took 0.96 ms at R-MAT 22 (4.2 M rows, a chain of LDS
+// accesses each) against 0.60 ms here with the rows that cross tiles.
+constexpr uint32_t kTileThreads = 512, kTileItems = 4, kTileEdges = kTileThreads * kTileItems;
+constexpr uint32_t kTileWords = kTileEdges / 64, kTileSlots = 2 * kTileEdges;  // 2^12
 
-template <int R>
-__device__ __forceinline__ void group_or_step(uint32_t idx, uint32_t own, uint32_t& all, bool& first, uint32_t at) {
-    if constexpr (R < 16) {  // row_ror:R: lane at receives from lane (at - R) mod 16
-        const uint32_t i = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)idx, 0x120 + R, 0xf, 0xf, false);
-        const uint32_t b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0x120 + R, 0xf, 0xf, false);
-        if (i == idx) {
-            all |= b;
-            first = first && at < (uint32_t)R;  // a sender at - R >= 0 is below this lane
+// Set bits of a tile's bit set before position p (pre: set bits before each word).
+__device__ __forceinline__ uint32_t bits_before(const unsigned long long* w, const uint32_t* pre, uint32_t p) {
+    if (p == kTileEdges) return pre[kTileWords];
+    return pre[p >> 6] + (uint32_t)__popcll(w[p >> 6] & ((1ull << (p & 63u)) - 1ull));
+}
+
+__global__ void __launch_bounds__(kTileThreads) k_core_tiles(CoreBuild a) {
+    __shared__ uint32_t s_key[kTileSlots], s_mask[kTileSlots];
+    __shared__ unsigned long long s_start[kTileWords], s_rest[kTileWords], s_new[kTileWords];
+    __shared__ uint32_t s_row[kTileWords + 1], s_prer[kTileWords + 1], s_pren[kTileWords + 1];
+    if (!core_on(*a.meta)) return;
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t m = a.meta->m;
+    const uint32_t S = a.S;
+    for (uint64_t base = blockIdx.x * (uint64_t)kTileEdges; base < m; base += (uint64_t)gridDim.x * kTileEdges) {
+        const uint32_t len = m - base < kTileEdges ? (uint32_t)(m - base) : kTileEdges;
+        uint32_t row[kTileItems], id[kTileItems];
+#pragma unroll
+        for (uint32_t i = 0; i < kTileItems; ++i) {
+            const uint32_t p = wave * (64u * kTileItems) + i * 64u + lane;
+            const unsigned long long k = a.okeys[base + (p < len ? p : len - 1)];
+            row[i] = (uint32_t)(k >> a.nb);
+            id[i] = (uint32_t)(k & a.mask);
         }
-        group_or_step<R + 1>(idx, own, all, first, at);
+        for (uint32_t i = tid; i < kTileSlots; i += kTileThreads) {
+            s_key[i] = kNone;
+            s_mask[i] = 0;
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kTileItems; ++i) {
+            const uint32_t p = wave * (64u * kTileItems) + i * 64u + lane;
+            uint32_t prev = (uint32_t)__shfl_up((int)row[i], 1, 64);
+            if (lane == 0 && base + p > 0 && p < len) prev = (uint32_t)(a.okeys[base + p - 1] >> a.nb);
+            const bool start = p < len && (base + p == 0 || prev != row[i]);
+            const unsigned long long st = __ballot(start), rs = __ballot(p < len && id[i] < a.c0);
+            if (lane == 0) {
+                s_start[wave * kTileItems + i] = st;
+                s_rest[wave * kTileItems + i] = rs;
+                s_new[wave * kTileItems + i] = 0;
+            }
+        }
+        // the tile's last row is closed when the next edge is another row's (or there is none)
+        const bool open = base + len < m &&
+                          (uint32_t)(a.okeys[base + len] >> a.nb) == (uint32_t)(a.okeys[base + len - 1] >> a.nb);
+        __syncthreads();
+        const unsigned long long starts = lane < kTileWords ? s_start[lane] : 0ull;
+        const unsigned long long has = __ballot(starts != 0);
+        if (wave == 0) {
+            const uint32_t c = (uint32_t)__popcll(starts), r = lane < kTileWords ? (uint32_t)__popcll(s_rest[lane]) : 0u;
+            const uint32_t ic = wave_incl_scan(c), ir = wave_incl_scan(r);
+            if (lane <= kTileWords) {
+                s_row[lane] = ic - c;
+                s_prer[lane] = ir - r;
+            }
+        }
+        __syncthreads();
+        if (!has) continue;  // uniform: the whole tile lies inside one row
+        const uint32_t w0 = (uint32_t)__builtin_ctzll(has), w1 = 63u - (uint32_t)__builtin_clzll(has);
+        const uint32_t p0 = w0 * 64u + (uint32_t)__builtin_ctzll(s_start[w0]);
+        const uint32_t stop = open ? w1 * 64u + 63u - (uint32_t)__builtin_clzll(s_start[w1]) : len;
+        // blocks: which edges bring one
+        uint32_t slot[kTileItems], first = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < kTileItems; ++i) {
+            const uint32_t p = wave * (64u * kTileItems) + i * 64u + lane;
+            slot[i] = 0;
+            if (p < p0 || p >= stop || id[i] < a.c0) continue;
+            const uint32_t g = bits_before(s_start, s_row, p) + ((s_start[p >> 6] >> (p & 63u)) & 1ull ? 1u : 0u);
+            const uint32_t x = id[i] - a.c0, idx = block_of(x, a.magic);
+            const uint32_t name = (g << (32 - S)) | idx;  // 12 bits of row, 12 at most of block
+            uint32_t at = (name * 0x9E3779B1u) >> 20;
+            for (;;) {
+                const uint32_t old = atomicCAS(&s_key[at], kNone, name);
+                if (old == kNone) first |= 1u << i;
+                if (old == kNone || old == name) break;
+                at = (at + 1) & (kTileSlots - 1);
+            }
+            slot[i] = at;
+            atomicOr(&s_mask[at], 1u << (x - idx * S));
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kTileItems; ++i) {
+            const unsigned long long f = __ballot((first >> i) & 1u);
+            if (lane == 0) s_new[wave * kTileItems + i] = f;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t c = lane < kTileWords ? (uint32_t)__popcll(s_new[lane]) : 0u;
+            const uint32_t ic = wave_incl_scan(c);
+            if (lane <= kTileWords) s_pren[lane] = ic - c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < kTileItems; ++i) {
+            const uint32_t p = wave * (64u * kTileItems) + i * 64u + lane;
+            if (p < p0 || p >= stop) continue;
+            // the row's edges [rs, re): the last start at or before p, the first after it
+            uint32_t w = p >> 6;
+            unsigned long long b = s_start[w] & ((2ull << (p & 63u)) - 1ull);
+            while (!b) b = s_start[--w];
+            const uint32_t rs = w * 64u + 63u - (uint32_t)__builtin_clzll(b);
+            uint32_t re = stop;
+            w = p >> 6;
+            b = (p & 63u) == 63u ? 0ull : s_start[w] & ~((2ull << (p & 63u)) - 1ull);
+            while (!b && ++w < kTileWords) b = s_start[w];
+            if (b) {
+                const uint32_t q = w * 64u + (uint32_t)__builtin_ctzll(b);
+                re = q < stop ? q : stop;
+            }
+            const uint32_t r0 = bits_before(s_rest, s_prer, rs), rests = bits_before(s_rest, s_prer, re) - r0;
+            const uint32_t rest_at = bits_before(s_rest, s_prer, p) - r0;
+            const bool rest = id[i] < a.c0;
+            const uint32_t off = (uint32_t)base + rs;
+            a.col[off + (rest ? rest_at : rests + (p - rs - rest_at))] = id[i];
+            const uint32_t n0 = bits_before(s_new, s_pren, rs);
+            uint32_t* const out = a.blk + 4 * core_start(off, row[i]);
+            if ((first >> i) & 1u) {
+                const uint32_t name = s_key[slot[i]];
+                out[bits_before(s_new, s_pren, p) - n0] = (name << S) | s_mask[slot[i]];  // the row's bits shift out
+            }
+            if (p == rs) {
+                const uint32_t nw = bits_before(s_new, s_pren, re) - n0;
+                for (uint32_t z = nw; z < ((nw + 3u) & ~3u); ++z) out[z] = 0;
+                a.bl[row[i]] = make_uint2((uint32_t)core_start(off, row[i]), (nw + 3u) / 4u);
+                a.rend[row[i]] = off + rests;
+            }
+        }
+        __syncthreads();  // the LDS is reused by the next tile
     }
 }
-// Within rows of 16 lanes: bits |= the bits of every lane with the same idx; first: no lane below has it.
-template <int R>
-__device__ __forceinline__ void group_or(uint32_t idx, uint32_t& bits, bool& first, uint32_t at) {
-    const uint32_t own = bits;
-    uint32_t all = own;
-    bool f = first;
-    group_or_step<R>(idx, own, all, f, at);
-    bits = all;
-    first = f;
-}
 
-// One wavefront per row: the row's core ids are ORed into the wavefront's LDS table of block masks; the
-// first lane to take a block's mask back (an exchange with zero, which also clears the table) writes its
-// word.  The row's ids go to col, those outside the core first.  Rows are short and the work per row is a
-// chain of LDS accesses, so the kernel lives from the number of wavefronts the tables (2^(32-S) words
-// each) leave room for.  Long rows are those of the last ranks: they go first.
-__global__ void __launch_bounds__(64) k_core_blocks(CoreBuild a) {
+// The other rows: those that cross a tile's end, one wavefront each (the wavefront of the tile where the row
+// begins), and those without edges.  The row's core ids are ORed into the wavefront's LDS table of block
+// masks (2^(32-S) words); the first lane to take a block's mask back (an exchange with zero, which also
+// clears the table) writes its word.  The row's ids go to col, those outside the core first.
+__global__ void __launch_bounds__(64) k_core_rows(CoreBuild a) {
     extern __shared__ __align__(16) uint32_t T[];
     if (!core_on(*a.meta)) return;
     const uint32_t lane = threadIdx.x, S = a.S, words = 1u << (32 - S);
+    for (uint64_t r = blockIdx.x * 64ull + lane; r < a.n; r += gridDim.x * 64ull) {
+        const uint32_t b = a.off[r];
+        if (a.off[r + 1] == b) {
+            a.bl[r] = make_uint2((uint32_t)core_start(b, (uint32_t)r), 0u);
+            a.rend[r] = b;
+        }
+    }
     for (uint32_t i = lane; i < words; i += 64) T[i] = 0;
     wave_sync();
-    const uint32_t batches = (a.n + kBlockRows - 1) / kBlockRows;
-    for (uint32_t t = blockIdx.x; t < batches; t += gridDim.x) {
-        const uint32_t r0 = (batches - 1 - t) * kBlockRows;
-        const uint32_t rows = a.n - r0 < kBlockRows ? a.n - r0 : kBlockRows;
-        uint32_t vb = 0, vd = 0, vq = 0, vr = 0;
-        if (lane < rows) {
-            vb = a.off[r0 + lane];
-            vd = a.off[r0 + lane + 1] - vb;
-        }
-        auto key = [&](uint32_t at) { return (uint32_t)(a.okeys[at] & a.mask); };
-        uint32_t ahead = 0;  // the next row's first 64 ids
-        {
-            const uint32_t b = __builtin_amdgcn_readlane(vb, 0), d = __builtin_amdgcn_readlane(vd, 0);
-            if (lane < d) ahead = key(b + lane);
-        }
-        for (uint32_t i = 0; i < rows; ++i) {
-            const uint32_t beg = __builtin_amdgcn_readlane(vb, i), d = __builtin_amdgcn_readlane(vd, i);
-            const uint32_t first = ahead;
-            if (i + 1 < rows) {
-                const uint32_t b = __builtin_amdgcn_readlane(vb, i + 1), dn = __builtin_amdgcn_readlane(vd, i + 1);
-                if (lane < dn) ahead = key(b + lane);
-            }
-            if (d <= 16) continue;
-            uint32_t* const out = a.blk + 4 * core_start(beg, r0 + i);
-            uint32_t rest = 0, cores = 0, nb = 0;
-            for (uint32_t c = 0; c < d; c += 64) {  // masks, and the ids outside the core
-                const bool act = c + lane < d;
-                const uint32_t id = c ? (act ? key(beg + c + lane) : 0u) : first;
-                const bool core = act && id >= a.c0;
-                if (core) {
-                    const uint32_t x = id - a.c0, idx = block_of(x, a.magic);
-                    atomicOr(&T[idx], 1u << (x - idx * S));
-                }
-                const unsigned long long rm = __ballot(act && !core);
-                if (act && !core) a.col[beg + rest + lanes_below(rm)] = id;
-                rest += (uint32_t)__popcll(rm);
-            }
-            wave_sync();
-            for (uint32_t c = 0; c < d; c += 64) {  // block words, and the core ids
-                const bool act = c + lane < d;
-                const uint32_t id = c ? (act ? key(beg + c + lane) : 0u) : first;
-                const bool core = act && id >= a.c0;
-                uint32_t word = 0;
-                if (core) {
-                    const uint32_t idx = block_of(id - a.c0, a.magic);
-                    const uint32_t m = atomicExch(&T[idx], 0u);
-                    if (m) word = (idx << S) | m;
-                }
-                const unsigned long long cm = __ballot(core), fm = __ballot(word != 0);
-                if (core) a.col[beg + rest + cores + lanes_below(cm)] = id;
-                if (word) out[nb + lanes_below(fm)] = word;
-                cores += (uint32_t)__popcll(cm);
-                nb += (uint32_t)__popcll(fm);
-            }
-            wave_sync();
-            const uint32_t pad = (0u - nb) & 3u;
-            if (lane < pad) out[nb + lane] = 0;
-            if (lane == i) {
-                vq = (nb + 3u) / 4u;
-                vr = rest;
-            }
-        }
-        // Rows of at most 16 ids, four at a time: 16 lanes hold a row, and a lane learns the ids of its block
-        // from the others' by row rotations; the lowest lane of a block writes its word.
-        const unsigned long long small = __ballot(vd > 0 && vd <= 16);
-        for (unsigned long long left = small; left;) {
-            uint32_t pick = 64;  // the row this lane's group takes
-#pragma unroll
-            for (uint32_t g = 0; g < 4; ++g)
-                if (left) {
-                    if ((lane >> 4) == g) pick = (uint32_t)__builtin_ctzll(left);
-                    left &= left - 1;
-                }
-            const uint32_t at = lane & 15u;
-            const uint32_t beg = (uint32_t)__shfl((int)vb, (int)(pick & 63u), 64);
-            const uint32_t dr = (uint32_t)__shfl((int)vd, (int)(pick & 63u), 64);  // every lane takes part
-            const uint32_t d = pick < 64 ? dr : 0u;
-            const bool act = at < d;
-            const uint32_t id = act ? key(beg + at) : 0u;
+    const uint64_t m = a.meta->m;
+    auto key = [&](uint64_t at) { return (uint32_t)(a.okeys[at] & a.mask); };
+    for (uint64_t e = (blockIdx.x + 1ull) * kTileEdges; e < m; e += (uint64_t)gridDim.x * kTileEdges) {
+        const uint32_t r = __builtin_amdgcn_readfirstlane((uint32_t)(a.okeys[e] >> a.nb));
+        const uint32_t beg = __builtin_amdgcn_readfirstlane(a.off[r]);
+        if (beg >= e || beg < e - kTileEdges) continue;  // begins here, or belongs to an earlier tile's end
+        const uint32_t d = __builtin_amdgcn_readfirstlane(a.off[r + 1]) - beg;
+        uint32_t* const out = a.blk + 4 * core_start(beg, r);
+        uint32_t rest = 0, cores = 0, nb = 0;
+        for (uint32_t c = 0; c < d; c += 64) {  // masks, and the ids outside the core
+            const bool act = c + lane < d;
+            const uint32_t id = act ? key((uint64_t)beg + c + lane) : 0u;
             const bool core = act && id >= a.c0;
-            const uint32_t x = id - a.c0, idx = core ? block_of(x, a.magic) : 0xFFFFFFFFu - at;
-            uint32_t bits = core ? 1u << (x - idx * S) : 0u;
-            bool first = core;
-            group_or<1>(idx, bits, first, at);
-            const unsigned long long rm = __ballot(act && !core), cm = __ballot(core), fm = __ballot(first);
-            const uint32_t sh = lane & 48u;
-            const uint32_t r16 = (uint32_t)(rm >> sh) & 0xFFFFu, c16 = (uint32_t)(cm >> sh) & 0xFFFFu;
-            const uint32_t f16 = (uint32_t)(fm >> sh) & 0xFFFFu, below = (1u << at) - 1u;
-            const uint32_t rest = (uint32_t)__popc(r16), nb = (uint32_t)__popc(f16);
-            if (act) a.col[beg + (core ? rest + (uint32_t)__popc(c16 & below) : (uint32_t)__popc(r16 & below))] = id;
-            uint32_t* const out = a.blk + 4 * core_start(beg, r0 + pick);
-            if (first) out[__popc(f16 & below)] = (idx << S) | bits;
-            if (d && at >= nb && at < ((nb + 3u) & ~3u)) out[at] = 0;
-            // back to the lane that holds the row
-            unsigned long long todo = __ballot(at == 0 && d != 0);
-            for (; todo; todo &= todo - 1) {
-                const int src = __builtin_ctzll(todo);
-                const uint32_t row = __builtin_amdgcn_readlane(pick, src);
-                const uint32_t q = (__builtin_amdgcn_readlane(nb, src) + 3u) / 4u, rr = __builtin_amdgcn_readlane(rest, src);
-                if (lane == row) {
-                    vq = q;
-                    vr = rr;
-                }
+            if (core) {
+                const uint32_t x = id - a.c0, idx = block_of(x, a.magic);
+                atomicOr(&T[idx], 1u << (x - idx * S));
             }
+            const unsigned long long rm = __ballot(act && !core);
+            if (act && !core) a.col[beg + rest + lanes_below(rm)] = id;
+            rest += (uint32_t)__popcll(rm);
         }
-        if (lane < rows) {
-            a.bl[r0 + lane] = make_uint2((uint32_t)core_start(vb, r0 + lane), vq);
-            a.rend[r0 + lane] = vb + vr;
+        wave_sync();
+        for (uint32_t c = 0; c < d; c += 64) {  // block words, and the core ids
+            const bool act = c + lane < d;
+            const uint32_t id = act ? key((uint64_t)beg + c + lane) : 0u;
+            const bool core = act && id >= a.c0;
+            uint32_t word = 0;
+            if (core) {
+                const uint32_t idx = block_of(id - a.c0, a.magic);
+                const uint32_t mk = atomicExch(&T[idx], 0u);
+                if (mk) word = (idx << S) | mk;
+            }
+            const unsigned long long cm = __ballot(core), fm = __ballot(word != 0);
+            if (core) a.col[beg + rest + cores + lanes_below(cm)] = id;
+            if (word) out[nb + lanes_below(fm)] = word;
+            cores += (uint32_t)__popcll(cm);
+            nb += (uint32_t)__popcll(fm);
+        }
+        wave_sync();
+        if (lane < ((0u - nb) & 3u)) out[nb + lane] = 0;
+        if (lane == 0) {
+            a.bl[r] = make_uint2((uint32_t)core_start(beg, r), (nb + 3u) / 4u);
+            a.rend[r] = beg + rest;
         }
     }
 }
@@ -712,10 +770,13 @@ hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream) {
     const uint32_t lds = 4u << (32 - a.S);
     const uint32_t cus = (uint32_t)(cu_count > 0 ? cu_count : 1);
     const uint32_t per_cu = 163840u / lds < 32u ? 163840u / lds : 32u;
-    const uint32_t batches = (a.n + kBlockRows - 1) / kBlockRows;
     TC_TRY(fill_u32(a.hist, 0, 2 * kRestClasses, stream));
     TC_TRY(fill_u32(a.rest_meta, 0, sizeof(GraphMeta) / 4, stream));
-    hipLaunchKernelGGL(k_core_blocks, dim3(batches < cus * per_cu ? batches : cus * per_cu), dim3(64), lds, stream, a);
+    const uint64_t tiles = (a.m_in + kTileEdges - 1) / kTileEdges;
+    hipLaunchKernelGGL(k_core_tiles, dim3((uint32_t)(tiles < 4ull * cus ? tiles : 4ull * cus)), dim3(kTileThreads), 0, stream, a);
+    TC_TRY(hipGetLastError());
+    const uint64_t rows = std::max<uint64_t>(tiles, ((uint64_t)a.n + 63) / 64);
+    hipLaunchKernelGGL(k_core_rows, dim3((uint32_t)(rows < cus * per_cu ? rows : cus * per_cu)), dim3(64), lds, stream, a);
     TC_TRY(hipGetLastError());
     if (a.c0 == 0) return hipSuccess;  // every rank is in the core: no cut lists
     const uint32_t per = 256 / kRestLanes, want = (a.n + per - 1) / per;

@@ -220,12 +220,16 @@ struct BatchIn {
 struct BuildTemp {
     unsigned long long* keys_a;
     unsigned long long* keys_b;
-    uint32_t* aux;       // [2 m_in]: sorted upper endpoints, then the sorted oriented keys
+    uint32_t* aux;       // [2 m_in]: partitioned upper endpoints, then the sorted oriented keys
+    uint32_t* zero;      // [zero_words] cleared at the start of a build: tickets, histograms, then:
+    size_t zero_words;
     uint32_t* deg;       // [n + 1]; reused as the fill cursor
-    uint32_t* dplus;     // [n + 1]
+    unsigned long long* first;   // a bit per sorted key: the first of a distinct edge
+    unsigned long long* status;  // look-back words of the sort passes
+    uint32_t* dplus;     // [n + 1] (relabelling and counting-sort builds)
     uint32_t* order;     // [n]
-    unsigned long long* skey_a;  // [n]
-    unsigned long long* skey_b;  // [n]
+    unsigned long long* skey_a;  // [n] degree << 32 | id by rank, then the schedule elements
+    unsigned long long* skey_b;  // [n] W by rank (and the other buffer of the vertex sorts)
     // relabelling (vertex orders other than the rank; null otherwise)
     unsigned long long* rk_a;    // [n]
     unsigned long long* rk_b;    // [n]
@@ -260,15 +264,20 @@ __host__ __device__ inline uint64_t record_words(uint32_t n, uint64_t m_in) { re
 // spread over hash buckets by their low bits.  Ids stay within p's 32-word line.
 __host__ __device__ inline uint32_t rec_id(uint32_t p) { return p ^ ((p >> 5) & 31u); }
 
+struct PrepZero {  // word offsets in BuildTemp::zero
+    size_t deg, first, status, words;
+};
+
 struct Layout {
     size_t storage, temp, scratch;
     // storage offsets
     size_t s_meta, s_off, s_off32, s_col, s_rank, s_items, s_gid, s_rec, s_place, s_blk, s_bl, s_rend, s_rmeta,
         s_ritems;
     // temp offsets
-    size_t t_keys_a, t_keys_b, t_aux, t_deg, t_dplus, t_order, t_skey_a, t_skey_b, t_rk_a, t_rk_b, t_off2, t_place,
+    size_t t_keys_a, t_keys_b, t_aux, t_zero, t_dplus, t_order, t_skey_a, t_skey_b, t_rk_a, t_rk_b, t_off2, t_place,
         t_sort;
     size_t sort_tmp_bytes;
+    PrepZero zero;
     bool relabel;  // temp holds the relabelling arrays
     bool records;  // storage holds the record layout, per-vertex scratch is indexed by record id
     uint32_t core_bits, core_first;  // storage holds the core path's layout (BinCaps)
@@ -355,7 +364,9 @@ struct CountArgs {
 };
 
 // tc_prep.hip
-size_t prep_sort_tmp_bytes(uint32_t n, uint64_t m_in);
+size_t prep_sort_tmp_bytes(uint32_t n, bool relabel, bool scatter);
+PrepZero prep_zero(uint32_t n, uint64_t m_in);
+hipError_t prep_init();
 hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint32_t* dst,
                       const GraphDev& g, const BuildTemp& t, const BinCaps& caps, const BatchIn* batch,
                       int cu_count, hipStream_t stream);
@@ -373,6 +384,7 @@ struct CoreBuild {
     const uint32_t* off;                 // [n + 1]
     const unsigned long long* okeys;     // sorted oriented keys (head in the bits of mask)
     unsigned long long mask;
+    uint32_t nb;                         // bits of a head; the row is above
     uint32_t* col;
     uint32_t* blk;
     uint2* bl;
@@ -383,6 +395,7 @@ struct CoreBuild {
     uint32_t* cls;                       // [n] temporary
     uint32_t* hist;                      // [320] temporary
     uint32_t n, S, c0, magic;
+    uint64_t m_in;
     bool big_all;
     BinCaps caps;
 };

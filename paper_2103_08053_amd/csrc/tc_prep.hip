@@ -4,36 +4,40 @@
 //     self-loops and out-of-range ids become a sentinel that sorts last
 //     (cleaning rules of the paper, Section 2.6: duplicates and self-loops
 //     removed, directed pairs read as undirected); single graphs form the
-//     keys as the sort reads its input;
-//  2. radix sort; distinct edges are the first keys of runs of equal keys
-//     (duplicates stay in place and are skipped downstream);
-//  3. degree of every vertex (distinct edges per run of equal lower ids, in
-//     the pass that flags the runs; runs of the sorted upper endpoints), then
-//     its rank in (degree, id) order;
+//     keys as the first sort pass reads its input;
+//  2. radix passes (tc_sort.h) over the top bits of the keys: all but at most 16 low bits of the upper
+//     id, so that equal keys meet in groups of equal top bits; k_dedup finds the first of each distinct
+//     key in its group (a bit per sample; duplicates stay in place and are skipped downstream) and
+//     counts the degrees of the lower ids (runs of equal ids);
+//  3. degrees of the upper ids: one partition pass by their top bits, then counters in LDS (k_upper_count);
+//     the rank in (degree, id) order from a radix sort of (degree, id);
 //  4. orientation by rank-by-degree (Section 2.2): the edge runs from the
 //     lower-ranked to the higher-ranked endpoint, and every id is replaced by
 //     its rank, so out-neighbour lists hold ranks and hashing the low bits of
 //     a rank spreads neighbours of similar degree over consecutive buckets
 //     (the reordering idea of Section 4.1; other orders are optional);
-//  5. CSR: stable radix sort of the oriented keys by row, row lengths from key
-//     runs, scan (int64 offsets);
+//  5. CSR: stable radix passes of the oriented keys by row; lists and offsets from the runs of equal rows;
 //  5c (optional): the record layout: rank r's record at p(r) holds d+(r) and then the record id
 //     rec_id(p(v)) of each out-neighbour v; records go in rank order, a short one moved to the next
-//     128-byte line where it would straddle one (placed first, written during the scan of step 6,
-//     which gathers d+(v) anyway);
-//  7. the core path's block words and the schedule of the lists cut before the core (tc_core.hip).
+//     128-byte line where it would straddle one (placed first, written by k_work, which reads d+(v)
+//     anyway);
 //  6. scheduling (Section 4.3): out-degree d+ and collective work
 //     W(u) = sum of d+(v) over out-neighbours v (the collective degree of
 //     Equation 2); vertices with d+ < 2 or W = 0 are skipped, the rest go by
 //     d+ to a global-memory-table bin, a large-LDS bin, a workgroup bin, a
 //     wavefront bin or (light vertices, when they dominate) a packed bin, and
-//     each bin is ordered by decreasing W (largest work first).
+//     each bin is ordered by decreasing W (largest work first);
+//  7. the core path's block words and the schedule of the lists cut before the core (tc_core.hip).
+//
+// Every histogram of digits is counted by the kernel that makes the keys, and a pass forms its keys as it
+// loads them, so the sorts add nothing but their passes.
 #include <algorithm>
 #include <cstring>
 
 #include <rocprim/rocprim.hpp>
 
 #include "tc_internal.h"
+#include "tc_sort.h"
 
 namespace tc {
 namespace {
@@ -53,44 +57,6 @@ inline uint32_t id_bits(uint32_t n) {  // bits to hold any id < n (at least 1)
     return b;
 }
 
-// Key sorts of the build over m_in samples.  64-bit keys sort in onesweep passes of 9-bit digits
-// (1024-thread blocks, 8 keys per thread): on gfx950 this beat the library's default 8-bit passes
-// at every size measured (44 bits of 2^26 keys 2.03 vs 2.44 ms, 50 bits of 2^29 keys 19.3 vs
-// 22.1 ms, rows-only 25 bits of 2^29 keys 10.3 vs 13.3 ms).  32-bit keys take 9-bit digits (16 keys
-// per thread) only where that saves a pass (26 bits of 2^29 keys 8.1 vs 9.8 ms; at 23 bits the
-// default's three passes are faster).  The size query takes the same path as the sort.
-using Onesweep9x64 = rocprim::radix_sort_config<
-    rocprim::default_config, rocprim::default_config,
-    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 8>, rocprim::kernel_config<1024, 8>, 9,
-                                        rocprim::block_radix_rank_algorithm::match>>;
-using Onesweep9x32 = rocprim::radix_sort_config<
-    rocprim::default_config, rocprim::default_config,
-    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<1024, 16>, rocprim::kernel_config<1024, 16>, 9,
-                                        rocprim::block_radix_rank_algorithm::match>>;
-
-template <typename In>
-hipError_t sort_keys(void* tmp, size_t& bytes, In in, unsigned long long* out, size_t count, uint32_t lo, uint32_t hi,
-                     hipStream_t stream) {
-    return rocprim::radix_sort_keys<Onesweep9x64>(tmp, bytes, in, out, count, lo, hi, stream);
-}
-
-hipError_t sort_keys(void* tmp, size_t& bytes, uint32_t* in, uint32_t* out, size_t count, uint32_t lo, uint32_t hi,
-                     hipStream_t stream) {
-    const uint32_t bits = hi - lo;
-    if ((bits + 8) / 9 < (bits + 7) / 8)
-        return rocprim::radix_sort_keys<Onesweep9x32>(tmp, bytes, in, out, count, lo, hi, stream);
-    return rocprim::radix_sort_keys(tmp, bytes, in, out, count, lo, hi, stream);
-}
-
-// 32-bit keys with their original positions as values (per-vertex sorts), by the same rule.
-hipError_t sort_pairs(void* tmp, size_t& bytes, uint32_t* kin, uint32_t* kout, uint32_t* vout, size_t count,
-                      uint32_t hi, hipStream_t stream) {
-    const auto pos = rocprim::counting_iterator<uint32_t>(0);
-    if ((hi + 8) / 9 < (hi + 7) / 8)
-        return rocprim::radix_sort_pairs<Onesweep9x32>(tmp, bytes, kin, kout, pos, vout, count, 0, hi, stream);
-    return rocprim::radix_sort_pairs(tmp, bytes, kin, kout, pos, vout, count, 0, hi, stream);
-}
-
 // Bits of any vertex degree: at most min(n - 1, 2 m_in).
 uint32_t degree_bits(uint32_t n, uint64_t m_in) {
     const uint64_t dmax = (uint64_t)n - 1 < 2 * m_in ? (uint64_t)n - 1 : 2 * m_in;
@@ -99,62 +65,121 @@ uint32_t degree_bits(uint32_t n, uint64_t m_in) {
     return b;
 }
 
-constexpr uint32_t kScheduleBits = 27;  // schedule keys: bin (0-5) << 24 | 24-bit reversed work
+// Canonical keys: passes over all but at most kGroupBits low bits (k_dedup tells the keys of a group of
+// equal top bits apart by those): R-MAT 22 takes four passes instead of five, 2^25 ids four instead of six.
+constexpr uint32_t kGroupBits = 16;
+inline uint32_t canon_passes(uint32_t nb) {
+    const uint32_t bits = 2 * nb > kGroupBits ? 2 * nb - kGroupBits : 1;
+    return (bits + kDigit - 1) / kDigit;
+}
+inline uint32_t canon_low(uint32_t nb) {  // low bits that the passes leave out
+    const uint32_t bits = canon_passes(nb) * kDigit;
+    return 2 * nb > bits ? 2 * nb - bits : 0;
+}
+inline uint32_t row_passes(uint32_t nb) { return (nb + kDigit - 1) / kDigit; }
 
-// Canonical key of sample i, formed as the sort reads its input (its key histogram reads the samples,
-// its first step stores the keys in its own buffer); an out-of-range id raises the range error and
-// gives the sentinel.
+// Upper ids: partitioned by their top bits (a digit of 9 or 10 bits) so that a partition's counters,
+// 2^15 at most at a time, fit in LDS.  No partition up to 15 bits; from 28 bits on one atomic per edge.
+constexpr uint32_t kCounterBits = 15;
+inline uint32_t upper_digit(uint32_t nb) { return nb <= kCounterBits ? 0u : nb <= 24 ? 9u : nb <= 27 ? 10u : 0u; }
+inline bool upper_atomics(uint32_t nb) { return nb > 27; }
+
+
+// Digit histograms of the build's passes (512 words each; the upper ids' has 1024) and their tickets.
+constexpr uint32_t kMaxPasses = 6 + 4 + 4 + 2;
+constexpr uint32_t kHistWords = kMaxPasses * 512 + 1024;
+constexpr uint32_t kTicketWords = 64;
+
+// Canonical key of sample i (a self-loop or out-of-range id gives the sentinel).
 struct CanonKey {
+    typedef uint2 Raw;
     const uint32_t* src;
     const uint32_t* dst;
     uint32_t n, nb;
     unsigned long long sentinel;
-    GraphMeta* meta;
-    __device__ unsigned long long operator()(uint64_t i) const {
-        const uint32_t a = src[i], b = dst[i];
-        if (a >= n || b >= n) {
-            if (!meta->err) atomicOr(&meta->err, 1u);
-            return sentinel;
-        }
-        if (a == b) return sentinel;
-        const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
-        return ((unsigned long long)lo << nb) | hi;
+    __device__ Raw raw(uint64_t i) const { return make_uint2(src[i], dst[i]); }
+    __device__ bool make(Raw r, uint32_t, unsigned long long& key) const {
+        const uint32_t lo = r.x < r.y ? r.x : r.y, hi = r.x < r.y ? r.y : r.x;
+        key = (hi >= n || lo == hi) ? sentinel : ((unsigned long long)lo << nb) | hi;
+        return true;
     }
 };
 
-// d+(col[e]) for edge e (0 past the last edge), for the collective-degree scan.
-struct HeadOutDegree {
-    const uint32_t* col;
-    const uint32_t* dplus;
-    const GraphMeta* meta;
-    __device__ unsigned long long operator()(uint64_t e) const {
-        return e < meta->m ? (unsigned long long)dplus[col[e]] : 0ull;
+struct LoadKey {
+    typedef unsigned long long Raw;
+    const unsigned long long* keys;
+    __device__ Raw raw(uint64_t i) const { return keys[i]; }
+    __device__ bool make(Raw r, uint32_t, unsigned long long& key) const {
+        key = r;
+        return true;
     }
 };
 
-// Record layout: for edge e (row r, head v: the sorted oriented key r << nb | v) the scan reads d+(v)
-// from v's placement {p(v), d+(v)} (one 8-byte load), and writes v's record id into r's record as a side
-// effect (element e - off32[r] of the list behind r's header); the row's first edge also writes the
-// row's header d+(r).  Row r's own placement and offset are read in row order.  Idempotent if
-// evaluated twice.
-struct RecordHead {
-    const unsigned long long* okeys;
-    const uint32_t* off32;
-    const uint2* place;
-    uint32_t* rec;
-    uint32_t nb;
+struct StoreKey {
+    unsigned long long* keys;
+    __device__ void operator()(uint64_t i, unsigned long long key) const { keys[i] = key; }
+};
+
+// Distinct edges are marked by one bit per sample of the sorted keys.
+__device__ __forceinline__ bool is_first(const unsigned long long* first, uint64_t i) {
+    return (first[i >> 6] >> (i & 63u)) & 1ull;
+}
+
+struct KeyBits {
+    unsigned long long key, bits;
+};
+struct LoadFirst {  // the distinct edges' keys (sorted or, at the same places, oriented)
+    typedef KeyBits Raw;
+    const unsigned long long* keys;
+    const unsigned long long* first;
+    __device__ Raw raw(uint64_t i) const { return {keys[i], first[i >> 6]}; }
+    __device__ bool make(const Raw& r, uint32_t lane, unsigned long long& key) const {
+        key = r.key;
+        return (r.bits >> lane) & 1ull;
+    }
+};
+
+struct LoadUpper {  // their upper ids
+    typedef KeyBits Raw;
+    const unsigned long long* keys;
+    const unsigned long long* first;
     unsigned long long mask;
-    const GraphMeta* meta;
-    __device__ unsigned long long operator()(uint64_t e) const {
-        if (e >= meta->m) return 0ull;
-        const unsigned long long k = okeys[e];
-        const uint32_t r = (uint32_t)(k >> nb), v = (uint32_t)(k & mask);
-        const uint2 pv = place[v], pr = place[r];
-        const uint32_t i = (uint32_t)e - off32[r];
-        rec[pr.x + 1u + i] = rec_id(pv.x);
-        if (i == 0) rec[pr.x] = pr.y;
-        return (unsigned long long)pv.y;
+    __device__ Raw raw(uint64_t i) const { return {keys[i], first[i >> 6]}; }
+    __device__ bool make(const Raw& r, uint32_t lane, uint32_t& id) const {
+        id = (uint32_t)(r.key & mask);
+        return (r.bits >> lane) & 1ull;
     }
+};
+
+struct StoreId {
+    uint32_t* ids;
+    __device__ void operator()(uint64_t i, uint32_t id) const { ids[i] = id; }
+};
+
+// Vertices by degree: elements degree << 32 | id; the last pass also writes the inverse (rank of every
+// id) and, in a batch, the graph of every rank.
+struct LoadDegree {
+    typedef unsigned long long Raw;
+    const uint32_t* deg;
+    __device__ Raw raw(uint64_t i) const { return ((unsigned long long)deg[i] << 32) | (uint32_t)i; }
+    __device__ bool make(Raw r, uint32_t, unsigned long long& e) const {
+        e = r;
+        return true;
+    }
+};
+__device__ __forceinline__ uint32_t owner(const unsigned long long* off, uint32_t k, unsigned long long x);
+struct StoreRank {
+    unsigned long long* order;
+    uint32_t* rank;
+    const unsigned long long* voff;
+    uint32_t k;
+    uint32_t* gid;
+    __device__ void operator()(uint64_t r, unsigned long long e) const;
+};
+
+struct StoreItem {  // schedule elements: key << 32 | rank
+    uint32_t* items;
+    __device__ void operator()(uint64_t i, unsigned long long e) const { items[i] = (uint32_t)e; }
 };
 
 // Record placement (kPlaceChunk ranks per thread, in rank order): the start of a record of s words
@@ -204,11 +229,6 @@ __global__ void k_clear_record_starts(unsigned long long* __restrict__ tv, const
         tv[rec_id(place[2 * (uint64_t)r])] = 0ull;
 }
 
-__device__ __forceinline__ bool first_of_run(const unsigned long long* keys, uint64_t i, unsigned long long sentinel) {
-    const unsigned long long k = keys[i];
-    return k != sentinel && (i == 0 || keys[i - 1] != k);
-}
-
 // The CSR offsets narrowed to 32 bits for the count kernels (m_in < 2^31): at 2^25 vertices the
 // 64-bit array (268 MB) no longer fits the Infinity Cache, the 32-bit one (134 MB) does.
 __global__ void k_narrow(const int64_t* __restrict__ off, uint64_t n1, uint32_t* __restrict__ off32) {
@@ -231,13 +251,51 @@ __device__ __forceinline__ uint32_t owner(const unsigned long long* off, uint32_
     return lo;
 }
 
+__device__ void StoreRank::operator()(uint64_t r, unsigned long long e) const {
+    order[r] = e;
+    rank[(uint32_t)e] = (uint32_t)r;
+    if (gid) gid[r] = owner(voff, k, (uint32_t)e);
+}
+
+constexpr uint32_t kMaxCanonPasses = 6;
+
+// Digit histograms of the canonical keys of a single graph; an out-of-range id raises the range error.
+__global__ void __launch_bounds__(1024) k_canon_hist(CanonKey canon, uint64_t m_in, uint32_t low, uint32_t passes,
+                                                     uint32_t* __restrict__ hist, GraphMeta* meta) {
+    __shared__ uint32_t s_h[kMaxCanonPasses][512];
+    for (uint32_t i = threadIdx.x; i < passes * 512; i += blockDim.x) (&s_h[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t bad = 0;
+    for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < m_in; base += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t i = base + threadIdx.x;
+        const bool act = i < m_in;
+        unsigned long long key = 0;
+        if (act) {
+            const uint2 s = canon.raw(i);
+            canon.make(s, 0, key);
+            if (s.x >= canon.n || s.y >= canon.n) bad = 1;
+        }
+        for (uint32_t p = 0; p < passes; ++p) count_digit(s_h[p], (uint32_t)(key >> (low + kDigit * p)) & 511u, act);
+    }
+    if (bad) atomicOr(&meta->err, 1u);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < passes * 512; i += blockDim.x)
+        if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
+}
+
 // Batch form: sample e belongs to graph g with eoff[g] <= e < eoff[g+1]; its
 // local ids are shifted by voff[g].  Local ids >= n_g, and union ids >= n
-// (malformed offsets), are range errors.
-__global__ void k_canon_batch(const uint32_t* __restrict__ src, const uint32_t* __restrict__ dst, uint64_t m_in,
-                              uint32_t n, uint32_t nb, unsigned long long sentinel,
-                              const unsigned long long* __restrict__ voff, const unsigned long long* __restrict__ eoff,
-                              uint32_t k, unsigned long long* __restrict__ keys, GraphMeta* meta) {
+// (malformed offsets), are range errors.  Writes the keys and their digit histograms.
+__global__ void __launch_bounds__(1024) k_canon_batch(const uint32_t* __restrict__ src,
+                                                      const uint32_t* __restrict__ dst, uint64_t m_in, uint32_t n,
+                                                      uint32_t nb, unsigned long long sentinel,
+                                                      const unsigned long long* __restrict__ voff,
+                                                      const unsigned long long* __restrict__ eoff, uint32_t k,
+                                                      uint32_t low, uint32_t passes,
+                                                      unsigned long long* __restrict__ keys,
+                                                      uint32_t* __restrict__ hist, GraphMeta* meta) {
+    __shared__ uint32_t s_h[kMaxCanonPasses][512];
+    for (uint32_t i = threadIdx.x; i < passes * 512; i += blockDim.x) (&s_h[0][0])[i] = 0;
     uint32_t bad = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 &&
         (voff[0] != 0 || eoff[0] != 0 || voff[k] != n || eoff[k] != m_in))
@@ -251,67 +309,202 @@ __global__ void k_canon_batch(const uint32_t* __restrict__ src, const uint32_t* 
         const uint64_t i = base + threadIdx.x;
         uint32_t g = s_g;
         __syncthreads();
-        if (i >= m_in) continue;
-        while (g + 1 < k && eoff[g + 1] <= i) ++g;
-        const unsigned long long v0 = voff[g], ng = voff[g + 1] - v0;
-        const unsigned long long a = (unsigned long long)src[i] + v0, b = (unsigned long long)dst[i] + v0;
-        unsigned long long key;
-        if (src[i] >= ng || dst[i] >= ng || a >= n || b >= n) { bad = 1; key = sentinel; }
-        else if (a == b) key = sentinel;
-        else {
-            const unsigned long long lo = a < b ? a : b, hi = a < b ? b : a;
-            key = (lo << nb) | hi;
+        const bool act = i < m_in;
+        unsigned long long key = sentinel;
+        if (act) {
+            while (g + 1 < k && eoff[g + 1] <= i) ++g;
+            const unsigned long long v0 = voff[g], ng = voff[g + 1] - v0;
+            const unsigned long long a = (unsigned long long)src[i] + v0, b = (unsigned long long)dst[i] + v0;
+            if (src[i] >= ng || dst[i] >= ng || a >= n || b >= n) bad = 1;
+            else if (a != b) {
+                const unsigned long long lo = a < b ? a : b, hi = a < b ? b : a;
+                key = (lo << nb) | hi;
+            }
+            keys[i] = key;
         }
-        keys[i] = key;
+        for (uint32_t p = 0; p < passes; ++p) count_digit(s_h[p], (uint32_t)(key >> (low + kDigit * p)) & 511u, act);
     }
     if (bad) atomicOr(&meta->err, 1u);
-}
-
-// Graph index of every vertex in rank space.
-__global__ void k_gid(const uint32_t* __restrict__ order, uint32_t n, const unsigned long long* __restrict__ voff,
-                      uint32_t k, uint32_t* __restrict__ gid) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x)
-        gid[r] = owner(voff, k, order[r]);
-}
-
-// One pass over the sorted keys (duplicates in place, sentinels last).  A distinct edge is the first
-// key of its run of equal keys.  upper[i] = its upper id, or (duplicates and sentinels) a value above
-// every id (bit nb set, or all ones when ids take 32 bits) so it sorts last.  Its lower id gets one
-// degree: a wavefront walks a chunk of kRunChunk consecutive keys 64 at a time; equal lower ids are
-// contiguous lanes (groups, found by ballot), the last lane of each group adds the group's distinct
-// edges, and the group reaching the wavefront's last lane carries over to the next step, so a long
-// run (a hub's row) costs one atomic per chunk (the sentinel's lower bits match no valid lower id,
-// which is below n - 1).  m = the number of distinct edges, one atomic per workgroup.
-constexpr uint32_t kRunChunk = 64 * 32;
-
-__global__ void k_runs(const unsigned long long* __restrict__ keys, uint32_t nb, uint64_t cap,
-                       unsigned long long sentinel, uint32_t* __restrict__ upper, uint32_t* __restrict__ deg,
-                       GraphMeta* meta) {
-    const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
-    const uint32_t above = nb >= 32 ? 0xFFFFFFFFu : (1u << nb);
-    const uint32_t lane = threadIdx.x & 63u;
-    __shared__ unsigned long long s_m;
-    if (threadIdx.x == 0) s_m = 0;
     __syncthreads();
-    unsigned long long firsts = 0;
+    for (uint32_t i = threadIdx.x; i < passes * 512; i += blockDim.x)
+        if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
+}
+
+// Distinct edges.  The keys are sorted by all but their `low` lowest bits; the keys of a group (equal top
+// bits) come in any order.  A workgroup handles the groups that start in its tile of kDedupTile keys: the
+// keys of groups of one are first by themselves, the others go into an LDS hash set (group number in the
+// tile << low | low bits: 28 bits name a key exactly), and the group that runs on into the next tile is
+// read to its end with a bit set over its low bits.  The first of each distinct key gets its bit in
+// `first` (cleared beforehand; words that two tiles share are ORed).
+//
+// Its lower id gets one degree: a wavefront walks 256 consecutive keys 64 at a time; equal lower ids are
+// contiguous lanes (groups, found by ballot), the last lane of each group adds the group's distinct
+// edges, and the group reaching the wavefront's last lane carries over to the next step, so a long run (a
+// hub's row) costs one atomic per 256 keys.  Upper ids: their digit histogram for the partition pass, or
+// (atomics) one degree atomic each.  m = the number of distinct edges.
+constexpr uint32_t kDedupThreads = 1024, kDedupItems = 4, kDedupTile = kDedupThreads * kDedupItems;
+constexpr uint32_t kDedupSlots = 2 * kDedupTile;  // 2^13
+constexpr uint32_t kDedupWords = kDedupTile / 64;
+
+__global__ void __launch_bounds__(kDedupThreads) __attribute__((amdgpu_waves_per_eu(8))) k_dedup(const unsigned long long* __restrict__ keys, uint32_t nb,
+                                                         uint32_t low, uint64_t cap, unsigned long long sentinel,
+                                                         unsigned long long* __restrict__ first,
+                                                         uint32_t* __restrict__ deg, uint32_t* __restrict__ uhist,
+                                                         uint32_t ubins, uint32_t ushift, bool uatomics,
+                                                         GraphMeta* meta) {
+    __shared__ __align__(16) uint32_t s_set[kDedupSlots];  // hash set, then the bits of the crossing group
+    __shared__ unsigned long long s_start[kDedupWords], s_first[kDedupWords];
+    __shared__ uint32_t s_pre[kDedupWords];
+    __shared__ uint32_t s_hist[1024];
+    __shared__ unsigned long long s_m;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
     const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
-    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
-    // wavefront-uniform trip counts: every lane takes part in the ballots
-    for (uint64_t c0 = (blockIdx.x * (uint64_t)(blockDim.x >> 6) + (threadIdx.x >> 6)) * kRunChunk; c0 < cap;
-         c0 += waves * kRunChunk) {
+    constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;
+    for (uint32_t i = tid; i < ubins; i += kDedupThreads) s_hist[i] = 0;
+    if (tid == 0) s_m = 0;
+    unsigned long long found = 0;
+    for (uint64_t base = blockIdx.x * (uint64_t)kDedupTile; base < cap; base += (uint64_t)gridDim.x * kDedupTile) {
+        const uint64_t end = base + kDedupTile < cap ? base + kDedupTile : cap;
+        unsigned long long k[kDedupItems];
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const uint64_t x = base + wave * (64u * kDedupItems) + i * 64u + lane;
+            k[i] = x < cap ? keys[x] : ~0ull;
+        }
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const uint64_t x = base + wave * (64u * kDedupItems) + i * 64u + lane;
+            unsigned long long before = ((unsigned long long)(uint32_t)__shfl_up((int)(uint32_t)(k[i] >> 32), 1, 64) << 32) |
+                                        (uint32_t)__shfl_up((int)(uint32_t)k[i], 1, 64);
+            if (lane == 0 && x > 0 && x < cap) before = keys[x - 1];
+            const bool start = x < cap && (x == 0 || (before >> low) != (k[i] >> low));
+            const unsigned long long s = __ballot(start);
+            if (lane == 0) s_start[wave * kDedupItems + i] = s;
+        }
+        __syncthreads();
+        const unsigned long long starts = lane < kDedupWords ? s_start[lane] : 0ull;
+        if (wave == 0) {  // starts before each word, and clear bits
+            const uint32_t c = (uint32_t)__popcll(starts);
+            const uint32_t pre = wave_incl_scan(c) - c;
+            if (lane < kDedupWords) {
+                s_pre[lane] = pre;
+                s_first[lane] = 0;
+            }
+        }
+        const unsigned long long has = __ballot(starts != 0);  // words with a start
+        __syncthreads();
+        if (!has) continue;  // uniform: the whole tile belongs to an earlier tile's group
+        const uint32_t w0 = (uint32_t)__builtin_ctzll(has), w1 = 63u - (uint32_t)__builtin_clzll(has);
+        const uint32_t p0 = w0 * 64u + (uint32_t)__builtin_ctzll(s_start[w0]);         // first start
+        const uint32_t p1 = w1 * 64u + 63u - (uint32_t)__builtin_clzll(s_start[w1]);   // last start
+        // (samples without an edge come last; where the top bits hold the whole lower id their group holds
+        // nothing else and is left alone)
+        const bool cross = end < cap && (keys[end] >> low) == (keys[end - 1] >> low) &&
+                           !(low <= nb && (keys[end] >> low) == (sentinel >> low));
+        const uint32_t stop = cross ? p1 : (uint32_t)(end - base);  // keys [p0, stop) are in closed groups
+        // groups of one, and whether there are others
+        uint32_t many = 0, one = 0;
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const uint32_t p = wave * (64u * kDedupItems) + i * 64u + lane;
+            if (p < p0 || p >= stop || k[i] == sentinel) continue;
+            const bool here = (s_start[p >> 6] >> (p & 63u)) & 1ull;
+            const uint32_t q = p + 1;
+            const bool next = q == stop || ((s_start[q >> 6] >> (q & 63u)) & 1ull);
+            if (here && next) one |= 1u << i;
+            else many |= 1u << i;
+        }
+        if (__syncthreads_or(many != 0)) {
+            for (uint32_t i = tid; i < kDedupSlots / 4; i += kDedupThreads)
+                reinterpret_cast<uint4*>(s_set)[i] = make_uint4(kEmptySlot, kEmptySlot, kEmptySlot, kEmptySlot);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < (int)kDedupItems; ++i) {
+                if (!((many >> i) & 1u)) continue;
+                const uint32_t p = wave * (64u * kDedupItems) + i * 64u + lane;
+                const uint32_t g = s_pre[p >> 6] + (uint32_t)__popcll(s_start[p >> 6] & upto) - 1u;
+                const uint32_t name = (g << low) | ((uint32_t)k[i] & ((1u << low) - 1u));
+                uint32_t at = (name * 0x9E3779B1u) >> 19;  // 13 bits: kDedupSlots
+                for (;;) {
+                    const uint32_t old = atomicCAS(&s_set[at], kEmptySlot, name);
+                    if (old == kEmptySlot) one |= 1u << i;
+                    if (old == kEmptySlot || old == name) break;
+                    at = (at + 1) & (kDedupSlots - 1);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const unsigned long long f = __ballot((one >> i) & 1u);
+            if (lane == 0) s_first[wave * kDedupItems + i] = f;
+        }
+        __syncthreads();
+        if (cross) {
+            for (uint32_t i = tid; i < ((1u << low) + 31u) / 32u; i += kDedupThreads) s_set[i] = 0;
+            __syncthreads();
+            const unsigned long long group = keys[base + p1] >> low;
+            uint32_t beyond = 0;  // distinct keys past this tile
+            uint32_t lo = 0;
+            for (uint64_t x0 = base + p1;; x0 += kDedupThreads) {
+                const uint64_t x = x0 + tid;
+                const unsigned long long key = x < cap ? keys[x] : ~0ull;
+                const bool in = x < cap && (key >> low) == group;
+                if (in && key != sentinel) {
+                    const uint32_t b = (uint32_t)key & ((1u << low) - 1u);
+                    if (!((atomicOr(&s_set[b >> 5], 1u << (b & 31u)) >> (b & 31u)) & 1u)) {
+                        if (x < end) {
+                            atomicOr(&s_first[(x - base) >> 6], 1ull << (x & 63u));
+                        } else {
+                            atomicOr(&first[x >> 6], 1ull << (x & 63u));
+                            const uint32_t hi = (uint32_t)(key & mask);
+                            if (ubins) atomicAdd(&s_hist[hi >> ushift], 1u);
+                            if (uatomics) atomicAdd(&deg[hi], 1u);
+                            const uint32_t l = (uint32_t)(key >> nb);
+                            if (beyond && l != lo) {
+                                atomicAdd(&deg[lo], beyond);
+                                beyond = 0;
+                            }
+                            lo = l;
+                            ++beyond;
+                            ++found;
+                        }
+                    }
+                }
+                if (!__syncthreads_and(in)) break;
+            }
+            // lower-id degrees of the keys past the tile (one id, or few where the group holds several)
+            const uint32_t lead = __builtin_amdgcn_readfirstlane(lo);
+            const unsigned long long differ = __ballot(beyond && lo != lead);
+            if (!differ) {
+                const uint32_t t = wave_sum(beyond);
+                if (lane == 0 && t) atomicAdd(&deg[lead], t);
+            } else if (beyond) {
+                atomicAdd(&deg[lo], beyond);
+            }
+        }
+        // bits, lower-id degrees and the upper digit histogram of this tile's distinct edges
         uint32_t clo = 0xFFFFFFFFu, cc = 0;  // carried group (uniform)
-        for (uint32_t st = 0; st < kRunChunk && c0 + st < cap; st += 64) {
-            const uint64_t i = c0 + st + lane;
-            bool first = false;
-            uint32_t lo = 0xFFFFFFFFu;
-            if (i < cap) {
-                const unsigned long long k = keys[i];
-                first = k != sentinel && (i == 0 || keys[i - 1] != k);
-                lo = (uint32_t)(k >> nb);
-                upper[i] = first ? (uint32_t)(k & mask) : above;
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const uint32_t word = wave * kDedupItems + i;
+            const unsigned long long F = s_first[word];
+            if (lane == 0) {
+                if (word * 64u >= p0) {
+                    if (base + word * 64u < cap) first[(base >> 6) + word] = F;
+                } else if (F) {
+                    atomicOr(&first[(base >> 6) + word], F);
+                }
+                found += (unsigned long long)__popcll(F);
+            }
+            const uint32_t lo = (uint32_t)(k[i] >> nb);
+            const bool mine = (F >> lane) & 1ull;
+            if (mine) {
+                const uint32_t hi = (uint32_t)(k[i] & mask);
+                if (ubins) atomicAdd(&s_hist[hi >> ushift], 1u);
+                if (uatomics) atomicAdd(&deg[hi], 1u);
             }
             const uint32_t lo_prev = (uint32_t)__shfl_up((int)lo, 1, 64);
-            const unsigned long long F = __ballot(first);
             const unsigned long long H = __ballot(lane == 0 || lo != lo_prev);  // group starts
             const uint32_t s = 63u - (uint32_t)__builtin_clzll(H & upto);      // this lane's group start
             const uint32_t c = (uint32_t)__popcll((F & upto) >> s);            // its firsts up to this lane
@@ -330,41 +523,96 @@ __global__ void k_runs(const unsigned long long* __restrict__ keys, uint32_t nb,
                 clo = lo63;
                 cc = c63;
             }
-            if (lane == 0) firsts += (unsigned long long)__popcll(F);
         }
         if (cc && lane == 0) atomicAdd(&deg[clo], cc);
+        __syncthreads();  // the LDS is reused by the next tile
     }
-    if (lane == 0 && firsts) atomicAdd(&s_m, firsts);
+    if (found) atomicAdd(&s_m, found);
     __syncthreads();
-    if (threadIdx.x == 0 && s_m) atomicAdd(&meta->m, s_m);
+    if (tid == 0 && s_m) atomicAdd(&meta->m, s_m);
+    for (uint32_t i = tid; i < ubins; i += kDedupThreads)
+        if (s_hist[i]) atomicAdd(&uhist[i], s_hist[i]);
 }
 
-// Upper endpoints' degrees: the sorted upper ids of the distinct edges, counted by run length (the
-// run's first element subtracts its index, its last adds index + 1; two atomics per run, mod 2^32:
-// no counter is hammered by a hub vertex).
-__global__ void k_degree(const uint32_t* __restrict__ upper, uint64_t cap, const GraphMeta* meta,
-                         uint32_t* __restrict__ deg) {
-    const uint64_t m = meta->m;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-        if (i < m) {
-            const uint32_t hi = upper[i];
-            if (i == 0 || upper[i - 1] != hi) atomicSub(&deg[hi], (uint32_t)i);
-            if (i + 1 == m || upper[i + 1] != hi) atomicAdd(&deg[hi], (uint32_t)(i + 1));
+// Upper ids' degrees.  The ids are partitioned by hi >> sub (bins partitions, sizes in uhist; with one
+// partition they are read from the sorted keys).  A work unit is up to kUpperUnit ids of one partition;
+// its counters live in LDS (2^kCounterBits at a time) and are added to deg, by atomics only where a
+// partition has several units.
+constexpr uint32_t kUpperUnit = 1u << 20;
+
+__global__ void __launch_bounds__(1024) k_upper_count(const uint32_t* __restrict__ ids, LoadUpper direct, uint64_t cap,
+                                                      uint32_t bins, uint32_t sub, uint32_t n,
+                                                      const uint32_t* __restrict__ uhist, uint32_t unit_size,
+                                                      uint32_t* __restrict__ deg) {
+    extern __shared__ __align__(16) uint32_t s_cnt[];
+    __shared__ uint32_t s_unit[1025], s_at[1025], s_scan[16];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t size = ids ? (tid < bins ? uhist[tid] : 0u) : (tid == 0 ? (uint32_t)cap : 0u);
+    const uint32_t units = (size + unit_size - 1) / unit_size;
+    const uint32_t u0 = block_excl_scan<16>(units, s_scan), a0 = block_excl_scan<16>(size, s_scan);
+    s_unit[tid] = u0;
+    s_at[tid] = a0;
+    if (tid == 1023) s_unit[1024] = u0 + units;
+    __syncthreads();
+    const uint32_t total = s_unit[1024];
+    const uint32_t span = sub < kCounterBits ? 1u << sub : 1u << kCounterBits;  // counters at a time
+    for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
+        uint32_t l = 0, r = 1023;  // the last partition with s_unit <= u (empty ones repeat the next value)
+        while (l < r) {
+            const uint32_t mid = (l + r + 1) >> 1;
+            if (s_unit[mid] <= u) l = mid; else r = mid - 1;
+        }
+        const uint32_t parts = s_unit[l + 1] - s_unit[l], part = u - s_unit[l];
+        const uint32_t len = ids ? uhist[l] : (uint32_t)cap;
+        const uint64_t x0 = s_at[l] + (uint64_t)part * unit_size;
+        const uint64_t x1 = part + 1 < parts ? x0 + unit_size : (uint64_t)s_at[l] + len;
+        for (uint32_t c0 = 0; c0 < (1u << sub); c0 += span) {
+            for (uint32_t i = tid; i < span; i += 1024) s_cnt[i] = 0;
+            __syncthreads();
+            for (uint64_t x = x0 + tid; x < x1; x += 1024) {
+                uint32_t id;
+                if (ids) id = ids[x];
+                else if (!direct.make(direct.raw(x), (uint32_t)(x & 63u), id)) continue;
+                const uint32_t c = (id & ((1u << sub) - 1u)) - c0;
+                if (c < span) atomicAdd(&s_cnt[c], 1u);
+            }
+            __syncthreads();
+            const uint64_t v0 = ((uint64_t)l << sub) + c0;
+            for (uint32_t i = tid; i < span && v0 + i < n; i += 1024) {
+                const uint32_t c = s_cnt[i];
+                if (c) {
+                    if (parts == 1) deg[v0 + i] += c;
+                    else atomicAdd(&deg[v0 + i], c);
+                }
+            }
+            __syncthreads();
         }
     }
 }
 
-__global__ void k_rank(const uint32_t* __restrict__ order, uint32_t n, uint32_t* __restrict__ rank) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x)
-        rank[order[r]] = r;
+// Digit histograms of the degrees.
+__global__ void __launch_bounds__(1024) k_degree_hist(const uint32_t* __restrict__ deg, uint32_t n, uint32_t passes,
+                                                      uint32_t* __restrict__ hist) {
+    __shared__ uint32_t s_h[4][512];
+    for (uint32_t i = threadIdx.x; i < passes * 512; i += blockDim.x) (&s_h[0][0])[i] = 0;
+    __syncthreads();
+    for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < n; base += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t i = base + threadIdx.x;
+        const bool act = i < n;
+        const uint32_t d = act ? deg[i] : 0u;
+        for (uint32_t p = 0; p < passes; ++p) count_digit(s_h[p], (d >> (kDigit * p)) & 511u, act);
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < passes * 512; i += blockDim.x)
+        if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
 }
 
 __global__ void k_orient_count(const unsigned long long* __restrict__ keys, uint32_t nb, uint64_t cap,
-                               unsigned long long sentinel, const uint32_t* __restrict__ rank,
+                               const unsigned long long* __restrict__ first, const uint32_t* __restrict__ rank,
                                uint32_t* __restrict__ dplus) {
     const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-        if (!first_of_run(keys, i, sentinel)) continue;
+        if (!is_first(first, i)) continue;
         const unsigned long long k = keys[i];
         const uint32_t ra = rank[(uint32_t)(k >> nb)], rb = rank[(uint32_t)(k & mask)];
         atomicAdd(&dplus[ra < rb ? ra : rb], 1u);
@@ -372,12 +620,12 @@ __global__ void k_orient_count(const unsigned long long* __restrict__ keys, uint
 }
 
 __global__ void k_orient_fill(const unsigned long long* __restrict__ keys, uint32_t nb, uint64_t cap,
-                              unsigned long long sentinel, const uint32_t* __restrict__ rank,
+                              const unsigned long long* __restrict__ first, const uint32_t* __restrict__ rank,
                               const int64_t* __restrict__ off, uint32_t* __restrict__ cursor,
                               uint32_t* __restrict__ col) {
     const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-        if (!first_of_run(keys, i, sentinel)) continue;
+        if (!is_first(first, i)) continue;
         const unsigned long long k = keys[i];
         const uint32_t ra = rank[(uint32_t)(k >> nb)], rb = rank[(uint32_t)(k & mask)];
         const uint32_t s = ra < rb ? ra : rb, d = ra < rb ? rb : ra;
@@ -386,73 +634,257 @@ __global__ void k_orient_fill(const unsigned long long* __restrict__ keys, uint3
     }
 }
 
-// Oriented keys (rank_lo << nb | rank_hi) of the distinct edges for a
-// sort-based CSR build; duplicates and sentinels stay the sentinel (sort last).
-__global__ void k_orient_keys(const unsigned long long* __restrict__ keys, uint32_t nb, uint64_t cap,
-                              const uint32_t* __restrict__ rank, unsigned long long sentinel,
-                              unsigned long long* __restrict__ okeys) {
+// Oriented keys (rank_lo << nb | rank_hi) of the distinct edges, at the places of the sorted keys, and
+// the digit histograms of their rows.  Bound by the gathers of rank[hi] (2^25 vertices: one 128-byte line
+// per edge).
+__global__ void __launch_bounds__(1024) k_orient_keys(const unsigned long long* __restrict__ keys, uint32_t nb,
+                                                      uint64_t cap, const unsigned long long* __restrict__ first,
+                                                      const uint32_t* __restrict__ rank, uint32_t passes,
+                                                      unsigned long long* __restrict__ okeys,
+                                                      uint32_t* __restrict__ hist) {
+    // The top digit has few values and on skewed graphs most rows share one: 16 copies of its counters.
+    __shared__ uint32_t s_h[3][512], s_top[512 * 16];
+    const uint32_t top = passes - 1, tops = 1u << (nb - kDigit * top);
+    for (uint32_t i = threadIdx.x; i < top * 512; i += blockDim.x) (&s_h[0][0])[i] = 0;
+    for (uint32_t i = threadIdx.x; i < tops * 16; i += blockDim.x) s_top[i] = 0;
+    __syncthreads();
     const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * blockDim.x) {
-        if (first_of_run(keys, i, sentinel)) {
-            const unsigned long long k = keys[i];
-            const uint32_t ra = rank[(uint32_t)(k >> nb)], rb = rank[(uint32_t)(k & mask)];
-            okeys[i] = ((unsigned long long)(ra < rb ? ra : rb) << nb) | (ra < rb ? rb : ra);
-        } else {
-            okeys[i] = sentinel;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < cap; base += 2 * stride) {
+        bool act[2];
+        uint32_t ra[2] = {0, 0}, rb[2] = {0, 0};
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint64_t i = base + j * stride + threadIdx.x;
+            act[j] = i < cap && is_first(first, i);
+            if (act[j]) {
+                const unsigned long long k = keys[i];
+                ra[j] = rank[(uint32_t)(k >> nb)];
+                rb[j] = rank[(uint32_t)(k & mask)];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t row = ra[j] < rb[j] ? ra[j] : rb[j], head = ra[j] < rb[j] ? rb[j] : ra[j];
+            if (act[j]) okeys[base + j * stride + threadIdx.x] = ((unsigned long long)row << nb) | head;
+            for (uint32_t p = 0; p < top; ++p) count_digit(s_h[p], (row >> (kDigit * p)) & 511u, act[j]);
+            if (act[j]) atomicAdd(&s_top[(row >> (kDigit * top)) * 16u + (threadIdx.x & 15u)], 1u);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < top * 512; i += blockDim.x)
+        if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
+    for (uint32_t i = threadIdx.x; i < tops; i += blockDim.x) {
+        uint32_t c = 0;
+        for (uint32_t j = 0; j < 16; ++j) c += s_top[i * 16 + j];
+        if (c) atomicAdd(&hist[top * 512 + i], c);
+    }
+}
+
+// From the m oriented keys sorted by row: the lists, and the offsets of every row (64 and 32 bits: the
+// count kernels read the latter, m_in < 2^31).  Edge e of a row unlike its predecessor's gives the offset
+// e to its row and to the empty rows before it; the rows before the first edge's and after the last
+// edge's are filled by the whole grid, long gaps in between by the wavefront.
+__global__ void __launch_bounds__(256) k_csr(const unsigned long long* __restrict__ okeys, uint32_t nb,
+                                             const GraphMeta* meta, uint32_t n, int64_t* __restrict__ off,
+                                             uint32_t* __restrict__ off32, uint32_t* __restrict__ col) {
+    const uint64_t m = meta->m;
+    const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
+    const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    const uint32_t lane = threadIdx.x & 63u;
+    auto put = [&](uint64_t r, uint32_t v) {
+        off[r] = v;
+        off32[r] = v;
+    };
+    const uint64_t head = m ? (uint32_t)(okeys[0] >> nb) : n;  // rows [0, head] start at 0
+    const uint64_t tail = m ? (uint32_t)(okeys[m - 1] >> nb) + 1ull : n + 1ull;
+    for (uint64_t r = t0; r <= head; r += step) put(r, 0u);
+    for (uint64_t r = tail + t0; r <= n; r += step) put(r, (uint32_t)m);
+    for (uint64_t base = t0 - lane; base < m; base += step) {
+        const uint64_t e = base + lane;
+        uint32_t r = 0, prev = 0;
+        if (e < m) {
+            const unsigned long long k = okeys[e];
+            col[e] = (uint32_t)(k & mask);
+            r = prev = (uint32_t)(k >> nb);
+            if (e) prev = (uint32_t)(okeys[e - 1] >> nb);
+        }
+        const uint32_t gap = r - prev;  // rows (prev, r] start at e
+        const bool far = gap > 32;
+        if (gap && !far)
+            for (uint32_t q = prev + 1; q <= r; ++q) put(q, (uint32_t)e);
+        for (unsigned long long left = __ballot(far); left; left &= left - 1) {
+            const int src = __builtin_ctzll(left);
+            const uint32_t a = __builtin_amdgcn_readlane(prev, src), b = __builtin_amdgcn_readlane(r, src);
+            const uint32_t at = (uint32_t)(base + (uint32_t)src);
+            for (uint64_t q = (uint64_t)a + 1 + lane; q <= b; q += 64) put(q, at);
         }
     }
 }
 
-// From sorted oriented keys: col[i] = head, and d+ of each row as its run
-// length (the run's first key subtracts its index, its last adds index + 1).
-__global__ void k_csr_runs(const unsigned long long* __restrict__ okeys, uint32_t nb, uint64_t cap,
-                           const GraphMeta* meta, uint32_t* __restrict__ dplus, uint32_t* __restrict__ col) {
+// Collective work W(r) = sum of d+(v) over r's out-neighbours v, from the oriented keys sorted by row.  A
+// wavefront takes 256 consecutive edges, issues their gathers (v's offsets) together, and sums the runs of
+// equal rows: runs that end and begin inside are stored, the first and the last are added to work (cleared
+// beforehand).  Bound by the gathers: one 128-byte line per edge at 2^25 vertices (11.8 ms for 537 M
+// edges), 0.51 ms for the 64 M of R-MAT 22, 0.09 ms for the 16 M of R-MAT 20 (16 lanes per row took 0.47
+// and 0.39, waiting for the longest rows).  Record layout: d+(v) comes with v's placement {p(v), d+(v)}, and edge e writes v's record id
+// into its row's record; the row's first edge also writes the header d+(r).
+constexpr uint32_t kWorkItems = 4;
+
+template <bool REC>
+__global__ void __launch_bounds__(256) k_work(const unsigned long long* __restrict__ okeys, uint32_t nb,
+                                              const uint32_t* __restrict__ off, const uint2* __restrict__ place,
+                                              uint32_t* __restrict__ rec, const GraphMeta* meta,
+                                              unsigned long long* __restrict__ work) {
     const uint64_t m = meta->m;
     const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < cap && i < m; i += (uint64_t)gridDim.x * blockDim.x) {
-        const unsigned long long k = okeys[i];
-        const uint32_t s = (uint32_t)(k >> nb);
-        col[i] = (uint32_t)(k & mask);
-        if (i == 0 || (uint32_t)(okeys[i - 1] >> nb) != s) atomicSub(&dplus[s], (uint32_t)i);
-        if (i + 1 == m || (uint32_t)(okeys[i + 1] >> nb) != s) atomicAdd(&dplus[s], (uint32_t)(i + 1));
+    const uint32_t lane = threadIdx.x & 63u;
+    const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
+    constexpr uint64_t kSpan = 64 * kWorkItems;
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+    for (uint64_t base = (blockIdx.x * (uint64_t)(blockDim.x >> 6) + (threadIdx.x >> 6)) * kSpan; base < m;
+         base += waves * kSpan) {
+        uint32_t row[kWorkItems], v[kWorkItems], len[kWorkItems];
+#pragma unroll
+        for (uint32_t i = 0; i < kWorkItems; ++i) {
+            const uint64_t e = base + i * 64u + lane;
+            const unsigned long long k = okeys[e < m ? e : m - 1];
+            row[i] = (uint32_t)(k >> nb);
+            v[i] = (uint32_t)(k & mask);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kWorkItems; ++i) {
+            const uint64_t e = base + i * 64u + lane;
+            if constexpr (REC) {
+                const uint2 pv = place[v[i]], pr = place[row[i]];
+                len[i] = pv.y;
+                if (e < m) {
+                    const uint32_t j = (uint32_t)e - off[row[i]];
+                    rec[pr.x + 1u + j] = rec_id(pv.x);
+                    if (j == 0) rec[pr.x] = pr.y;
+                }
+            } else {
+                struct __attribute__((packed, aligned(4))) Pair { uint32_t a, b; };  // one 8-byte load
+                const Pair o = *reinterpret_cast<const Pair*>(off + v[i]);
+                len[i] = o.b - o.a;
+            }
+            if (e >= m) len[i] = 0;
+        }
+        // carried run (uniform): row, sum so far, and whether it may have begun before this span
+        uint32_t crow = __builtin_amdgcn_readfirstlane(row[0]);
+        unsigned long long csum = 0;
+        bool open = true;
+#pragma unroll
+        for (uint32_t i = 0; i < kWorkItems; ++i) {
+            const uint32_t prev = (uint32_t)__shfl_up((int)row[i], 1, 64);
+            const unsigned long long H = __ballot(lane == 0 ? row[i] != crow : row[i] != prev);  // run starts
+            const uint32_t incl = wave_incl_scan(len[i]);  // out-degrees are below 2^17 (m < 2^31): no overflow
+            const unsigned long long mine = H & upto;
+            const uint32_t s = mine ? 63u - (uint32_t)__builtin_clzll(mine) : 0u;  // this lane's run start
+            const uint32_t from = (uint32_t)__shfl((int)incl, (int)((s + 63u) & 63u), 64);  // every lane takes part
+            const uint32_t sum = incl - (s ? from : 0u);
+            const bool last = lane != 63 && ((H >> (lane + 1)) & 1ull);  // the next lane starts another run
+            if (last) {
+                if (mine) {
+                    work[row[i]] = sum;  // begins and ends in this step
+                } else {
+                    const unsigned long long t = csum + sum;
+                    if (open) atomicAdd(&work[row[i]], t);
+                    else work[row[i]] = t;
+                }
+            }
+            if (H & 1ull) {  // the carried run ended with the previous step
+                if (lane == 0) {
+                    if (open) atomicAdd(&work[crow], csum);
+                    else work[crow] = csum;
+                }
+            }
+            const uint32_t sum63 = (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
+            csum = H ? sum63 : csum + sum63;
+            open = H ? false : open;
+            crow = (uint32_t)__builtin_amdgcn_readlane((int)row[i], 63);
+        }
+        if (lane == 0 && csum) atomicAdd(&work[crow], csum);  // may go on in the next span
+    }
+}
+
+// The same from lists (relabelled graphs and counting-sort builds, which have no sorted keys): 16 lanes per row.
+constexpr uint32_t kWorkLanes = 16;
+
+__global__ void __launch_bounds__(256) k_work_rows(const uint32_t* __restrict__ off, const uint32_t* __restrict__ col,
+                                                   uint32_t n, unsigned long long* __restrict__ work) {
+    const uint32_t sub = threadIdx.x % kWorkLanes, per = blockDim.x / kWorkLanes;
+    for (uint64_t r = blockIdx.x * (uint64_t)per + threadIdx.x / kWorkLanes; r < n; r += (uint64_t)gridDim.x * per) {
+        const uint32_t b = off[r], d = off[r + 1] - b;
+        unsigned long long w = 0;
+        for (uint32_t p = sub; p < d; p += kWorkLanes) {
+            const uint32_t v = col[b + p];
+            w += off[v + 1] - off[v];
+        }
+#pragma unroll
+        for (uint32_t o = 1; o < kWorkLanes; o <<= 1) w += __shfl_xor(w, o);  // lanes of a row run together
+        if (sub == 0) work[r] = w;
+    }
+}
+
+// The headers of rows without edges (record layout; the others: k_work).
+__global__ void k_record_empty(const uint2* __restrict__ place, uint32_t n, uint32_t* __restrict__ rec) {
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
+        const uint2 p = place[r];
+        if (p.y == 0) rec[p.x] = 0;
     }
 }
 
 // Census for the packed bin: vertices that would get a wavefront-size table, and how many of them
 // are light enough to pack (out-degree <= pack_cap, W(u) <= kPackMaxWork).  Packing pays when light
 // vertices dominate (their per-vertex fixed work is what it shares); the schedule packs only then.
-__global__ void k_pack_census(const int64_t* __restrict__ off, const unsigned long long* __restrict__ wscan,
-                              uint32_t n, BinCaps caps, GraphMeta* meta) {
+__global__ void __launch_bounds__(1024) k_pack_census(const uint32_t* __restrict__ off,
+                                                      const unsigned long long* __restrict__ work, uint32_t n,
+                                                      BinCaps caps, GraphMeta* meta) {
+    __shared__ uint32_t s_w, s_p;
+    if (threadIdx.x == 0) s_w = s_p = 0;
+    __syncthreads();
     uint32_t wc = 0, pc = 0;
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-        const int64_t b = off[r], e = off[r + 1];
-        const uint32_t d = (uint32_t)(e - b);
-        const unsigned long long w = d ? wscan[e - 1] - (b ? wscan[b - 1] : 0ull) : 0ull;
-        if (d < 2 || w == 0 || caps.force_hub || caps.force_big || caps.force_wg || d > caps.wave_cap) continue;
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t d = off[r + 1] - off[r];
+        const unsigned long long w = work[r];
+        if (d < 2 || w == 0 || d > caps.wave_cap) continue;
         ++wc;
         pc += (d <= caps.pack_cap && w <= kPackMaxWork) ? 1u : 0u;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        wc += __shfl_xor(wc, o);
-        pc += __shfl_xor(pc, o);
-    }
-    if ((threadIdx.x & 63) == 0 && wc) {
-        atomicAdd(&meta->wave_cands, wc);
-        atomicAdd(&meta->pack_cands, pc);
+    if (wc) atomicAdd(&s_w, wc);
+    if (pc) atomicAdd(&s_p, pc);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_w) {
+        atomicAdd(&meta->wave_cands, s_w);
+        atomicAdd(&meta->pack_cands, s_p);
     }
 }
 
-// One thread per vertex: d+, W(u) = sum of d+(v) over v in N+(u) (from the
-// inclusive scan of d+(col[e]) over the edges), bin, and the sort key
-// (bin << 24 | reversed work, clamped to 24 bits).  Bins: 0 global-memory table (too large for
-// any LDS table), 1 large LDS table (whole LDS of a workgroup, one per CU),
+// Largest-work-first code of 15 bits, smaller for more work: exponent and 10 bits below the leading one
+// (exact below 2048, to 0.1% above: ties there only loosen the order, and kCoreMinWork = 2^10 divides it).
+__device__ __forceinline__ uint32_t work_code(unsigned long long w) {
+    const uint32_t x = w > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)w;
+    if (x == 0) return 32767u;
+    const uint32_t e = 31u - (uint32_t)__builtin_clz(x);
+    const uint32_t f = (e >= 10 ? x >> (e - 10) : x << (10 - e)) & 1023u;
+    return 32767u - ((e << 10) | f);
+}
+static_assert(kCoreMinWork == 1024, "the core path's owners of the wavefront bin are a prefix of its order");
+
+// One thread per vertex: bin and schedule element (group of the bin << 15 | work code) << 32 | rank, which
+// replaces the rank's (degree << 32 | id), and the digit histograms of the keys.  Bins: 0 global-memory
+// table (too large for any LDS table), 1 large LDS table (whole LDS of a workgroup, one per CU),
 // 2 workgroup LDS table, 3 wavefront LDS slice, 4 light vertices packed
-// several to a wavefront, 5 skipped.  Bin 1 is split in two parts, each by decreasing work: first
+// several to a wavefront, 5 skipped.  Bin 1 is split in two groups, each by decreasing work: first
 // the vertices whose tables need more than half a CU's LDS (counted by one workgroup per CU), then
-// those up to caps.mid_cap (two workgroups per CU); the work field there takes 23 bits.
-__global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long long* __restrict__ wscan, uint32_t n,
-                           BinCaps caps, GraphMeta* meta, uint32_t* skey, uint32_t* __restrict__ rec,
-                           const uint32_t* __restrict__ place) {
+// those up to caps.mid_cap (two workgroups per CU).
+__global__ void __launch_bounds__(1024) k_schedule(const uint32_t* __restrict__ off,
+                                                  const unsigned long long* __restrict__ work, uint32_t n, BinCaps caps,
+                                                  GraphMeta* meta, unsigned long long* elem,
+                                                  uint32_t* __restrict__ hist) {
+    __shared__ uint32_t s_h[2][512];
+    for (uint32_t i = threadIdx.x; i < 1024; i += blockDim.x) (&s_h[0][0])[i] = 0;
     __shared__ unsigned long long s_hw, s_ce;
     __shared__ unsigned int s_h3;
     __shared__ unsigned long long s_w;
@@ -464,8 +896,6 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
     }
     if (threadIdx.x == 0) { s_w = 0; s_max = 0; s_full = 0; s_hw = 0; s_ce = 0; s_h3 = 0; }
     __syncthreads();
-    const unsigned long long kWorkMax = (1ull << 24) - 1;  // larger work ties: LPT order is a heuristic
-    const unsigned long long kWorkMax1 = (1ull << 23) - 1;  // bin 1: below the part bit
     const uint32_t pack_cap = (caps.pack_cap && 2ull * meta->pack_cands >= meta->wave_cands) ? caps.pack_cap : 0u;
     // Per-thread partials, reduced across the wave, then one LDS atomic per wave.
     unsigned long long wsum = 0;
@@ -473,33 +903,34 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
     unsigned long long bw[6] = {0, 0, 0, 0, 0, 0};
     unsigned long long hw = 0, ce = 0;
     uint32_t h3 = 0;
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-        const int64_t b = off[r], e = off[r + 1];
-        const uint32_t d = (uint32_t)(e - b);
-        const unsigned long long w = d ? wscan[e - 1] - (b ? wscan[b - 1] : 0ull) : 0ull;
-        if (rec && d == 0) rec[place[2 * r]] = 0;  // the header of a row without edges (the others: in the W scan)
-        uint32_t bin;
-        if (d < 2 || w == 0) bin = 5;
-        else if (caps.force_hub || d > caps.big_cap) bin = 0;
-        else if (caps.force_big || d > caps.wg_cap) bin = 1;
-        else if (caps.force_wg || d > caps.wave_cap) bin = 2;
-        else if (d <= pack_cap && w <= kPackMaxWork) bin = 4;
-        else bin = 3;
-        if (caps.core_bits) {  // skey[r] still holds r's degree: deg - d+ edges end in r
-            if (r >= caps.core_first) ce += skey[r] - d;
-            const bool h = bin == 3 && w >= kCoreMinWork;
-            h3 += h;
-            if (h || bin == 2 || (bin == 1 && (caps.core_big_all || d <= caps.mid_cap))) hw += w;
+    for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < n; base += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t r = (uint32_t)base + threadIdx.x;
+        const bool act = r < n;
+        const uint32_t d = act ? off[r + 1] - off[r] : 0u;
+        const unsigned long long w = act ? work[r] : 0ull;
+        uint32_t bin = 5, group = 6;
+        if (act) {
+            if (d < 2 || w == 0) bin = 5;
+            else if (caps.force_hub || d > caps.big_cap) bin = 0;
+            else if (caps.force_big || d > caps.wg_cap) bin = 1;
+            else if (caps.force_wg || d > caps.wave_cap) bin = 2;
+            else if (d <= pack_cap && w <= kPackMaxWork) bin = 4;
+            else bin = 3;
+            if (caps.core_bits) {  // elem[r] still holds r's degree: deg - d+ edges end in r
+                if (r >= caps.core_first) ce += (uint32_t)(elem[r] >> 32) - d;
+                const bool h = bin == 3 && w >= kCoreMinWork;
+                h3 += h;
+                if (h || bin == 2 || (bin == 1 && (caps.core_big_all || d <= caps.mid_cap))) hw += w;
+            }
+            const bool full = bin == 1 && d > caps.mid_cap;
+            nfull += full;
+            group = bin + ((bin > 1 || (bin == 1 && !full)) ? 1u : 0u);
         }
-        if (bin == 1) {
-            const uint32_t half = d <= caps.mid_cap ? 1u : 0u;
-            const unsigned long long wk = w > kWorkMax1 ? kWorkMax1 : w;
-            skey[r] = (1u << 24) | (half << 23) | (uint32_t)(caps.lpt ? (kWorkMax1 - wk) : 0ull);
-            nfull += half ^ 1u;
-        } else {
-            const unsigned long long wk = w > kWorkMax ? kWorkMax : w;
-            skey[r] = (bin << 24) | (uint32_t)(caps.lpt ? (kWorkMax - wk) : 0ull);
-        }
+        const uint32_t key = (group << 15) | (caps.lpt ? work_code(w) : 0u);
+        if (act) elem[r] = ((unsigned long long)key << 32) | r;
+        count_digit(s_h[0], key & 511u, act);
+        count_digit(s_h[1], key >> kDigit, act);
+        if (!act) continue;
         wsum += w;
 #pragma unroll
         for (int q = 0; q < 6; ++q) bw[q] += (bin == (uint32_t)q) ? w : 0ull;
@@ -559,26 +990,37 @@ __global__ void k_schedule(const int64_t* __restrict__ off, const unsigned long 
         for (int i = 0; i < 6; ++i)
             if (s_bw[i]) atomicAdd(&meta->bin_work[i], s_bw[i]);
     }
+    for (uint32_t i = threadIdx.x; i < 1024; i += blockDim.x)
+        if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
+}
+
+__global__ void k_rank(const uint32_t* __restrict__ order, uint32_t n, uint32_t* __restrict__ rank) {
+    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x)
+        rank[order[r]] = r;
+}
+
+// Out-degrees from the offsets (entry n: 0), for the relabelling.
+__global__ void k_dplus(const uint32_t* __restrict__ off, uint32_t n, uint32_t* __restrict__ dplus) {
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r <= n; r += (uint64_t)gridDim.x * blockDim.x)
+        dplus[r] = r < n ? off[r + 1] - off[r] : 0u;
 }
 
 // ---- vertex orders for the hash ids (Section 4.1, reordering)
 
 // In-degree order: larger oriented in-degree d-(r) = deg(r) - d+(r) first, ties by rank.
-__global__ void k_key_indegree(const uint32_t* __restrict__ deg_sorted, const uint32_t* __restrict__ dplus,
+__global__ void k_key_indegree(const unsigned long long* __restrict__ order, const uint32_t* __restrict__ dplus,
                                uint32_t n, unsigned long long* __restrict__ key) {
     for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-        const uint32_t din = deg_sorted[r] - dplus[r];
+        const uint32_t din = (uint32_t)(order[r] >> 32) - dplus[r];  // order[r] = degree << 32 | id
         key[r] = ((unsigned long long)(0xFFFFFFFFu - din) << 32) | r;
     }
 }
 
-// Collective degree W(r) (from the inclusive scan of d+(col[e])), larger first, ties by rank.
-__global__ void k_key_collective(const int64_t* __restrict__ off, const unsigned long long* __restrict__ wscan,
-                                 uint32_t n, unsigned long long* __restrict__ key) {
+// Collective degree W(r), larger first, ties by rank.
+__global__ void k_key_collective(const unsigned long long* __restrict__ work, uint32_t n,
+                                 unsigned long long* __restrict__ key) {
     for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-        const int64_t b = off[r], e = off[r + 1];
-        unsigned long long w = e > b ? wscan[e - 1] - (b ? wscan[b - 1] : 0ull) : 0ull;
-        if (w > 0xFFFFFFFFull) w = 0xFFFFFFFFull;
+        const unsigned long long w = work[r] > 0xFFFFFFFFull ? 0xFFFFFFFFull : work[r];
         key[r] = ((0xFFFFFFFFull - w) << 32) | r;
     }
 }
@@ -671,60 +1113,45 @@ hipError_t clear_record_staging(unsigned long long* tv, const uint32_t* place, u
     return hipGetLastError();
 }
 
-size_t prep_sort_tmp_bytes(uint32_t n, uint64_t m_in) {
+size_t prep_sort_tmp_bytes(uint32_t n, bool relabel, bool scatter) {
     size_t best = 0, sz = 0;
-    const uint32_t nb = id_bits(n);
     unsigned long long* k64 = nullptr;
     uint32_t* u32p = nullptr;
-    if (sort_keys(nullptr, sz, k64, k64, (size_t)m_in, 0, 2 * nb, 0) == hipSuccess && sz > best) best = sz;
-    sz = 0;
-    {
-        auto keys = rocprim::make_transform_iterator(rocprim::make_counting_iterator<uint64_t>(0),
-                                                     CanonKey{u32p, u32p, n, nb, 0ull, nullptr});
-        if (sort_keys(nullptr, sz, keys, k64, (size_t)m_in, 0, 2 * nb, 0) == hipSuccess && sz > best) best = sz;
-    }
-    sz = 0;
-    if (sort_keys(nullptr, sz, k64, k64, (size_t)m_in, nb, 2 * nb, 0) == hipSuccess && sz > best) best = sz;
-    sz = 0;
-    if (sort_keys(nullptr, sz, u32p, u32p, (size_t)m_in, 0, nb < 32 ? nb + 1 : 32, 0) == hipSuccess && sz > best)
-        best = sz;
-    sz = 0;
-    if (rocprim::radix_sort_pairs(nullptr, sz, u32p, u32p, rocprim::counting_iterator<uint32_t>(0), u32p,
-                                  (size_t)n, 0, 32) == hipSuccess && sz > best) best = sz;
-    sz = 0;
-    {
-        auto heads = rocprim::make_transform_iterator(rocprim::make_counting_iterator<uint64_t>(0),
-                                                      HeadOutDegree{u32p, u32p, nullptr});
-        if (rocprim::inclusive_scan(nullptr, sz, heads, k64, (size_t)m_in, rocprim::plus<unsigned long long>()) ==
-                hipSuccess && sz > best) best = sz;
-        sz = 0;
-        if (rocprim::exclusive_scan(nullptr, sz, k64, k64, (unsigned long long)0, (size_t)place_chunks(n) + 1,
-                                    rocprim::plus<unsigned long long>()) == hipSuccess && sz > best) best = sz;
-        sz = 0;
-        auto rheads = rocprim::make_transform_iterator(rocprim::make_counting_iterator<uint64_t>(0),
-                                                       RecordHead{k64, u32p, nullptr, u32p, 1u, 1ull, nullptr});
-        if (rocprim::inclusive_scan(nullptr, sz, rheads, k64, (size_t)m_in, rocprim::plus<unsigned long long>()) ==
-                hipSuccess && sz > best) best = sz;
-        sz = 0;
-    }
-    {
-        size_t q = 0;
-        if (rocprim::radix_sort_pairs(nullptr, q, k64, k64, rocprim::counting_iterator<uint32_t>(0), u32p, (size_t)n, 0,
-                                      64) == hipSuccess && q > best) best = q;
-    }
-    sz = 0;
-    if (sort_pairs(nullptr, sz, u32p, u32p, u32p, (size_t)n, degree_bits(n, m_in), 0) == hipSuccess && sz > best)
-        best = sz;
-    sz = 0;
-    if (sort_pairs(nullptr, sz, u32p, u32p, u32p, (size_t)n, kScheduleBits, 0) == hipSuccess && sz > best) best = sz;
-    sz = 0;
     int64_t* i64p = nullptr;
-    if (rocprim::exclusive_scan(nullptr, sz, u32p, i64p, (unsigned long long)0, (size_t)n + 1,
+    if ((relabel || scatter) &&
+        rocprim::exclusive_scan(nullptr, sz, u32p, i64p, (unsigned long long)0, (size_t)n + 1,
                                 rocprim::plus<unsigned long long>()) == hipSuccess && sz > best) best = sz;
     sz = 0;
-    if (rocprim::radix_sort_pairs(nullptr, sz, k64, k64, rocprim::counting_iterator<uint32_t>(0), u32p,
-                                  (size_t)n, 0, 42) == hipSuccess && sz > best) best = sz;
+    if (rocprim::exclusive_scan(nullptr, sz, k64, k64, (unsigned long long)0, (size_t)place_chunks(n) + 1,
+                                rocprim::plus<unsigned long long>()) == hipSuccess && sz > best) best = sz;
+    sz = 0;
+    if (relabel && rocprim::radix_sort_pairs(nullptr, sz, k64, k64, rocprim::counting_iterator<uint32_t>(0), u32p,
+                                             (size_t)n, 0, 64) == hipSuccess && sz > best) best = sz;
     return best;
+}
+
+PrepZero prep_zero(uint32_t n, uint64_t m_in) {
+    PrepZero z{};
+    const uint32_t nb = id_bits(n);
+    size_t w = kTicketWords + kHistWords;
+    z.deg = w;     w += ((size_t)n + 1 + 3) & ~(size_t)3;
+    z.first = w;   w += 2 * (((size_t)m_in + 63) / 64 + 1);
+    w = (w + 3) & ~(size_t)3;
+    z.status = w;
+    const uint64_t tm = pass_tiles(m_in, 8), tu = pass_tiles(m_in, 4), tn = pass_tiles(n, 8);
+    const uint64_t words = std::max<uint64_t>({tm * 512, upper_digit(nb) ? tu << upper_digit(nb) : 0, tn * 512});
+    w += 2 * (size_t)words;
+    z.words = w;
+    return z;
+}
+
+hipError_t prep_init() {  // once per device: the counters of k_upper_count take up to 128 KB of LDS
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_upper_count),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 4 << kCounterBits);
+}
+
+inline uint32_t work_grid(uint32_t n) {
+    return std::min(grid_for((uint64_t)n * kWorkLanes), 16384u);
 }
 
 // Relabel the oriented rank-space CSR into another order of hash ids (the orientation stays).
@@ -732,18 +1159,16 @@ hipError_t relabel(uint32_t n, const GraphDev& g, const BuildTemp& t, const Batc
                    uint64_t m_in, hipStream_t stream) {
     size_t tmp;
     const uint32_t wave_grid = std::min<uint32_t>(grid_for((uint64_t)n * 64), 8192u);
+    hipLaunchKernelGGL(k_dplus, dim3(grid_for((uint64_t)n + 1)), dim3(kThreads), 0, stream, g.off32, n, t.dplus);
+    TC_TRY(hipGetLastError());
     if (order == 1) {
-        hipLaunchKernelGGL(k_key_indegree, dim3(grid_for(n)), dim3(kThreads), 0, stream,
-                           reinterpret_cast<const uint32_t*>(t.skey_a), t.dplus, n, t.rk_a);
+        hipLaunchKernelGGL(k_key_indegree, dim3(grid_for(n)), dim3(kThreads), 0, stream, t.skey_a, t.dplus, n, t.rk_a);
         TC_TRY(hipGetLastError());
     } else {
-        unsigned long long* wscan = t.keys_a;
-        auto heads = rocprim::make_transform_iterator(rocprim::make_counting_iterator<uint64_t>(0),
-                                                      HeadOutDegree{g.col, t.dplus, g.meta});
-        tmp = t.sort_tmp_bytes;
-        TC_TRY(rocprim::inclusive_scan(t.sort_tmp, tmp, heads, wscan, (size_t)m_in,
-                                       rocprim::plus<unsigned long long>(), stream));
-        hipLaunchKernelGGL(k_key_collective, dim3(grid_for(n)), dim3(kThreads), 0, stream, g.off, wscan, n, t.rk_a);
+        unsigned long long* work = t.skey_b;
+        hipLaunchKernelGGL(k_work_rows, dim3(work_grid(n)), dim3(kThreads), 0, stream, g.off32, g.col, n, work);
+        TC_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_key_collective, dim3(grid_for(n)), dim3(kThreads), 0, stream, work, n, t.rk_a);
         TC_TRY(hipGetLastError());
         tmp = t.sort_tmp_bytes;
         TC_TRY(rocprim::radix_sort_pairs(t.sort_tmp, tmp, t.rk_a, t.rk_b, rocprim::counting_iterator<uint32_t>(0),
@@ -790,96 +1215,171 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
                       hipStream_t stream) {
     const uint32_t nb = id_bits(n);
     const unsigned long long sentinel = (2 * nb >= 64) ? ~0ull : ((1ull << (2 * nb)) - 1);
+    const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
     size_t tmp = t.sort_tmp_bytes;
 
+    // Zeroed memory: tickets and digit histograms, degrees, first bits, look-back words.
+    uint32_t* next_ticket = t.zero;
+    uint32_t* next_hist = t.zero + kTicketWords;
+    uint32_t epoch = 0;
+    auto take_hist = [&](uint32_t words) {
+        uint32_t* h = next_hist;
+        next_hist += words;
+        return h;
+    };
     TC_TRY(fill_u32(g.meta, 0, sizeof(GraphMeta) / 4, stream));
-    TC_TRY(fill_u32(t.deg, 0, (size_t)n + 1, stream));
-    TC_TRY(fill_u32(t.dplus, 0, (size_t)n + 1, stream));
+    TC_TRY(fill_u32(t.zero, 0, t.zero_words, stream));
+    // two workgroups of 1024 threads per CU: each ends with an atomic per digit
+    const uint32_t hist_grid = (uint32_t)std::min<uint64_t>((m_in + 4095) / 4096, 2 * (uint64_t)cu_count);
 
-    // 1-2: canonical keys, sort (batches form the keys first: each sample's graph is searched for).
-    tmp = t.sort_tmp_bytes;
-    if (batch) {
-        hipLaunchKernelGGL(k_canon_batch, dim3(grid_for(m_in)), dim3(kThreads), 0, stream, src, dst, m_in, n, nb,
-                           sentinel, batch->voff, batch->eoff, batch->k, t.keys_a, g.meta);
-        TC_TRY(hipGetLastError());
-        TC_TRY(sort_keys(t.sort_tmp, tmp, t.keys_a, t.keys_b, (size_t)m_in, 0, 2 * nb, stream));
-    } else {
-        auto keys = rocprim::make_transform_iterator(rocprim::make_counting_iterator<uint64_t>(0),
-                                                     CanonKey{src, dst, n, nb, sentinel, g.meta});
-        TC_TRY(sort_keys(t.sort_tmp, tmp, keys, t.keys_b, (size_t)m_in, 0, 2 * nb, stream));
-    }
-
-    // 3: distinct edges and degree (lower ids in the run pass, upper ids from runs of the sorted upper
-    // endpoints), rank in (degree, id) order (stable sort keeps ids ascending among equal degrees).
+    // 1-2: canonical keys (sorted into keys_b by all but their `low` lowest bits; batches form the keys
+    // first: each sample's graph is searched for).
+    const uint32_t cp = canon_passes(nb), low = canon_low(nb);
     {
-        uint32_t* up_a = t.aux;
-        uint32_t* up_b = t.aux + m_in;
-        const uint64_t chunks = (m_in + kRunChunk - 1) / kRunChunk;  // one wavefront each (4 per block)
-        hipLaunchKernelGGL(k_runs, dim3(grid_for(chunks * 64)), dim3(kThreads), 0, stream, t.keys_b, nb, m_in, sentinel,
-                           up_a, t.deg, g.meta);
+        uint32_t* hist = take_hist(512 * cp);
+        auto buf = [&](uint32_t writes_left) { return writes_left % 2 ? t.keys_b : t.keys_a; };  // the last write: keys_b
+        const CanonKey canon{src, dst, n, nb, sentinel};
+        unsigned long long* in = nullptr;
+        if (batch) {
+            in = buf(cp + 1);
+            hipLaunchKernelGGL(k_canon_batch, dim3(hist_grid), dim3(1024), 0, stream, src, dst, m_in, n, nb, sentinel,
+                               batch->voff, batch->eoff, batch->k, low, cp, in, hist, g.meta);
+        } else {
+            hipLaunchKernelGGL(k_canon_hist, dim3(hist_grid), dim3(1024), 0, stream, canon, m_in, low, cp, hist, g.meta);
+        }
         TC_TRY(hipGetLastError());
-        tmp = t.sort_tmp_bytes;
-        TC_TRY(sort_keys(t.sort_tmp, tmp, up_a, up_b, (size_t)m_in, 0, nb < 32 ? nb + 1 : 32, stream));
-        hipLaunchKernelGGL(k_degree, dim3(grid_for(m_in)), dim3(kThreads), 0, stream, up_b, m_in, g.meta, t.deg);
-        TC_TRY(hipGetLastError());
+        for (uint32_t p = 0; p < cp; ++p) {
+            unsigned long long* out = buf(cp - p);
+            const uint32_t shift = low + kDigit * p;
+            if (p > 0)
+                TC_TRY((radix_pass<kDigit, true, unsigned long long>(LoadKey{in}, StoreKey{out}, m_in, nullptr, shift,
+                                                               hist + 512 * p, t.status, ++epoch, next_ticket++, stream)));
+            else if (batch)
+                TC_TRY((radix_pass<kDigit, false, unsigned long long>(LoadKey{in}, StoreKey{out}, m_in, nullptr, shift,
+                                                               hist + 512 * p, t.status, ++epoch, next_ticket++, stream)));
+            else
+                TC_TRY((radix_pass<kDigit, false, unsigned long long>(canon, StoreKey{out}, m_in, nullptr, shift,
+                                                               hist + 512 * p, t.status, ++epoch, next_ticket++, stream)));
+            in = out;
+        }
     }
-    uint32_t* deg_sorted = reinterpret_cast<uint32_t*>(t.skey_a);
-    tmp = t.sort_tmp_bytes;
-    TC_TRY(sort_pairs(t.sort_tmp, tmp, t.deg, deg_sorted, t.order, (size_t)n, degree_bits(n, m_in), stream));
-    hipLaunchKernelGGL(k_rank, dim3(grid_for(n)), dim3(kThreads), 0, stream, t.order, n, g.rank);
-    TC_TRY(hipGetLastError());
-    if (batch) {
-        hipLaunchKernelGGL(k_gid, dim3(grid_for(n)), dim3(kThreads), 0, stream, t.order, n, batch->voff, batch->k,
-                           g.gid);
+
+    // 2-3: distinct edges and degrees, rank in (degree, id) order (the sort is stable).
+    {
+        const uint32_t ud = upper_digit(nb), sub = ud ? nb - ud : nb;
+        uint32_t* uhist = take_hist(1024);
+        const uint64_t tiles = (m_in + kDedupTile - 1) / kDedupTile;
+        hipLaunchKernelGGL(k_dedup, dim3((uint32_t)std::min<uint64_t>(tiles, 2 * (uint64_t)cu_count)), dim3(kDedupThreads), 0, stream,
+                           t.keys_b, nb, low, m_in, sentinel, t.first, t.deg, uhist, ud ? 1u << ud : 0u, sub,
+                           upper_atomics(nb), g.meta);
         TC_TRY(hipGetLastError());
+        const LoadUpper upper{t.keys_b, t.first, mask};
+        uint32_t* ids = nullptr;
+        if (ud) {
+            ids = t.aux;
+            if (ud == 9)
+                TC_TRY((radix_pass<9, false, uint32_t>(upper, StoreId{ids}, m_in, nullptr, sub, uhist, t.status, ++epoch,
+                                                next_ticket++, stream)));
+            else
+                TC_TRY((radix_pass<10, false, uint32_t>(upper, StoreId{ids}, m_in, nullptr, sub, uhist, t.status, ++epoch,
+                                                 next_ticket++, stream)));
+        }
+        if (!upper_atomics(nb)) {
+            const uint32_t unit = (uint32_t)std::max<uint64_t>(4096, std::min<uint64_t>(kUpperUnit, m_in / 512));
+            const uint64_t units = (m_in + unit - 1) / unit + (ud ? 1u << ud : 1u);
+            hipLaunchKernelGGL(k_upper_count, dim3((uint32_t)std::min<uint64_t>(units, 2 * (uint32_t)cu_count)), dim3(1024),
+                               4u << std::min(sub, kCounterBits), stream, ids, upper, m_in, ud ? 1u << ud : 1u, sub, n,
+                               uhist, unit, t.deg);
+            TC_TRY(hipGetLastError());
+        }
+    }
+    {
+        const uint32_t passes = (degree_bits(n, m_in) + kDigit - 1) / kDigit;
+        uint32_t* hist = take_hist(512 * passes);
+        hipLaunchKernelGGL(k_degree_hist, dim3(std::min(((n - 1) / 4096) + 1, 512u)), dim3(1024), 0, stream, t.deg, n,
+                           passes, hist);
+        TC_TRY(hipGetLastError());
+        auto buf = [&](uint32_t writes_left) { return writes_left % 2 ? t.skey_a : t.skey_b; };  // the last write: skey_a
+        const StoreRank last{t.skey_a, g.rank, batch ? batch->voff : nullptr, batch ? batch->k : 0u, g.gid};
+        for (uint32_t p = 0; p < passes; ++p) {
+            const uint32_t* h = hist + 512 * p;
+            const uint32_t shift = 32 + kDigit * p;
+            unsigned long long* in = buf(passes - p + 1);
+            unsigned long long* out = buf(passes - p);
+            const bool end = p + 1 == passes;
+            const LoadDegree deg{t.deg};
+            if (p == 0 && end)
+                TC_TRY((radix_pass<kDigit, true, unsigned long long>(deg, last, n, nullptr, shift, h, t.status, ++epoch,
+                                                               next_ticket++, stream)));
+            else if (p == 0)
+                TC_TRY((radix_pass<kDigit, true, unsigned long long>(deg, StoreKey{out}, n, nullptr, shift, h, t.status, ++epoch,
+                                                               next_ticket++, stream)));
+            else if (end)
+                TC_TRY((radix_pass<kDigit, true, unsigned long long>(LoadKey{in}, last, n, nullptr, shift, h, t.status, ++epoch,
+                                                               next_ticket++, stream)));
+            else
+                TC_TRY((radix_pass<kDigit, true, unsigned long long>(LoadKey{in}, StoreKey{out}, n, nullptr, shift, h, t.status,
+                                                               ++epoch, next_ticket++, stream)));
+        }
     }
 
     // 4-5: orientation and CSR in rank space.
+    unsigned long long* const osorted = reinterpret_cast<unsigned long long*>(t.aux);
     if (!caps.scatter_csr) {
-        // Sort the oriented keys by row only (the high nb bits; radix sort is stable, so each list keeps
-        // the canonical-key order; lists need no order for hashing): rows come out contiguous.  The
-        // sentinel's row bits exceed every valid row, so unused entries sort last.
-        unsigned long long* okeys = t.keys_a;
-        unsigned long long* osorted = reinterpret_cast<unsigned long long*>(t.aux);
-        hipLaunchKernelGGL(k_orient_keys, dim3(grid_for(m_in)), dim3(kThreads), 0, stream, t.keys_b, nb, m_in, g.rank,
-                           sentinel, okeys);
+        // Sort the oriented keys by row only (the high nb bits; the passes are stable, so each list keeps
+        // the order of the canonical keys; lists need no order for hashing): rows come out contiguous, in
+        // aux.
+        const uint32_t passes = row_passes(nb);
+        auto buf = [&](uint32_t writes_left) { return writes_left % 2 ? osorted : t.keys_a; };
+        uint32_t* hist = take_hist(512 * passes);
+        unsigned long long* in = buf(passes + 1);
+        hipLaunchKernelGGL(k_orient_keys, dim3(hist_grid), dim3(1024), 0, stream, t.keys_b, nb, m_in,
+                           t.first, g.rank, passes, in, hist);
         TC_TRY(hipGetLastError());
-        tmp = t.sort_tmp_bytes;
-        TC_TRY(sort_keys(t.sort_tmp, tmp, okeys, osorted, (size_t)m_in, nb, 2 * nb, stream));
-        hipLaunchKernelGGL(k_csr_runs, dim3(grid_for(m_in)), dim3(kThreads), 0, stream, osorted, nb, m_in, g.meta,
-                           t.dplus, g.col);
+        for (uint32_t p = 0; p < passes; ++p) {
+            unsigned long long* out = buf(passes - p);
+            const uint32_t shift = nb + kDigit * p;
+            if (p == 0)
+                TC_TRY((radix_pass<kDigit, false, unsigned long long>(LoadFirst{in, t.first}, StoreKey{out}, m_in, nullptr, shift,
+                                                               hist, t.status, ++epoch, next_ticket++, stream)));
+            else
+                TC_TRY((radix_pass<kDigit, true, unsigned long long>(LoadKey{in}, StoreKey{out}, m_in, &g.meta->m, shift,
+                                                               hist + 512 * p, t.status, ++epoch, next_ticket++, stream)));
+            in = out;
+        }
+        hipLaunchKernelGGL(k_csr, dim3(std::min(grid_for(std::max<uint64_t>(m_in, n)), 16384u)), dim3(kThreads), 0, stream,
+                           osorted, nb, g.meta, n, g.off, g.off32, g.col);
         TC_TRY(hipGetLastError());
-        tmp = t.sort_tmp_bytes;
-        TC_TRY(rocprim::exclusive_scan(t.sort_tmp, tmp, t.dplus, g.off, (unsigned long long)0, (size_t)n + 1,
-                                       rocprim::plus<unsigned long long>(), stream));
     } else {
         // Counting sort: out-degrees, offsets, then an atomic scatter (list order unspecified).
+        TC_TRY(fill_u32(t.dplus, 0, (size_t)n + 1, stream));
         hipLaunchKernelGGL(k_orient_count, dim3(grid_for(m_in)), dim3(kThreads), 0, stream, t.keys_b, nb, m_in,
-                           sentinel, g.rank, t.dplus);
+                           t.first, g.rank, t.dplus);
         TC_TRY(hipGetLastError());
         tmp = t.sort_tmp_bytes;
         TC_TRY(rocprim::exclusive_scan(t.sort_tmp, tmp, t.dplus, g.off, (unsigned long long)0, (size_t)n + 1,
                                        rocprim::plus<unsigned long long>(), stream));
         TC_TRY(fill_u32(t.deg, 0, (size_t)n + 1, stream));
         hipLaunchKernelGGL(k_orient_fill, dim3(grid_for(m_in)), dim3(kThreads), 0, stream, t.keys_b, nb, m_in,
-                           sentinel, g.rank, g.off, t.deg, g.col);
+                           t.first, g.rank, g.off, t.deg, g.col);
+        TC_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_narrow, dim3(grid_for((uint64_t)n + 1)), dim3(kThreads), 0, stream, g.off, (uint64_t)n + 1,
+                           g.off32);
         TC_TRY(hipGetLastError());
     }
 
     // 5b (optional): hash ids in another vertex order.
-    if (caps.order) TC_TRY(relabel(n, g, t, batch, caps.order, m_in, stream));
+    if (caps.order) {
+        TC_TRY(relabel(n, g, t, batch, caps.order, m_in, stream));
+        hipLaunchKernelGGL(k_narrow, dim3(grid_for((uint64_t)n + 1)), dim3(kThreads), 0, stream, g.off, (uint64_t)n + 1,
+                           g.off32);
+        TC_TRY(hipGetLastError());
+    }
 
-    hipLaunchKernelGGL(k_narrow, dim3(grid_for((uint64_t)n + 1)), dim3(kThreads), 0, stream, g.off, (uint64_t)n + 1,
-                       g.off32);
-    TC_TRY(hipGetLastError());
-
-    // 6: bins and largest-work-first order; W(u) from a scan of d+(col[e]).
-    unsigned long long* wscan = reinterpret_cast<unsigned long long*>(t.keys_a);
-    // 5c with it: records are placed first ({p(r), d+(r)} per rank), then the scan's gather of d+(v)
-    // reads v's placement, whose p(v) goes into the records (the sorted oriented keys give each edge's
-    // row; no relabelling or counting-sort build here).  Rows without edges get their header in
-    // k_schedule.
+    // 6: W(u), bins and largest-work-first order.  5c with it: records are placed first ({p(r), d+(r)} per
+    // rank), then k_work reads v's placement for d+(v) and writes p(v) into the records.
     uint32_t* rec = (caps.records && !caps.order && !caps.scatter_csr) ? g.rec : nullptr;
+    unsigned long long* const work = t.skey_b;
     if (rec) {
         const uint64_t chunks = place_chunks(n);
         hipLaunchKernelGGL(k_place_size, dim3(grid_for(chunks + 1)), dim3(kThreads), 0, stream, g.off32, n,
@@ -893,40 +1393,47 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         hipLaunchKernelGGL(k_place_write, dim3(grid_for(chunks + 1)), dim3(kThreads), 0, stream, g.off32, n,
                            cbase, place);
         TC_TRY(hipGetLastError());
-        const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
-        auto heads = rocprim::make_transform_iterator(
-            rocprim::make_counting_iterator<uint64_t>(0),
-            RecordHead{reinterpret_cast<const unsigned long long*>(t.aux), g.off32, place, rec, nb, mask, g.meta});
-        tmp = t.sort_tmp_bytes;
-        TC_TRY(rocprim::inclusive_scan(t.sort_tmp, tmp, heads, wscan, (size_t)m_in,
-                                       rocprim::plus<unsigned long long>(), stream));
-    } else {
-        auto heads = rocprim::make_transform_iterator(rocprim::make_counting_iterator<uint64_t>(0),
-                                                      HeadOutDegree{g.col, t.dplus, g.meta});
-        tmp = t.sort_tmp_bytes;
-        TC_TRY(rocprim::inclusive_scan(t.sort_tmp, tmp, heads, wscan, (size_t)m_in,
-                                       rocprim::plus<unsigned long long>(), stream));
-    }
-    if (caps.pack_cap) {
-        hipLaunchKernelGGL(k_pack_census, dim3(std::min(grid_for(n), 1024u)), dim3(kThreads), 0, stream, g.off, wscan,
-                           n, caps, g.meta);
+        hipLaunchKernelGGL(k_record_empty, dim3(grid_for(n)), dim3(kThreads), 0, stream, place, n, rec);
         TC_TRY(hipGetLastError());
     }
-    // at most 1024 blocks: each block ends with a few global atomics on the same summary words
-    uint32_t* skey = reinterpret_cast<uint32_t*>(t.skey_a);
-    hipLaunchKernelGGL(k_schedule, dim3(std::min(grid_for(n), 1024u)), dim3(kThreads), 0, stream, g.off, wscan, n, caps, g.meta,
-                       skey, rec, rec ? g.place : nullptr);
+    if (caps.order || caps.scatter_csr) {
+        hipLaunchKernelGGL(k_work_rows, dim3(work_grid(n)), dim3(kThreads), 0, stream, g.off32, g.col, n, work);
+    } else {
+        TC_TRY(fill_u32(work, 0, 2 * (size_t)n, stream));
+        const uint32_t grid = (uint32_t)std::min<uint64_t>((m_in + 1023) / 1024, 16384);
+        if (rec)
+            hipLaunchKernelGGL(k_work<true>, dim3(grid), dim3(kThreads), 0, stream, osorted, nb, g.off32,
+                               reinterpret_cast<const uint2*>(g.place), rec, g.meta, work);
+        else
+            hipLaunchKernelGGL(k_work<false>, dim3(grid), dim3(kThreads), 0, stream, osorted, nb, g.off32, nullptr, nullptr,
+                               g.meta, work);
+    }
     TC_TRY(hipGetLastError());
-    tmp = t.sort_tmp_bytes;
-    TC_TRY(sort_pairs(t.sort_tmp, tmp, skey, reinterpret_cast<uint32_t*>(t.skey_b), g.items, (size_t)n, kScheduleBits,
-                      stream));
+    if (caps.pack_cap && !(caps.force_hub || caps.force_big || caps.force_wg)) {
+        hipLaunchKernelGGL(k_pack_census, dim3(std::min((n - 1) / 1024 + 1, 2 * (uint32_t)cu_count)), dim3(1024), 0, stream,
+                           g.off32, work, n, caps, g.meta);
+        TC_TRY(hipGetLastError());
+    }
+    // one block of 1024 threads per CU: each ends with some 20 atomics on the same summary words (R-MAT 20:
+    // 1024 blocks of 256 threads spent 0.1 ms on them)
+    {
+        uint32_t* hist = take_hist(1024);
+        hipLaunchKernelGGL(k_schedule, dim3(std::min((n - 1) / 1024 + 1, (uint32_t)cu_count)), dim3(1024), 0, stream, g.off32, work, n,
+                           caps, g.meta, t.skey_a, hist);
+        TC_TRY(hipGetLastError());
+        TC_TRY((radix_pass<kDigit, true, unsigned long long>(LoadKey{t.skey_a}, StoreKey{t.skey_b}, n, nullptr, 32, hist,
+                                                       t.status, ++epoch, next_ticket++, stream)));
+        TC_TRY((radix_pass<kDigit, true, unsigned long long>(LoadKey{t.skey_b}, StoreItem{g.items}, n, nullptr, 32 + kDigit,
+                                                       hist + 512, t.status, ++epoch, next_ticket++, stream)));
+    }
     // 7: block words of the core path and the schedule of the lists cut before the core.
     if (caps.core_bits) {
         CoreBuild c{};
         c.meta = g.meta;
         c.off = g.off32;
-        c.okeys = reinterpret_cast<const unsigned long long*>(t.aux);
-        c.mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
+        c.okeys = osorted;
+        c.mask = mask;
+        c.nb = nb;
         c.col = g.col;
         c.blk = reinterpret_cast<uint32_t*>(g.blk);
         c.bl = g.bl;
@@ -937,6 +1444,7 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         c.cls = t.order;
         c.hist = t.deg;
         c.n = n;
+        c.m_in = m_in;
         c.S = caps.core_bits;
         c.c0 = caps.core_first;
         c.magic = core_magic(c.S);

@@ -1,0 +1,90 @@
+"""The build (canonical sort, distinct edges, degrees, rank, CSR, schedule) against the oracle.
+
+Sizes sit at the edges of its tiles (2048 keys of the distinct-edge pass, 2048, 4096 and 18432 elements of a
+sort pass, 28672 of the upper-id partition), at the id widths where the number of passes or the
+treatment of the upper ids changes (2^9, 2^12, 2^15, 2^16, 2^24, 2^25 ids), and at inputs made of
+duplicates or of self-loops, whose groups of equal keys run over many tiles.
+"""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(g):
+    from paper_2103_08053_amd import Context
+    print(f"[gpu] build {g.name} n={g.n} m_in={g.m_in}", flush=True)
+    want = oracle.count(g.n, g.src, g.dst, per_vertex=True)
+    gr = Context(0).build(g.src, g.dst, g.n)
+    info = gr.info()
+    assert (info.m, info.wedges_plus, info.max_dplus) == (want.m, want.wedges_plus, want.max_dplus)
+    assert sum(gr.bin_work()) == want.wedges_plus
+    total, pv = gr.count(per_vertex=True)
+    assert total == want.total
+    assert (pv.cpu().numpy().astype(np.uint64) == want.per_vertex).all()
+
+
+def _pairs(n, m, seed, distinct=None):
+    """m random pairs on n ids; with `distinct`, drawn from that many pairs."""
+    rng = np.random.default_rng(seed)
+    s = rng.integers(0, n, distinct or m, dtype=np.uint32)
+    d = rng.integers(0, n, distinct or m, dtype=np.uint32)
+    if distinct:
+        pick = rng.integers(0, distinct, m)
+        s, d = s[pick], d[pick]
+        flip = rng.random(m) < 0.5
+        s, d = np.where(flip, d, s), np.where(flip, s, d)
+    return gg.EdgeList(n, s, d, f"pairs{n}_{m}_{distinct}")
+
+
+@pytest.mark.parametrize("m", [1, 2, 63, 64, 65, 2047, 2048, 2049, 4096, 4097, 7168, 7169, 14337])
+@pytest.mark.parametrize("n", [3, 60, 700])
+def test_build_tile_edges(n, m):
+    _check(_pairs(n, m, seed=m + n))
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 4096, 4097, 32768, 32769, 65536, 65537, 131073, 1 << 24, (1 << 24) + 1,
+                               (1 << 25) + 1, (1 << 27) + 3])
+def test_build_id_widths(n):
+    g = gg.rmat(12, 16, seed=n % 97)
+    spread = np.sort(np.random.default_rng(n % 89).choice(n, min(n, g.n), replace=False)).astype(np.uint32)
+    keep = (g.src < len(spread)) & (g.dst < len(spread))
+    _check(gg.EdgeList(n, spread[g.src[keep]], spread[g.dst[keep]], f"rmat12 on {n} ids"))
+
+
+@pytest.mark.parametrize("n,distinct", [(2, 1), (5, 4), (900, 1), (900, 3000), (70000, 50), (70000, 30000),
+                                        (1 << 20, 2), (1 << 20, 90000)])
+def test_build_duplicates(n, distinct):
+    _check(_pairs(n, 150_001, seed=n + distinct, distinct=distinct))
+
+
+@pytest.mark.parametrize("n", [3, 4096, 100_000])
+def test_build_self_loops_and_a_few_edges(n):
+    rng = np.random.default_rng(n)
+    s = np.full(60_000, n - 1, np.uint32)
+    d = s.copy()
+    s[::3] = rng.integers(0, n, len(s[::3]))
+    d[::3] = s[::3]
+    s[:300], d[:300] = rng.integers(0, n, 300), rng.integers(0, n, 300)
+    _check(gg.EdgeList(n, s, d, f"loops{n}"))
+
+
+@pytest.mark.parametrize("m", [(1 << 19) - 1, 1 << 19, 3_499_999, 3_500_000, 190 * 18432 + 1])  # tile sizes
+def test_build_tile_sizes(m):
+    _check(_pairs(300_000, m, seed=m))
+    _check(gg.dirty(gg.rmat(17, 12, seed=m % 31), seed=3))
+
+
+@pytest.mark.parametrize("flags", [0x8, 0x40, 0x80, 0x4000, 0x1000])
+def test_build_variants(flags):
+    from paper_2103_08053_amd import Context, Params
+    g = gg.dirty(gg.rmat(14, 16, seed=11), seed=5)
+    print(f"[gpu] build flags {flags:#x} n={g.n} m_in={g.m_in}", flush=True)
+    want = oracle.count(g.n, g.src, g.dst, per_vertex=True)
+    gr = Context(0, Params(flags=flags)).build(g.src, g.dst, g.n)
+    assert gr.info().wedges_plus == want.wedges_plus
+    total, pv = gr.count(per_vertex=True)
+    assert total == want.total and (pv.cpu().numpy().astype(np.uint64) == want.per_vertex).all()
