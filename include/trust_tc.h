@@ -322,7 +322,7 @@ tc_status tc_graph_k(const tc_graph* g, uint32_t* k);
  * the triangles through each vertex of handle g (input-id order; may be NULL when n_g = 0).
  * d_ws: device workspace of ws_bytes (TC_E_NOMEM if smaller than these graphs need); its contents
  * are clobbered.  Asynchronous on `stream`: the handles' builds must be ordered before it (same
- * stream, or an event), and the call copies a header and one 80-byte descriptor per handle from
+ * stream, or an event), and the call copies a header and one 88-byte descriptor per handle from
  * context-owned pinned host memory into the start of d_ws (pinned host buffers are the only memory
  * a context allocates for itself, apart from the handles).  Calls that share a workspace must be
  * ordered on one stream.

@@ -283,6 +283,8 @@ Layout layout(const tc_context* ctx, const tc_params& p, uint32_t n, uint64_t m_
     L.s_gid = o;   o = align_up(o + (batch ? sizeof(uint32_t) * (size_t)n : 0));
     L.s_rec = o;   o = align_up(o + (L.records ? sizeof(uint32_t) * tc::record_words(n, m_in) : 0));
     L.s_place = o; o = align_up(o + (L.records ? 8 * ((size_t)n + 1) : 0));
+    L.edge_lists = !(p.flags & (TC_F_ORDER_INDEGREE | TC_F_ORDER_COLLECTIVE | TC_F_SCATTER_CSR));
+    L.s_elist = o;  o = align_up(o + (L.edge_lists ? 8 * (size_t)m_in : 0));
     core_shape(ctx, p, bin_caps(ctx, p), n, m_in, batch, L);
     const bool core = L.core_bits != 0;
     L.s_blk = o;    o = align_up(o + (core ? 16 * (tc::core_start((uint32_t)m_in, n) + 1) : 0));
@@ -343,6 +345,7 @@ tc::GraphDev graph_ptrs(void* storage, const Layout& L) {
     g.gid = nullptr;
     g.rec = L.records ? reinterpret_cast<uint32_t*>(b + L.s_rec) : nullptr;
     g.place = L.records ? reinterpret_cast<uint32_t*>(b + L.s_place) : nullptr;
+    g.elist = L.edge_lists ? reinterpret_cast<uint2*>(b + L.s_elist) : nullptr;
     const bool core = L.core_bits != 0;
     g.blk = core ? reinterpret_cast<uint4*>(b + L.s_blk) : nullptr;
     g.bl = core ? reinterpret_cast<uint2*>(b + L.s_bl) : nullptr;
@@ -563,6 +566,7 @@ tc_status count_into(tc_context* ctx, const tc_graph* g, uint64_t* d_totals, uin
     if (tc_status st = launch_shapes(ctx, g, pv, &sh)) return st;
     if (sh.grid_hub < a.hub_wgs) a.hub_wgs = sh.grid_hub;
     a.end = a.off + 1;
+    a.elist = g->dev.elist;
     HIP_TRY(ctx, tc::fill_u32(a.heads, 0, tc::kHeadWords, s));
     HIP_TRY(ctx, tc::fill_u32(d_totals, 0, 2 * (size_t)g->k, s));
     if (pv) {
@@ -619,6 +623,7 @@ tc_status count_into(tc_context* ctx, const tc_graph* g, uint64_t* d_totals, uin
         a.meta = g->dev.rest_meta;
         a.items = g->dev.rest_items;
         a.end = g->dev.rend;
+        a.elist = nullptr;
         a.heads += 1;  // other words of the same lines
         if (tc_status st = buckets()) return st;
     }
@@ -1330,6 +1335,8 @@ tc_status count_graphs(tc_context* ctx, uint32_t k, tc_graph* const* graphs, uin
         d.items = G->dev.items;
         d.rank = G->dev.rank;
         d.gid = G->dev.gid;
+        // (many-graph counts read lists through col, also those of a graph with records)
+        d.elist = G->dev.rec ? nullptr : G->dev.elist;
         d.totals = reinterpret_cast<unsigned long long*>(d_totals + t0);
         d.out = pv ? reinterpret_cast<unsigned long long*>(d_per_vertex[g]) : nullptr;
         d.tv0 = tv0;

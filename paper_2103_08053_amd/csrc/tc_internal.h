@@ -44,7 +44,9 @@ struct GraphMeta {
     // kCoreMinWork (the first of the bin), work of all owners the path would take, edges into the core
     unsigned int heavy3, pad0;
     unsigned long long heavy_work, core_edges;
-    unsigned int pad[30];
+    // owners (d+ >= 2) and W+, known before the W(u) (0 where the build has no sorted edges)
+    unsigned long long pre_work, pre_owners;
+    unsigned int pad[26];
 };
 static_assert(sizeof(GraphMeta) == 256, "meta is one 256-byte block");
 
@@ -54,8 +56,14 @@ static_assert(sizeof(GraphMeta) == 256, "meta is one 256-byte block");
 // S << (32 - S) ranks (all of them where n is smaller).
 constexpr uint32_t kCoreMinBits = 20;
 constexpr uint64_t kCoreMinWork = 1024;
+// Graphs of little work per owner (mean W(u) at most this) get their edges' list bounds (GraphDev::elist):
+// where lists are short, finding them costs the count as much as reading them.
+constexpr uint64_t kLightMeanWork = 512;
+__host__ __device__ inline bool light_on(const GraphMeta& m) {
+    return m.pre_owners > 0 && m.pre_work <= kLightMeanWork * m.pre_owners;
+}
 __host__ __device__ inline bool core_on(const GraphMeta& m) {
-    return m.heavy_work > 0 && 2 * m.heavy_work >= m.wplus && 4 * m.core_edges >= m.m;
+    return !light_on(m) && m.heavy_work > 0 && 2 * m.heavy_work >= m.wplus && 4 * m.core_edges >= m.m;
 }
 // First quad (16 bytes) of row r's block words when its list starts at col[off]: rows in order, each
 // with room for one word per id padded to whole quads (ceil4(d) <= d + 3).
@@ -202,6 +210,9 @@ struct GraphDev {
                         // r's record at p(r) holds d+(r), then rec_id(p(v)) of each out-neighbour v
     uint32_t* place;    // [2 (n + 1)] record layout: {p(r), d+(r)} of every rank r; entry n holds the
                         // records' extent (words up to the end of the last one)
+    uint2* elist;       // [m_in] light graphs: list {start, length} of every edge's head, edges in row order
+                        // (starts as the count reads lists: in col, or in rec); null where the rows are not
+                        // in rank order (relabelled and counting-sort builds)
     // core path only, else null
     uint4* blk;         // [core_start(m_in, n)] block words of every list
     uint2* bl;          // [n] {first quad, quads} of each list's block words
@@ -271,7 +282,7 @@ struct PrepZero {  // word offsets in BuildTemp::zero
 struct Layout {
     size_t storage, temp, scratch;
     // storage offsets
-    size_t s_meta, s_off, s_off32, s_col, s_rank, s_items, s_gid, s_rec, s_place, s_blk, s_bl, s_rend, s_rmeta,
+    size_t s_meta, s_off, s_off32, s_col, s_rank, s_items, s_gid, s_rec, s_place, s_elist, s_blk, s_bl, s_rend, s_rmeta,
         s_ritems;
     // temp offsets
     size_t t_keys_a, t_keys_b, t_aux, t_zero, t_dplus, t_order, t_skey_a, t_skey_b, t_rk_a, t_rk_b, t_off2, t_place,
@@ -280,6 +291,7 @@ struct Layout {
     PrepZero zero;
     bool relabel;  // temp holds the relabelling arrays
     bool records;  // storage holds the record layout, per-vertex scratch is indexed by record id
+    bool edge_lists;  // storage holds list bounds per edge
     uint32_t core_bits, core_first;  // storage holds the core path's layout (BinCaps)
     bool core_big_all;
     // scratch offsets
@@ -300,13 +312,14 @@ struct MultiDesc {
     const uint32_t* items;
     const uint32_t* rank;            // [n] input id -> rank (for the per-vertex gather)
     const uint32_t* gid;             // batch handles: graph of each rank; else null
+    const uint2* elist;              // GraphDev::elist
     unsigned long long* totals;      // the handle's k totals (one for a single graph)
     unsigned long long* out;         // per-vertex output, input-id order, or null
     unsigned long long tv0;          // first entry of the handle's per-vertex staging
     uint32_t n;
     uint32_t wide;                   // 64-bit list addressing in the probe
 };
-static_assert(sizeof(MultiDesc) == 80, "descriptor layout is shared with the host");
+static_assert(sizeof(MultiDesc) == 88, "descriptor layout is shared with the host");
 struct MultiHeader {
     uint32_t k;                      // graph handles
     uint32_t pv;                     // per-vertex output requested
@@ -335,6 +348,7 @@ struct CountArgs {
     const uint32_t* end;  // [n] ends of the lists (off + 1, or where they are cut)
     const uint32_t* col;
     const uint32_t* items;
+    const uint2* elist;              // light graphs: list bounds of the heads (read when light_on), or null
     uint32_t core;                   // core launches count the owners they take (when core_on): 1 all of
                                      // bin 1, 2 its half-LDS part; 0 no such launches
     uint32_t* heads;                 // [kHeadWords] queue heads (zeroed before the launches)

@@ -723,27 +723,35 @@ __global__ void __launch_bounds__(256) k_csr(const unsigned long long* __restric
 }
 
 // Collective work W(r) = sum of d+(v) over r's out-neighbours v, from the oriented keys sorted by row.  A
-// wavefront takes 256 consecutive edges, issues their gathers (v's offsets) together, and sums the runs of
-// equal rows: runs that end and begin inside are stored, the first and the last are added to work (cleared
-// beforehand).  Bound by the gathers: one 128-byte line per edge at 2^25 vertices (11.8 ms for 537 M
+// wavefront walks a range of consecutive edges, 256 at a time with their gathers (v's offsets) issued
+// together, and sums the runs of equal rows: runs that begin and end inside are stored, the first and the
+// last are added to work (cleared beforehand; with ranges of 256 edges those atomics cost 2 of 13 ms).  Bound by the gathers: one 128-byte line per edge at 2^25 vertices (11.8 ms for 537 M
 // edges), 0.51 ms for the 64 M of R-MAT 22, 0.09 ms for the 16 M of R-MAT 20 (16 lanes per row took 0.47
 // and 0.39, waiting for the longest rows).  Record layout: d+(v) comes with v's placement {p(v), d+(v)}, and edge e writes v's record id
-// into its row's record; the row's first edge also writes the header d+(r).
+// into its row's record; the row's first edge also writes the header d+(r).  On light graphs the bounds of
+// v's list are kept per edge as well: 8 coalesced bytes that spare the count its own gather of them.
 constexpr uint32_t kWorkItems = 4;
 
 template <bool REC>
 __global__ void __launch_bounds__(256) k_work(const unsigned long long* __restrict__ okeys, uint32_t nb,
                                               const uint32_t* __restrict__ off, const uint2* __restrict__ place,
                                               uint32_t* __restrict__ rec, const GraphMeta* meta,
-                                              unsigned long long* __restrict__ work) {
+                                              unsigned long long* __restrict__ work, uint2* __restrict__ elist) {
     const uint64_t m = meta->m;
+    if (!light_on(*meta)) elist = nullptr;
     const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
     const uint32_t lane = threadIdx.x & 63u;
     const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
     constexpr uint64_t kSpan = 64 * kWorkItems;
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
-    for (uint64_t base = (blockIdx.x * (uint64_t)(blockDim.x >> 6) + (threadIdx.x >> 6)) * kSpan; base < m;
-         base += waves * kSpan) {
+    const uint64_t per = ((m + waves - 1) / waves + kSpan - 1) / kSpan * kSpan;  // this wavefront's edges
+    const uint64_t lo = (blockIdx.x * (uint64_t)(blockDim.x >> 6) + (threadIdx.x >> 6)) * per;
+    const uint64_t hi = lo + per < m ? lo + per : m;
+    // carried run (uniform): row, sum so far, and whether it may have begun before these edges
+    uint32_t crow = 0;
+    unsigned long long csum = 0;
+    bool open = true;
+    for (uint64_t base = lo; base < hi; base += kSpan) {
         uint32_t row[kWorkItems], v[kWorkItems], len[kWorkItems];
 #pragma unroll
         for (uint32_t i = 0; i < kWorkItems; ++i) {
@@ -762,18 +770,17 @@ __global__ void __launch_bounds__(256) k_work(const unsigned long long* __restri
                     const uint32_t j = (uint32_t)e - off[row[i]];
                     rec[pr.x + 1u + j] = rec_id(pv.x);
                     if (j == 0) rec[pr.x] = pr.y;
+                    if (elist) elist[e] = make_uint2(pv.x + 1u, pv.y);
                 }
             } else {
                 struct __attribute__((packed, aligned(4))) Pair { uint32_t a, b; };  // one 8-byte load
                 const Pair o = *reinterpret_cast<const Pair*>(off + v[i]);
                 len[i] = o.b - o.a;
+                if (elist && e < m) elist[e] = make_uint2(o.a, len[i]);
             }
             if (e >= m) len[i] = 0;
         }
-        // carried run (uniform): row, sum so far, and whether it may have begun before this span
-        uint32_t crow = __builtin_amdgcn_readfirstlane(row[0]);
-        unsigned long long csum = 0;
-        bool open = true;
+        if (base == lo) crow = __builtin_amdgcn_readfirstlane(row[0]);
 #pragma unroll
         for (uint32_t i = 0; i < kWorkItems; ++i) {
             const uint32_t prev = (uint32_t)__shfl_up((int)row[i], 1, 64);
@@ -804,8 +811,8 @@ __global__ void __launch_bounds__(256) k_work(const unsigned long long* __restri
             open = H ? false : open;
             crow = (uint32_t)__builtin_amdgcn_readlane((int)row[i], 63);
         }
-        if (lane == 0 && csum) atomicAdd(&work[crow], csum);  // may go on in the next span
     }
+    if (lane == 0 && csum) atomicAdd(&work[crow], csum);  // may go on in the next wavefront's edges
 }
 
 // The same from lists (relabelled graphs and counting-sort builds, which have no sorted keys): 16 lanes per row.
@@ -832,6 +839,34 @@ __global__ void k_record_empty(const uint2* __restrict__ place, uint32_t n, uint
     for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
         const uint2 p = place[r];
         if (p.y == 0) rec[p.x] = 0;
+    }
+}
+
+// W+ = sum over v of (in-degree) d+(v), and the owners, before any W(u) is known (light_on).
+__global__ void __launch_bounds__(1024) k_owners(const uint32_t* __restrict__ off,
+                                                 const unsigned long long* __restrict__ order, uint32_t n,
+                                                 GraphMeta* meta) {
+    __shared__ unsigned long long s_w, s_o;
+    if (threadIdx.x == 0) s_w = s_o = 0;
+    __syncthreads();
+    unsigned long long w = 0, o = 0;
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t d = off[r + 1] - off[r], deg = (uint32_t)(order[r] >> 32);  // degree << 32 | id
+        w += (unsigned long long)(deg - d) * d;
+        o += d >= 2;
+    }
+    for (int k = 32; k > 0; k >>= 1) {
+        w += __shfl_xor(w, k);
+        o += __shfl_xor(o, k);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&s_w, w);
+        atomicAdd(&s_o, o);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_o) {
+        atomicAdd(&meta->pre_work, s_w);
+        atomicAdd(&meta->pre_owners, s_o);
     }
 }
 
@@ -1400,13 +1435,16 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         hipLaunchKernelGGL(k_work_rows, dim3(work_grid(n)), dim3(kThreads), 0, stream, g.off32, g.col, n, work);
     } else {
         TC_TRY(fill_u32(work, 0, 2 * (size_t)n, stream));
-        const uint32_t grid = (uint32_t)std::min<uint64_t>((m_in + 1023) / 1024, 16384);
+        hipLaunchKernelGGL(k_owners, dim3(std::min((n - 1) / 1024 + 1, 2 * (uint32_t)cu_count)), dim3(1024), 0, stream,
+                           g.off32, t.skey_a, n, g.meta);
+        TC_TRY(hipGetLastError());
+        const uint32_t grid = (uint32_t)std::min<uint64_t>((m_in + 1023) / 1024, 32 * (uint64_t)cu_count);
         if (rec)
             hipLaunchKernelGGL(k_work<true>, dim3(grid), dim3(kThreads), 0, stream, osorted, nb, g.off32,
-                               reinterpret_cast<const uint2*>(g.place), rec, g.meta, work);
+                               reinterpret_cast<const uint2*>(g.place), rec, g.meta, work, g.elist);
         else
             hipLaunchKernelGGL(k_work<false>, dim3(grid), dim3(kThreads), 0, stream, osorted, nb, g.off32, nullptr, nullptr,
-                               g.meta, work);
+                               g.meta, work, g.elist);
     }
     TC_TRY(hipGetLastError());
     if (caps.pack_cap && !(caps.force_hub || caps.force_big || caps.force_wg)) {
