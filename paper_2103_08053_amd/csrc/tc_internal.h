@@ -430,6 +430,29 @@ hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream);
 hipError_t core_info(int part, bool pv, uint32_t S, int* blocks_per_cu);
 hipError_t core_launch(int part, bool pv, uint32_t grid, CoreArgs a, hipStream_t stream);
 
+// tc_small.hip: one-shot counts of graphs of at most kSmallMaxN vertices by their adjacency bit matrix.
+constexpr uint32_t kSmallMaxN = 8192;
+struct SmallResult {
+    unsigned long long total;
+    uint32_t err, done;  // err: bit 0 some input id >= n; done: workgroups of the count that have finished
+};
+struct SmallArgs {
+    uint32_t n, quads;        // quads: 16-byte words per row
+    uint64_t m_in;
+    const uint32_t* src;
+    const uint32_t* dst;
+    uint4* rows;              // [n][quads]
+    unsigned long long* first;  // [ceil(m_in / 64)] bit per sample: the first of its edge
+    unsigned long long* out;  // [n] per-vertex counts, or null
+    SmallResult* result;
+};
+struct SmallLayout {
+    uint64_t rows, first, bytes;  // offsets; the result is at 0
+};
+SmallLayout small_layout(uint32_t n, uint64_t m_in);
+hipError_t small_set(const SmallArgs& a, int cu_count, hipStream_t stream);
+hipError_t small_count(const SmallArgs& a, int cu_count, hipStream_t stream);
+
 // tc_diag.hip: per-table collision statistics of a built graph (the cost model of Equation 2) for
 // the tables the count kernels build; avail[bin] = table words of bins 0-4.  stats = {phi,
 // sum of max collisions, tables, largest collision} (zeroed here).

@@ -1,0 +1,84 @@
+"""One-shot counts by the adjacency bit matrix (up to 8192 vertices) against the oracle and the general path.
+
+Sizes sit at the row widths (128 vertices per 16-byte word; the lanes per edge double at 1, 2, 4, ... words),
+at the sample counts of a wavefront, and around the rule's lines (8192 vertices; samples x vertices 2^32).
+TC_F_NO_MID moves no count and keeps a call on the general path.
+"""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+TC_F_NO_MID = 0x2000
+
+
+def _pairs(n, m, seed):
+    rng = np.random.default_rng(seed)
+    u = rng.random((2, m))
+    e = (u * u * n).astype(np.uint32)
+    return gg.EdgeList(n, e[0], e[1], f"pairs{n}_{m}")
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 5), (3, 64), (127, 1000), (128, 1001), (129, 63), (256, 65), (257, 3000),
+                                 (511, 4096), (513, 4097), (1000, 4000), (1024, 20000), (1025, 20001), (2049, 9999),
+                                 (4096, 65536), (4097, 30011), (8191, 70001), (8192, 524288), (8192, 524289),
+                                 (8193, 40000), (300, 300_000)])
+def test_small_against_oracle_and_general_path(n, m):
+    from paper_2103_08053_amd import Context, Params
+    g = _pairs(n, m, seed=n + m)
+    print(f"[gpu] small {g.name}", flush=True)
+    want = oracle.count(g.n, g.src, g.dst, per_vertex=True)
+    for flags in (0, TC_F_NO_MID):
+        ctx = Context(0, Params(flags=flags))
+        for pv in (False, True, True):  # twice: the workspace holds the first call's rows
+            total, got = ctx.count(g.src, g.dst, g.n, per_vertex=pv)
+            assert total == want.total
+            if pv:
+                assert (got.cpu().numpy().astype(np.uint64) == want.per_vertex).all()
+
+
+def test_small_workspace_reused_unaligned_and_checked():
+    import torch
+
+    from paper_2103_08053_amd import Context, TCError
+    g = gg.dirty(gg.rmat(10, 8, seed=3), seed=1)
+    want = oracle.count(g.n, g.src, g.dst, per_vertex=True)
+    ctx = Context(0)
+    print(f"[gpu] small {g.name} n={g.n} m_in={g.m_in}", flush=True)
+    need = ctx.workspace_bytes(g.n, g.m_in)
+    s, d = (torch.as_tensor(x.astype(np.int64)).to("cuda").to(torch.int32) for x in (g.src, g.dst))
+    for shift in (0, 256, 4096 + 8):
+        ws = torch.full((need + shift,), 0xA5, dtype=torch.uint8, device="cuda")
+        total, pv = ctx.count(s, d, g.n, per_vertex=True, workspace=ws[shift:])
+        assert total == want.total and (pv.cpu().numpy().astype(np.uint64) == want.per_vertex).all()
+        assert bool((ws[:shift] == 0xA5).all())
+    import ctypes
+    tot = ctypes.c_uint64()
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert ctx.lib.tc_count(ctx.h, g.n, g.m_in, s.data_ptr(), d.data_ptr(), None, ws.data_ptr(), need - 1, st,
+                            ctypes.byref(tot)) == 3
+    bad = s.clone()
+    bad[7] = g.n
+    with pytest.raises(TCError):
+        ctx.count(bad, d, g.n)
+    assert ctx.count(s, d, g.n)[0] == want.total
+
+
+def test_small_timing_and_stream():
+    import torch
+
+    from paper_2103_08053_amd import Context
+    g = gg.complete(300)
+    ctx = Context(0)
+    ctx.timing(True)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        total, pv = ctx.count(g.src, g.dst, g.n, per_vertex=True, stream=side)
+    side.synchronize()
+    assert total == 300 * 299 * 298 // 6 and bool((pv == 299 * 298 // 2).all())
+    b, c = ctx.last_times_ms()
+    assert b >= 0 and c >= 0
