@@ -568,12 +568,10 @@ tc_status count_into(tc_context* ctx, const tc_graph* g, uint64_t* d_totals, uin
     if (sh.grid_hub < a.hub_wgs) a.hub_wgs = sh.grid_hub;
     a.end = a.off + 1;
     a.elist = g->dev.elist;
-    HIP_TRY(ctx, tc::fill_u32(a.heads, 0, tc::kHeadWords, s));
-    HIP_TRY(ctx, tc::fill_u32(d_totals, 0, 2 * (size_t)g->k, s));
-    if (pv) {
-        if (g->dev.rec) HIP_TRY(ctx, tc::clear_record_staging(a.tv, g->dev.place, g->n, s));
-        else HIP_TRY(ctx, tc::fill_u32(a.tv, 0, 2 * tv_words, s));
-    }
+    HIP_TRY(ctx, tc::clear_ranges({{a.heads, reinterpret_cast<uint32_t*>(d_totals),
+                                    g->dev.rec ? nullptr : reinterpret_cast<uint32_t*>(a.tv)},
+                                   {tc::kHeadWords, 2 * (size_t)g->k, 2 * tv_words}}, s));
+    if (pv && g->dev.rec) HIP_TRY(ctx, tc::clear_record_staging(a.tv, g->dev.place, g->n, s));
     const bool rec = record && ctx->timing;
     if (rec) HIP_TRY(ctx, hipEventRecord(ctx->ev[2], s));
     // The bucket kernels over one set of bins.
@@ -974,10 +972,14 @@ tc_status count_one_shot(tc_context* ctx, uint32_t n, uint64_t m_in, const uint3
     tc_graph g;
     if (tc_status s = build_into(ctx, &g, n, m_in, d_src, d_dst, ws, ws + L.storage, L, st)) return s;
     char* d_scr = ws + L.storage + L.temp;
-    uint64_t* d_total = reinterpret_cast<uint64_t*>(scratch_base(d_scr) + L.c_total);
+    uint64_t* d_total = g.empty ? reinterpret_cast<uint64_t*>(scratch_base(d_scr) + L.c_total)
+                                : reinterpret_cast<uint64_t*>(&g.dev.meta->total);
     if (tc_status s = count_into(ctx, &g, d_total, d_per_vertex, d_scr, L, st)) return s;
-    HIP_TRY(ctx, hipMemcpyAsync(&host->total, d_total, 8, hipMemcpyDeviceToHost, st));
-    if (!g.empty) HIP_TRY(ctx, hipMemcpyAsync(&host->err, &g.dev.meta->err, 4, hipMemcpyDeviceToHost, st));
+    if (!g.empty) {
+        static_assert(sizeof(tc::SmallResult) == sizeof(tc::GraphMeta) - offsetof(tc::GraphMeta, total) &&
+                      offsetof(tc::SmallResult, err) == 8, "total and flag in one copy");
+        HIP_TRY(ctx, hipMemcpyAsync(host, d_total, sizeof(*host), hipMemcpyDeviceToHost, st));
+    }
     HIP_TRY(ctx, hipStreamSynchronize(st));
     const unsigned int err = host->err;
     if (err & 1u) return fail(ctx, TC_E_RANGE, "an input vertex id is >= n = %u", n);

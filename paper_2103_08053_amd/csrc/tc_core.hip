@@ -242,7 +242,6 @@ __global__ void __launch_bounds__(64) k_core_rows(CoreBuild a) {
 // work, in the bins of the bucket kernels by cut out-degree, each bin by the power of two of its work
 // (largest first).  Five groups: the global-table bin, the two parts of the large-LDS bin, the workgroup
 // and the wavefront bin.
-constexpr uint32_t kRestClasses = 5 * 32;
 constexpr uint32_t kRestLanes = 8;  // lanes per owner
 
 __device__ __forceinline__ uint32_t heavy_items(const GraphMeta& m, uint32_t big_lo, uint32_t& base) {
@@ -770,8 +769,6 @@ hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream) {
     const uint32_t lds = 4u << (32 - a.S);
     const uint32_t cus = (uint32_t)(cu_count > 0 ? cu_count : 1);
     const uint32_t per_cu = 163840u / lds < 32u ? 163840u / lds : 32u;
-    TC_TRY(fill_u32(a.hist, 0, 2 * kRestClasses, stream));
-    TC_TRY(fill_u32(a.rest_meta, 0, sizeof(GraphMeta) / 4, stream));
     const uint64_t tiles = (a.m_in + kTileEdges - 1) / kTileEdges;
     hipLaunchKernelGGL(k_core_tiles, dim3((uint32_t)(tiles < 4ull * cus ? tiles : 4ull * cus)), dim3(kTileThreads), 0, stream, a);
     TC_TRY(hipGetLastError());

@@ -32,8 +32,7 @@ struct GraphMeta {
     unsigned long long m;           // oriented edges
     unsigned long long wplus;       // W+ = sum over oriented (u, v) of d+(v)
     unsigned int big_full;          // bin-1 vertices whose tables need more than half a CU's LDS (first in bin 1)
-    unsigned int max_dplus;
-    unsigned int err;               // bit 0: some input id >= n
+    unsigned int max_dplus, pad1;
     // vertex counts: global-memory tables, large LDS tables (one workgroup per CU), workgroup LDS
     // tables, wavefront LDS slices, light vertices packed several per wavefront, skipped (d+ < 2 or
     // no 2-hop work)
@@ -46,15 +45,19 @@ struct GraphMeta {
     unsigned long long heavy_work, core_edges;
     // owners (d+ >= 2) and W+, known before the W(u) (0 where the build has no sorted edges)
     unsigned long long pre_work, pre_owners;
-    unsigned int pad[26];
+    unsigned int pad[22];
+    // side by side, so that a one-shot count fetches both with one copy
+    unsigned long long total;       // one-shot counts: the triangles
+    unsigned int err, pad2;         // bit 0: some input id >= n
 };
-static_assert(sizeof(GraphMeta) == 256, "meta is one 256-byte block");
+static_assert(sizeof(GraphMeta) == 256 && offsetof(GraphMeta, total) == 240, "meta is one 256-byte block");
 
 // Core path (tc_core.hip): lists' ids among the last ranks as words of a block index above a mask of S
 // ids.  It takes the owners of the workgroup bin, those of the large-LDS bin whose out-degree a table
 // entry can index, and those of the wavefront bin with W(u) >= kCoreMinWork; the core is the last
 // S << (32 - S) ranks (all of them where n is smaller).
 constexpr uint32_t kCoreMinBits = 20;
+constexpr uint32_t kRestClasses = 5 * 32;  // schedule classes of the cut lists: five groups of bins by 32 powers of two
 constexpr uint64_t kCoreMinWork = 1024;
 // Graphs of little work per owner (mean W(u) at most this) get their edges' list bounds (GraphDev::elist):
 // where lists are short, finding them costs the count as much as reading them.
@@ -385,6 +388,13 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
                       const GraphDev& g, const BuildTemp& t, const BinCaps& caps, const BatchIn* batch,
                       int cu_count, hipStream_t stream);
 hipError_t fill_u32(void* p, uint32_t value, size_t words, hipStream_t stream);
+// Zeroes up to three ranges of words in one launch (a null range is skipped): a launch of its own costs a small
+// graph 5 us, and its build and count clear six ranges.
+struct Ranges {
+    uint32_t* p[3];
+    size_t words[3];
+};
+hipError_t clear_ranges(const Ranges& r, hipStream_t stream);
 // out[x] = tv[id(rank[x])] with id(r) = r, or the record id rec_id(place[2r]) when place is given.
 hipError_t gather_per_vertex(const unsigned long long* tv, const uint32_t* rank, uint32_t n, const uint32_t* place,
                              unsigned long long* out, hipStream_t stream);
@@ -407,7 +417,7 @@ struct CoreBuild {
     GraphMeta* rest_meta;
     uint32_t* rest_items;
     uint32_t* cls;                       // [n] temporary
-    uint32_t* hist;                      // [320] temporary
+    uint32_t* hist;                      // [2 * kRestClasses] cleared at the start of the build
     uint32_t n, S, c0, magic;
     uint64_t m_in;
     bool big_all;

@@ -87,7 +87,7 @@ inline bool upper_atomics(uint32_t nb) { return nb > 27; }
 
 // Digit histograms of the build's passes (512 words each; the upper ids' has 1024) and their tickets.
 constexpr uint32_t kMaxPasses = 6 + 4 + 4 + 2;
-constexpr uint32_t kHistWords = kMaxPasses * 512 + 1024;
+constexpr uint32_t kHistWords = kMaxPasses * 512 + 1024 + 2 * kRestClasses;
 constexpr uint32_t kTicketWords = 64;
 
 // Canonical key of sample i (a self-loop or out-of-range id gives the sentinel).
@@ -239,6 +239,14 @@ __global__ void k_narrow(const int64_t* __restrict__ off, uint64_t n1, uint32_t*
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, size_t words) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < words; i += (size_t)gridDim.x * blockDim.x)
         p[i] = v;
+}
+
+__global__ void k_clear_ranges(Ranges r) {
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        if (r.p[q])
+            for (size_t i = t; i < r.words[q]; i += step) r.p[q][i] = 0;
 }
 
 // Largest g in [0, k) with off[g] <= x (off is non-decreasing, off[0] = 0).
@@ -684,10 +692,12 @@ __global__ void __launch_bounds__(1024) k_orient_keys(const unsigned long long* 
 // From the m oriented keys sorted by row: the lists, and the offsets of every row (64 and 32 bits: the
 // count kernels read the latter, m_in < 2^31).  Edge e of a row unlike its predecessor's gives the offset
 // e to its row and to the empty rows before it; the rows before the first edge's and after the last
-// edge's are filled by the whole grid, long gaps in between by the wavefront.
+// edge's are filled by the whole grid, long gaps in between by the wavefront.  work (W of every row, summed
+// next) is cleared here.
 __global__ void __launch_bounds__(256) k_csr(const unsigned long long* __restrict__ okeys, uint32_t nb,
                                              const GraphMeta* meta, uint32_t n, int64_t* __restrict__ off,
-                                             uint32_t* __restrict__ off32, uint32_t* __restrict__ col) {
+                                             uint32_t* __restrict__ off32, uint32_t* __restrict__ col,
+                                             unsigned long long* __restrict__ work) {
     const uint64_t m = meta->m;
     const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
     const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
@@ -698,6 +708,7 @@ __global__ void __launch_bounds__(256) k_csr(const unsigned long long* __restric
     };
     const uint64_t head = m ? (uint32_t)(okeys[0] >> nb) : n;  // rows [0, head] start at 0
     const uint64_t tail = m ? (uint32_t)(okeys[m - 1] >> nb) + 1ull : n + 1ull;
+    for (uint64_t r = t0; r < n; r += step) work[r] = 0;
     for (uint64_t r = t0; r <= head; r += step) put(r, 0u);
     for (uint64_t r = tail + t0; r <= n; r += step) put(r, (uint32_t)m);
     for (uint64_t base = t0 - lane; base < m; base += step) {
@@ -1135,6 +1146,15 @@ hipError_t fill_u32(void* p, uint32_t value, size_t words, hipStream_t stream) {
     return hipGetLastError();
 }
 
+hipError_t clear_ranges(const Ranges& r, hipStream_t stream) {
+    size_t most = 0;
+    for (int q = 0; q < 3; ++q)
+        if (r.p[q]) most = std::max(most, r.words[q]);
+    if (most == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_clear_ranges, dim3(grid_for(most)), dim3(kThreads), 0, stream, r);
+    return hipGetLastError();
+}
+
 hipError_t gather_per_vertex(const unsigned long long* tv, const uint32_t* rank, uint32_t n, const uint32_t* place,
                              unsigned long long* out, hipStream_t stream) {
     if (n == 0) return hipSuccess;
@@ -1262,8 +1282,8 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         next_hist += words;
         return h;
     };
-    TC_TRY(fill_u32(g.meta, 0, sizeof(GraphMeta) / 4, stream));
-    TC_TRY(fill_u32(t.zero, 0, t.zero_words, stream));
+    TC_TRY(clear_ranges({{t.zero, reinterpret_cast<uint32_t*>(g.meta), caps.core_bits ? reinterpret_cast<uint32_t*>(g.rest_meta) : nullptr},
+                         {t.zero_words, sizeof(GraphMeta) / 4, sizeof(GraphMeta) / 4}}, stream));
     // two workgroups of 1024 threads per CU: each ends with an atomic per digit
     const uint32_t hist_grid = (uint32_t)std::min<uint64_t>((m_in + 4095) / 4096, 2 * (uint64_t)cu_count);
 
@@ -1383,7 +1403,7 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
             in = out;
         }
         hipLaunchKernelGGL(k_csr, dim3(std::min(grid_for(std::max<uint64_t>(m_in, n)), 16384u)), dim3(kThreads), 0, stream,
-                           osorted, nb, g.meta, n, g.off, g.off32, g.col);
+                           osorted, nb, g.meta, n, g.off, g.off32, g.col, t.skey_b);
         TC_TRY(hipGetLastError());
     } else {
         // Counting sort: out-degrees, offsets, then an atomic scatter (list order unspecified).
@@ -1434,7 +1454,6 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
     if (caps.order || caps.scatter_csr) {
         hipLaunchKernelGGL(k_work_rows, dim3(work_grid(n)), dim3(kThreads), 0, stream, g.off32, g.col, n, work);
     } else {
-        TC_TRY(fill_u32(work, 0, 2 * (size_t)n, stream));
         hipLaunchKernelGGL(k_owners, dim3(std::min((n - 1) / 1024 + 1, 2 * (uint32_t)cu_count)), dim3(1024), 0, stream,
                            g.off32, t.skey_a, n, g.meta);
         TC_TRY(hipGetLastError());
@@ -1480,7 +1499,7 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         c.rest_meta = g.rest_meta;
         c.rest_items = g.rest_items;
         c.cls = t.order;
-        c.hist = t.deg;
+        c.hist = take_hist(2 * kRestClasses);
         c.n = n;
         c.m_in = m_in;
         c.S = caps.core_bits;
