@@ -81,6 +81,36 @@ hipError_t static_scratch(int device, void** out) {
     return hipSuccess;
 }
 
+// Pinned host memory of the contexts' one-shot answers: 64 bytes per context, cut from one page that is
+// kept once allocated (an allocation of its own made creating a context 75 us slower).  Contexts beyond
+// the page's 64 take an allocation each.
+constexpr size_t kAnswerBytes = 64;
+std::mutex g_answer_mutex;
+char* g_answer_page = nullptr;
+uint64_t g_answer_used = 0;  // a bit per slot
+
+hipError_t take_answer(void** out) {
+    std::lock_guard<std::mutex> lock(g_answer_mutex);
+    if (~g_answer_used) {
+        if (!g_answer_page)
+            if (hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g_answer_page), 64 * kAnswerBytes,
+                                             hipHostMallocPortable); e != hipSuccess) return e;
+        const int slot = __builtin_ctzll(~g_answer_used);
+        g_answer_used |= 1ull << slot;
+        *out = g_answer_page + slot * kAnswerBytes;
+        return hipSuccess;
+    }
+    return hipHostMalloc(out, kAnswerBytes, hipHostMallocPortable);
+}
+
+void give_answer(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(g_answer_mutex);
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p) - reinterpret_cast<uintptr_t>(g_answer_page);
+    if (g_answer_page && at < 64 * kAnswerBytes) g_answer_used &= ~(1ull << (at / kAnswerBytes));
+    else (void)hipHostFree(p);
+}
+
 }  // namespace
 
 struct tc_graph {
@@ -818,7 +848,7 @@ tc_status tc_create(int hip_device, const tc_params* p, tc_context** out) {
             return TC_E_DEVICE;
         }
     }
-    if (hipHostMalloc(&c->answer, 64, hipHostMallocDefault) != hipSuccess) {
+    if (take_answer(&c->answer) != hipSuccess) {
         delete c;
         return TC_E_DEVICE;
     }
@@ -843,7 +873,7 @@ tc_status tc_destroy(tc_context* ctx) {
         if (st.host) (void)hipHostFree(st.host);
     }
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
-    if (ctx->answer) (void)hipHostFree(ctx->answer);
+    give_answer(ctx->answer);
     delete ctx;
     return TC_OK;
 }
