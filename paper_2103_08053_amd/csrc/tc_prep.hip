@@ -84,6 +84,16 @@ constexpr uint32_t kCounterBits = 15;
 inline uint32_t upper_digit(uint32_t nb) { return nb <= kCounterBits ? 0u : nb <= 24 ? 9u : nb <= 27 ? 10u : 0u; }
 inline bool upper_atomics(uint32_t nb) { return nb > 27; }
 
+// Orientation.  The rank of an edge's lower id comes with the sorted order; the upper id's is a gather from
+// anywhere, 128 bytes moved for 4 (2^25 vertices, 537 M edges: 10.7 ms of 66).  From 2^21 vertices on the
+// edges take one more pass, partitioned by upper id with the lower id's rank in place, and the gather goes to
+// a partition's ranks in LDS: 5.2 ms.  Whole one-shot counts without / with it, 8 samples a vertex, ids at
+// random: 3 M vertices 3.10 / 3.04 ms, 2^22 3.98 / 3.80, 2^23 7.92 / 7.36, 2^25 32.4 / 29.5; R-MAT (16 samples),
+// whose hubs' ranks stay in the caches: 2^22 12.49 / 12.51, 2^23 29.00 / 29.09, 2^24 72.0 / 71.3.  Up to 25
+// bits (2^15 ranks per partition: the LDS); not for batches, whose gathers stay within a small graph.
+inline bool attach_ranks(uint32_t nb) { return nb >= 22 && nb <= 25; }
+// Its ranks and the counters of the rows' top digit (three row passes).
+inline uint32_t orient_lds(uint32_t nb) { return (4u << (nb - upper_digit(nb))) + (64u << (nb - 2 * kDigit)); }
 
 // Digit histograms of the build's passes (512 words each; the upper ids' has 1024) and their tickets.
 constexpr uint32_t kMaxPasses = 6 + 4 + 4 + 2;
@@ -136,6 +146,22 @@ struct LoadFirst {  // the distinct edges' keys (sorted or, at the same places, 
     __device__ bool make(const Raw& r, uint32_t lane, unsigned long long& key) const {
         key = r.key;
         return (r.bits >> lane) & 1ull;
+    }
+};
+
+struct LoadRanked {  // the same with the lower id's rank in place of the lower id
+    typedef KeyBits Raw;
+    const unsigned long long* keys;
+    const unsigned long long* first;
+    const uint32_t* rank;
+    uint32_t n, nb;
+    unsigned long long mask;
+    __device__ Raw raw(uint64_t i) const { return {keys[i], first[i >> 6]}; }
+    __device__ bool make(const Raw& r, uint32_t lane, unsigned long long& key) const {
+        const bool on = (r.bits >> lane) & 1ull;
+        const uint32_t lo = (uint32_t)(r.key >> nb);  // (past the last sample a lane has another's bit: any key)
+        key = ((unsigned long long)rank[on && lo < n ? lo : 0u] << nb) | (r.key & mask);
+        return on;
     }
 };
 
@@ -548,6 +574,16 @@ __global__ void __launch_bounds__(kDedupThreads) __attribute__((amdgpu_waves_per
 // partition has several units.
 constexpr uint32_t kUpperUnit = 1u << 20;
 
+// The partition of unit u, given the 1024 partitions' first units (empty ones repeat the next value).
+__device__ __forceinline__ uint32_t partition_of(const uint32_t* s_unit, uint32_t u) {
+    uint32_t l = 0, r = 1023;
+    while (l < r) {
+        const uint32_t mid = (l + r + 1) >> 1;
+        if (s_unit[mid] <= u) l = mid; else r = mid - 1;
+    }
+    return l;
+}
+
 __global__ void __launch_bounds__(1024) k_upper_count(const uint32_t* __restrict__ ids, LoadUpper direct, uint64_t cap,
                                                       uint32_t bins, uint32_t sub, uint32_t n,
                                                       const uint32_t* __restrict__ uhist, uint32_t unit_size,
@@ -565,11 +601,7 @@ __global__ void __launch_bounds__(1024) k_upper_count(const uint32_t* __restrict
     const uint32_t total = s_unit[1024];
     const uint32_t span = sub < kCounterBits ? 1u << sub : 1u << kCounterBits;  // counters at a time
     for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
-        uint32_t l = 0, r = 1023;  // the last partition with s_unit <= u (empty ones repeat the next value)
-        while (l < r) {
-            const uint32_t mid = (l + r + 1) >> 1;
-            if (s_unit[mid] <= u) l = mid; else r = mid - 1;
-        }
+        const uint32_t l = partition_of(s_unit, u);
         const uint32_t parts = s_unit[l + 1] - s_unit[l], part = u - s_unit[l];
         const uint32_t len = ids ? uhist[l] : (uint32_t)cap;
         const uint64_t x0 = s_at[l] + (uint64_t)part * unit_size;
@@ -643,8 +675,7 @@ __global__ void k_orient_fill(const unsigned long long* __restrict__ keys, uint3
 }
 
 // Oriented keys (rank_lo << nb | rank_hi) of the distinct edges, at the places of the sorted keys, and
-// the digit histograms of their rows.  Bound by the gathers of rank[hi] (2^25 vertices: one 128-byte line
-// per edge).
+// the digit histograms of their rows.  Bound by the gathers of rank[hi] (see attach_ranks for large graphs).
 __global__ void __launch_bounds__(1024) k_orient_keys(const unsigned long long* __restrict__ keys, uint32_t nb,
                                                       uint64_t cap, const unsigned long long* __restrict__ first,
                                                       const uint32_t* __restrict__ rank, uint32_t passes,
@@ -683,6 +714,74 @@ __global__ void __launch_bounds__(1024) k_orient_keys(const unsigned long long* 
     for (uint32_t i = threadIdx.x; i < top * 512; i += blockDim.x)
         if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
     for (uint32_t i = threadIdx.x; i < tops; i += blockDim.x) {
+        uint32_t c = 0;
+        for (uint32_t j = 0; j < 16; ++j) c += s_top[i * 16 + j];
+        if (c) atomicAdd(&hist[top * 512 + i], c);
+    }
+}
+
+// The same from the distinct edges with the lower ids' ranks in place, partitioned by their upper ids
+// (LoadRanked): a work unit is a share of one partition, and gathers from the ranks of the partition's ids in
+// LDS (2^15 at most: one workgroup per CU then, two at 2^14).  2^25 vertices, 537 M edges: 2.2 ms (bytes 1.8 at
+// the copy rate), after a pass of 3.0; the lookups past the L1 instead, in partitions of 2^16 ids: 6.3.
+__global__ void __launch_bounds__(1024) k_orient_parts(const unsigned long long* __restrict__ keys, uint32_t nb,
+                                                       uint32_t bins, uint32_t sub, uint32_t n,
+                                                       const uint32_t* __restrict__ uhist,
+                                                       uint32_t unit, const uint32_t* __restrict__ rank, uint32_t passes,
+                                                       unsigned long long* __restrict__ okeys,
+                                                       uint32_t* __restrict__ hist) {
+    constexpr int kItems = 4;
+    extern __shared__ __align__(16) uint32_t s_rank[];  // [1 << sub], then the top digit's counters (16 copies)
+    __shared__ uint32_t s_h[2][512];
+    __shared__ uint32_t s_unit[1025], s_at[1025], s_scan[16];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t top = passes - 1, tops = 1u << (nb - kDigit * top);
+    uint32_t* const s_top = s_rank + (1u << sub);
+    for (uint32_t i = tid; i < top * 512; i += 1024) (&s_h[0][0])[i] = 0;
+    for (uint32_t i = tid; i < tops * 16; i += 1024) s_top[i] = 0;
+    const uint32_t size = tid < bins ? uhist[tid] : 0u;
+    const uint32_t units = (size + unit - 1) / unit;
+    const uint32_t u0 = block_excl_scan<16>(units, s_scan), a0 = block_excl_scan<16>(size, s_scan);
+    s_unit[tid] = u0;
+    s_at[tid] = a0;
+    if (tid == 1023) {
+        s_unit[1024] = u0 + units;
+        s_at[1024] = a0 + size;
+    }
+    __syncthreads();
+    const unsigned long long mask = (1ull << nb) - 1;
+    const uint32_t total = s_unit[1024], ids = (1u << sub) - 1u;
+    for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
+        const uint32_t l = partition_of(s_unit, u);
+        const uint32_t parts = s_unit[l + 1] - s_unit[l], part = u - s_unit[l];
+        const uint32_t len = s_at[l + 1] - s_at[l], share = (len + parts - 1) / parts;
+        const uint32_t x0 = s_at[l] + part * share, x1 = part + 1 < parts ? x0 + share : s_at[l] + len;
+        const uint32_t v0 = l << sub, have = n - v0 < ids + 1 ? n - v0 : ids + 1;
+        for (uint32_t i = tid; i < have; i += 1024) s_rank[i] = rank[v0 + i];
+        __syncthreads();
+        for (uint32_t base = x0; base < x1; base += kItems * 1024) {
+            unsigned long long k[kItems];
+#pragma unroll
+            for (int j = 0; j < kItems; ++j) {
+                const uint32_t x = base + j * 1024 + tid;
+                k[j] = keys[x < x1 ? x : x1 - 1];
+            }
+#pragma unroll
+            for (int j = 0; j < kItems; ++j) {
+                const uint32_t x = base + j * 1024 + tid;
+                const bool act = x < x1;
+                const uint32_t ra = (uint32_t)(k[j] >> nb), rb = s_rank[(uint32_t)(k[j] & mask) & ids];
+                const uint32_t row = ra < rb ? ra : rb, head = ra < rb ? rb : ra;
+                if (act) okeys[x] = ((unsigned long long)row << nb) | head;
+                for (uint32_t p = 0; p < top; ++p) count_digit(s_h[p], (row >> (kDigit * p)) & 511u, act);
+                if (act) atomicAdd(&s_top[(row >> (kDigit * top)) * 16u + (tid & 15u)], 1u);
+            }
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = tid; i < top * 512; i += 1024)
+        if (const uint32_t c = (&s_h[0][0])[i]) atomicAdd(&hist[i], c);
+    for (uint32_t i = tid; i < tops; i += 1024) {
         uint32_t c = 0;
         for (uint32_t j = 0; j < 16; ++j) c += s_top[i * 16 + j];
         if (c) atomicAdd(&hist[top * 512 + i], c);
@@ -1194,13 +1293,15 @@ PrepZero prep_zero(uint32_t n, uint64_t m_in) {
     w = (w + 3) & ~(size_t)3;
     z.status = w;
     const uint64_t tm = pass_tiles(m_in, 8), tu = pass_tiles(m_in, 4), tn = pass_tiles(n, 8);
-    const uint64_t words = std::max<uint64_t>({tm * 512, upper_digit(nb) ? tu << upper_digit(nb) : 0, tn * 512});
+    const uint64_t words = std::max<uint64_t>({attach_ranks(nb) ? tm << upper_digit(nb) : tm * 512, upper_digit(nb) ? tu << upper_digit(nb) : 0, tn * 512});
     w += 2 * (size_t)words;
     z.words = w;
     return z;
 }
 
-hipError_t prep_init() {  // once per device: the counters of k_upper_count take up to 128 KB of LDS
+hipError_t prep_init() {  // opt-in LDS: 2^15 counters of k_upper_count, as many ranks of k_orient_parts
+    TC_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_orient_parts),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)orient_lds(25)));
     return hipFuncSetAttribute(reinterpret_cast<const void*>(k_upper_count),
                                hipFuncAttributeMaxDynamicSharedMemorySize, 4 << kCounterBits);
 }
@@ -1319,10 +1420,10 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         }
     }
 
+    uint32_t* uhist = take_hist(1024);
     // 2-3: distinct edges and degrees, rank in (degree, id) order (the sort is stable).
     {
         const uint32_t ud = upper_digit(nb), sub = ud ? nb - ud : nb;
-        uint32_t* uhist = take_hist(1024);
         const uint64_t tiles = (m_in + kDedupTile - 1) / kDedupTile;
         hipLaunchKernelGGL(k_dedup, dim3((uint32_t)std::min<uint64_t>(tiles, 2 * (uint64_t)cu_count)), dim3(kDedupThreads), 0, stream,
                            t.keys_b, nb, low, m_in, sentinel, t.first, t.deg, uhist, ud ? 1u << ud : 0u, sub,
@@ -1388,13 +1489,30 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
         auto buf = [&](uint32_t writes_left) { return writes_left % 2 ? osorted : t.keys_a; };
         uint32_t* hist = take_hist(512 * passes);
         unsigned long long* in = buf(passes + 1);
-        hipLaunchKernelGGL(k_orient_keys, dim3(hist_grid), dim3(1024), 0, stream, t.keys_b, nb, m_in,
-                           t.first, g.rank, passes, in, hist);
+        const bool attach = !batch && attach_ranks(nb);
+        if (attach) {
+            const uint32_t ud = upper_digit(nb), sub = nb - ud;
+            unsigned long long* ranked = buf(passes);
+            const LoadRanked load{t.keys_b, t.first, g.rank, n, nb, mask};
+            if (ud == 9)
+                TC_TRY((radix_pass<9, false, unsigned long long>(load, StoreKey{ranked}, m_in, nullptr, sub, uhist, t.status,
+                                                          ++epoch, next_ticket++, stream)));
+            else
+                TC_TRY((radix_pass<10, false, unsigned long long>(load, StoreKey{ranked}, m_in, nullptr, sub, uhist, t.status,
+                                                           ++epoch, next_ticket++, stream)));
+            // four units per CU or more (R-MAT 22 in units of 2^19: half the CUs idle), large enough to load ranks for
+            const uint32_t unit = (uint32_t)std::max<uint64_t>(1u << 15, m_in / (4 * (uint64_t)cu_count));
+            hipLaunchKernelGGL(k_orient_parts, dim3(2 * (uint32_t)cu_count), dim3(1024), orient_lds(nb), stream, ranked, nb,
+                               1u << ud, sub, n, uhist, unit, g.rank, passes, in, hist);
+        } else {
+            hipLaunchKernelGGL(k_orient_keys, dim3(hist_grid), dim3(1024), 0, stream, t.keys_b, nb, m_in,
+                               t.first, g.rank, passes, in, hist);
+        }
         TC_TRY(hipGetLastError());
         for (uint32_t p = 0; p < passes; ++p) {
             unsigned long long* out = buf(passes - p);
             const uint32_t shift = nb + kDigit * p;
-            if (p == 0)
+            if (p == 0 && !attach)
                 TC_TRY((radix_pass<kDigit, false, unsigned long long>(LoadFirst{in, t.first}, StoreKey{out}, m_in, nullptr, shift,
                                                                hist, t.status, ++epoch, next_ticket++, stream)));
             else

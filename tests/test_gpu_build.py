@@ -88,3 +88,16 @@ def test_build_variants(flags):
     assert gr.info().wedges_plus == want.wedges_plus
     total, pv = gr.count(per_vertex=True)
     assert total == want.total and (pv.cpu().numpy().astype(np.uint64) == want.per_vertex).all()
+
+
+@pytest.mark.parametrize("m", [40_000, 3_600_000])  # tile sizes
+@pytest.mark.parametrize("n", [(1 << 21), (1 << 21) + 1, 1 << 22, (1 << 23) - 5, 1 << 25, (1 << 25) + 1])
+def test_build_upper_partitions(n, m):
+    """Upper ids in every partition, and all of them within two neighbouring ones (many units of each)."""
+    rng = np.random.default_rng(n + m)
+    _check(_pairs(n, m, seed=m + n % 83))
+    at = n - 1 - (1 << 16) - 1000  # across a multiple of 2^16, the ids of a partition at most
+    at += (1 << 16) - (at & 0xFFFF) - 1000
+    ids = np.concatenate([at + np.arange(2000), [n - 1, 0, 1]]).astype(np.uint32)
+    s, d = ids[rng.integers(0, len(ids), m)], ids[rng.integers(0, len(ids), m)]
+    _check(gg.EdgeList(n, s, d, f"narrow{n}_{m}"))
