@@ -63,7 +63,8 @@ def sq_summary(workload: str) -> str:
 
 
 # Sources the count kernels are compiled from (the kernel file and the headers it includes).
-KERNEL_SRCS = [os.path.join(ROOT, "paper_2103_08053_amd", "csrc", f) for f in ("tc_count.hip", "tc_internal.h", "tc_wave.h")]
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2103_08053_amd", "csrc", f)
+               for f in ("tc_count.hip", "tc_core.hip", "tc_fetch.h", "tc_internal.h", "tc_wave.h")]
 
 
 def pmc_summary(workload: str) -> str:

@@ -18,8 +18,9 @@
  *     caller-provided workspace sized by the matching *_bytes query (except
  *     tc_graph_count_static, whose scratch is a static buffer that every
  *     device holds for the life of the process).  Host
- *     memory is allocated only for the opaque handles and a context's pinned
- *     staging buffers (tc_count_graphs).
+ *     memory is allocated only for the opaque handles and pinned buffers: a
+ *     context's staging (tc_count_graphs) and 64 bytes for the answer of its
+ *     one-shot counts.
  *   - Ids: vertex ids are uint32 in [0, n), n <= 2^32 - 1.  Edge samples may
  *     repeat, appear in both directions or be self-loops; all are accepted and
  *     cleaned.  n = 0 or m_in = 0 gives a count of 0.
@@ -63,7 +64,7 @@ typedef struct tc_params {
     uint32_t load_factor_pct;   /* buckets B = smallest power of two with B*S*load >= d+, and B >= d+; 10..100 */
     uint32_t hash_kind;         /* 0: low bits of the id (the degree rank, or the record id with
                                    TC_F_RECORDS); 1: multiplicative (Fibonacci) hash */
-    uint32_t light_chunk;       /* vertices a wavefront takes per queue access, 1..256 */
+    uint32_t light_chunk;       /* most vertices a wavefront takes per queue access, 1..256 */
     uint32_t grid_wgs;          /* persistent grid size in workgroups; 0 = fill the device */
     uint32_t flags;             /* TC_F_* below */
 } tc_params;
@@ -72,7 +73,7 @@ typedef struct tc_params {
 #define TC_F_FORCE_WG   0x2u    /* every vertex goes to the workgroup bin (tests) */
 #define TC_F_FORCE_HUB  0x4u    /* every vertex goes to the global-memory table bin (tests) */
 #define TC_F_SCATTER_CSR 0x8u   /* build the CSR by an atomic counting sort (list order unspecified) instead
-                                   of the default stable radix sort of the oriented edges by row */
+                                   of the default radix passes of the oriented edges by row */
 #define TC_F_WIDE_ADDR  0x10u   /* 64-bit list addressing even below 2^30 edges (tests) */
 #define TC_F_FORCE_BIG  0x20u   /* every vertex goes to the large-LDS-table bin (tests) */
 /* Vertex order used as the hash ids (paper Section 4.1, reordering; the orientation stays the
