@@ -315,7 +315,7 @@ class Context:
     def count_graphs(self, graphs, per_vertex: bool = False, workspace=None, stream=None, replay: bool = False):
         """Count built handles (:class:`Graph` / :class:`Batch`) together.  Returns (totals, per-vertex):
         totals[g] is an int for a single graph and a list for a batch handle; per-vertex is None or a
-        list of device tensors."""
+        list of device tensors (of one allocation, which each of them keeps alive)."""
         torch = _torch()
         dev = torch.device("cuda", self.device)
         nt = sum(g.k for g in graphs)
