@@ -101,6 +101,11 @@ __global__ void __launch_bounds__(kThreads) k_small_count(SmallArgs a) {
     }
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
     if (lane == 0 && sum) atomicAdd(&s_sum, sum);
+    // Every wavefront's adds to `out` are done before this workgroup counts as finished: the barrier waits for
+    // LDS only, and thread 0's fence below for its own wavefront's adds.  A wait is enough: what the adds leave in
+    // the XCD's L2 is written back by that fence (8192 vertices and 2^19 samples 469 us, as without the wait;
+    // 4096 and 2^16 125 -> 130; with a fence per wavefront 606 and 174).
+    if constexpr (PV) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         if (s_sum) atomicAdd(&a.result->total, s_sum);
