@@ -396,6 +396,7 @@ tc::BuildTemp temp_ptrs(void* temp, const Layout& L) {
     t.zero_words = L.zero.words;
     t.deg = t.zero + L.zero.deg;
     t.first = reinterpret_cast<unsigned long long*>(t.zero + L.zero.first);
+    t.bits = t.zero + L.zero.bits;
     t.status = reinterpret_cast<unsigned long long*>(t.zero + L.zero.status);
     t.dplus = reinterpret_cast<uint32_t*>(b + L.t_dplus);
     t.order = reinterpret_cast<uint32_t*>(b + L.t_order);

@@ -239,6 +239,7 @@ struct BuildTemp {
     size_t zero_words;
     uint32_t* deg;       // [n + 1]; reused as the fill cursor
     unsigned long long* first;   // a bit per sorted key: the first of a distinct edge
+    uint32_t* bits;              // bit sets of long groups of equal keys (k_dedup)
     unsigned long long* status;  // look-back words of the sort passes
     uint32_t* dplus;     // [n + 1] (relabelling and counting-sort builds)
     uint32_t* order;     // [n]
@@ -279,7 +280,7 @@ __host__ __device__ inline uint64_t record_words(uint32_t n, uint64_t m_in) { re
 __host__ __device__ inline uint32_t rec_id(uint32_t p) { return p ^ ((p >> 5) & 31u); }
 
 struct PrepZero {  // word offsets in BuildTemp::zero
-    size_t deg, first, status, words;
+    size_t deg, first, bits, status, words;
 };
 
 struct Layout {

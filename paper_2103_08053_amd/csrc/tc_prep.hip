@@ -365,11 +365,17 @@ __global__ void __launch_bounds__(1024) k_canon_batch(const uint32_t* __restrict
 }
 
 // Distinct edges.  The keys are sorted by all but their `low` lowest bits; the keys of a group (equal top
-// bits) come in any order.  A workgroup handles the groups that start in its tile of kDedupTile keys: the
+// bits) come in any order.  The first of each distinct key gets its bit in `first` (cleared beforehand).
+// k_dedup: a workgroup handles the groups that start in its tile of kDedupTile keys, other than long ones: the
 // keys of groups of one are first by themselves, the others go into an LDS hash set (group number in the
-// tile << low | low bits: 28 bits name a key exactly), and the group that runs on into the next tile is
-// read to its end with a bit set over its low bits.  The first of each distinct key gets its bit in
-// `first` (cleared beforehand; words that two tiles share are ORed).
+// tile << low | low bits: 28 bits name a key exactly), and the group that runs on into the next tiles is
+// read to its end with a bit set over its low bits (words of `first` that two tiles share are ORed).
+// k_dedup_long: long groups hold the first keys of kLongTiles tiles or more (dense neighbourhoods, samples
+// that repeat), and every tile marks its own keys of them: a bit set over the low bits in LDS, merged word
+// by word into the group's bit set in memory (`bits`, cleared beforehand); what the merge finds clear is
+// first.  The first boundary of tiles in the group names its set: those of long groups are at least
+// kLongTiles apart.  (One workgroup reading every group to its end took 25 ms for 2^24 samples of one pair, whole
+// calls of 0.5 to 0.9 ms now, and 0.65 ms for the 4 M edges between 2000 and 2000 vertices, calls of 0.41.)
 //
 // Its lower id gets one degree: a wavefront walks 256 consecutive keys 64 at a time; equal lower ids are
 // contiguous lanes (groups, found by ballot), the last lane of each group adds the group's distinct
@@ -379,26 +385,106 @@ __global__ void __launch_bounds__(1024) k_canon_batch(const uint32_t* __restrict
 constexpr uint32_t kDedupThreads = 1024, kDedupItems = 4, kDedupTile = kDedupThreads * kDedupItems;
 constexpr uint32_t kDedupSlots = 2 * kDedupTile;  // 2^13
 constexpr uint32_t kDedupWords = kDedupTile / 64;
+constexpr uint32_t kLongTiles = 4;
 
-__global__ void __launch_bounds__(kDedupThreads) __attribute__((amdgpu_waves_per_eu(8))) k_dedup(const unsigned long long* __restrict__ keys, uint32_t nb,
-                                                         uint32_t low, uint64_t cap, unsigned long long sentinel,
-                                                         unsigned long long* __restrict__ first,
-                                                         uint32_t* __restrict__ deg, uint32_t* __restrict__ uhist,
-                                                         uint32_t ubins, uint32_t ushift, bool uatomics,
-                                                         GraphMeta* meta) {
+// Words of a long group's bit set, and of those that m_in samples can need.
+__host__ __device__ inline uint32_t long_words(uint32_t low) { return low > 5 ? 1u << (low - 5) : 1u; }
+inline uint64_t long_set_words(uint32_t low, uint64_t m_in) {
+    return (uint64_t)long_words(low) * ((m_in + kDedupTile - 1) / kDedupTile / kLongTiles + 1);
+}
+
+struct Dedup {
+    const unsigned long long* keys;
+    uint64_t cap;
+    unsigned long long sentinel;
+    unsigned long long* first;
+    uint32_t* bits;
+    uint32_t* deg;
+    uint32_t* uhist;
+    GraphMeta* meta;
+    uint32_t* any_long;  // set when there is a long group
+    uint32_t nb, low, ubins, ushift;
+    bool uatomics;
+};
+
+// Degrees and the upper digit histogram of a tile's distinct edges: k its keys, s_first their bits.
+__device__ __forceinline__ void count_firsts(const Dedup& a, const unsigned long long (&k)[kDedupItems],
+                                             const unsigned long long* s_first, uint32_t* s_hist, uint32_t wave,
+                                             uint32_t lane) {
+    const unsigned long long mask = (a.nb >= 32) ? 0xFFFFFFFFull : ((1ull << a.nb) - 1);
+    const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
+    uint32_t clo = 0xFFFFFFFFu, cc = 0;  // carried group (uniform)
+#pragma unroll
+    for (int i = 0; i < (int)kDedupItems; ++i) {
+        const unsigned long long F = s_first[wave * kDedupItems + i];
+        const uint32_t lo = (uint32_t)(k[i] >> a.nb);
+        const bool mine = (F >> lane) & 1ull;
+        if (mine) {
+            const uint32_t hi = (uint32_t)(k[i] & mask);
+            if (a.ubins) atomicAdd(&s_hist[hi >> a.ushift], 1u);
+            if (a.uatomics) atomicAdd(&a.deg[hi], 1u);
+        }
+        const uint32_t lo_prev = (uint32_t)__shfl_up((int)lo, 1, 64);
+        const unsigned long long H = __ballot(lane == 0 || lo != lo_prev);  // group starts
+        const uint32_t s = 63u - (uint32_t)__builtin_clzll(H & upto);      // this lane's group start
+        const uint32_t c = (uint32_t)__popcll((F & upto) >> s);            // its firsts up to this lane
+        const bool merge = __builtin_amdgcn_readfirstlane(lo) == clo;     // first group continues the carry
+        const uint32_t tail = 63u - (uint32_t)__builtin_clzll(H);          // start of lane 63's group
+        if (lane != 63 && ((H >> (lane + 1)) & 1ull)) {                    // last lane of an inner group
+            const uint32_t cnt = c + ((s == 0 && merge) ? cc : 0u);
+            if (cnt) atomicAdd(&a.deg[lo], cnt);
+        }
+        const uint32_t c63 = (uint32_t)__builtin_amdgcn_readlane((int)c, 63);
+        const uint32_t lo63 = (uint32_t)__builtin_amdgcn_readlane((int)lo, 63);
+        if (tail == 0 && merge) {
+            cc += c63;
+        } else {
+            if (!merge && cc && lane == 0) atomicAdd(&a.deg[clo], cc);
+            clo = lo63;
+            cc = c63;
+        }
+    }
+    if (cc && lane == 0) atomicAdd(&a.deg[clo], cc);
+}
+
+// A tile's view of long groups, by the groups at its boundary and those of three tiles before and four after (a
+// wavefront's lanes 0..7): bit 0, the group of the tile's first key is long; bit 1, that of the next tile's
+// first key, and begins in this tile or there.
+__device__ __forceinline__ uint32_t long_groups(const Dedup& a, uint64_t base, uint32_t lane) {
+    static_assert(kLongTiles == 4, "boundaries looked at");
+    const int64_t x = (int64_t)base + ((int64_t)lane - 3) * kDedupTile;
+    const bool on = lane < 8 && x >= 0 && x < (int64_t)a.cap;
+    const unsigned long long top = on ? a.keys[x] >> a.low : ~0ull;
+    // (samples without an edge come last; where the top bits hold the whole lower id their group holds
+    // nothing else and is left alone)
+    const bool edges = on && (a.low > a.nb || top != a.sentinel >> a.low);
+    const uint32_t here = (uint32_t)__ballot(edges && top == __shfl(top, 3, 64));  // consecutive, lane 3 among them
+    const uint32_t next = (uint32_t)__ballot(edges && top == __shfl(top, 4, 64));
+    return ((uint32_t)__popc(here) >= kLongTiles ? 1u : 0u) | ((next >> 4) == 15u ? 2u : 0u);
+}
+
+__global__ void __launch_bounds__(kDedupThreads) __attribute__((amdgpu_waves_per_eu(8))) k_dedup(Dedup a) {
     __shared__ __align__(16) uint32_t s_set[kDedupSlots];  // hash set, then the bits of the crossing group
     __shared__ unsigned long long s_start[kDedupWords], s_first[kDedupWords];
     __shared__ uint32_t s_pre[kDedupWords];
     __shared__ uint32_t s_hist[1024];
     __shared__ unsigned long long s_m;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
-    const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
+    const unsigned long long* const keys = a.keys;
+    const uint64_t cap = a.cap;
+    const unsigned long long sentinel = a.sentinel;
+    const uint32_t nb = a.nb, low = a.low;
     constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;
-    for (uint32_t i = tid; i < ubins; i += kDedupThreads) s_hist[i] = 0;
-    if (tid == 0) s_m = 0;
+    for (uint32_t i = threadIdx.x; i < a.ubins; i += kDedupThreads) s_hist[i] = 0;
+    if (threadIdx.x == 0) s_m = 0;
     unsigned long long found = 0;
     for (uint64_t base = blockIdx.x * (uint64_t)kDedupTile; base < cap; base += (uint64_t)gridDim.x * kDedupTile) {
+        // (What follows from the thread's number is worked out anew for every tile: kept across tiles it takes
+        // the registers that the tile needs.)
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const uint32_t lane = tid & 63u, wave = tid >> 6;
+        const unsigned long long mask = (nb >= 32) ? 0xFFFFFFFFull : ((1ull << nb) - 1);
+        const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
         const uint64_t end = base + kDedupTile < cap ? base + kDedupTile : cap;
         unsigned long long k[kDedupItems];
 #pragma unroll
@@ -428,12 +514,10 @@ __global__ void __launch_bounds__(kDedupThreads) __attribute__((amdgpu_waves_per
         }
         const unsigned long long has = __ballot(starts != 0);  // words with a start
         __syncthreads();
-        if (!has) continue;  // uniform: the whole tile belongs to an earlier tile's group
+        if (!has) continue;  // uniform: the whole tile belongs to another tile's group
         const uint32_t w0 = (uint32_t)__builtin_ctzll(has), w1 = 63u - (uint32_t)__builtin_clzll(has);
         const uint32_t p0 = w0 * 64u + (uint32_t)__builtin_ctzll(s_start[w0]);         // first start
         const uint32_t p1 = w1 * 64u + 63u - (uint32_t)__builtin_clzll(s_start[w1]);   // last start
-        // (samples without an edge come last; where the top bits hold the whole lower id their group holds
-        // nothing else and is left alone)
         const bool cross = end < cap && (keys[end] >> low) == (keys[end - 1] >> low) &&
                            !(low <= nb && (keys[end] >> low) == (sentinel >> low));
         const uint32_t stop = cross ? p1 : (uint32_t)(end - base);  // keys [p0, stop) are in closed groups
@@ -474,98 +558,176 @@ __global__ void __launch_bounds__(kDedupThreads) __attribute__((amdgpu_waves_per
             if (lane == 0) s_first[wave * kDedupItems + i] = f;
         }
         __syncthreads();
-        if (cross) {
-            for (uint32_t i = tid; i < ((1u << low) + 31u) / 32u; i += kDedupThreads) s_set[i] = 0;
+        // (long: the group holds the boundary kLongTiles - 1 past its first one)
+        const uint64_t far = base + (p1 ? kLongTiles : kLongTiles - 1) * kDedupTile;
+        if (cross && far < cap && (keys[far] >> low) == (keys[end] >> low)) {
+            if (tid == 0) *a.any_long = 1;
+        } else if (cross) {
+            for (uint32_t i = tid; i < long_words(low); i += kDedupThreads) s_set[i] = 0;
             __syncthreads();
-            const unsigned long long group = keys[base + p1] >> low;
             uint32_t beyond = 0;  // distinct keys past this tile
             uint32_t lo = 0;
-            for (uint64_t x0 = base + p1;; x0 += kDedupThreads) {
+            const unsigned long long group = keys[base + p1] >> low;
+            for (uint64_t x0 = base + (p1 & ~63u);; x0 += kDedupThreads) {
                 const uint64_t x = x0 + tid;
                 const unsigned long long key = x < cap ? keys[x] : ~0ull;
                 const bool in = x < cap && (key >> low) == group;
-                if (in && key != sentinel) {
+                bool win = false;
+                if (in && x >= base + p1 && key != sentinel) {
                     const uint32_t b = (uint32_t)key & ((1u << low) - 1u);
-                    if (!((atomicOr(&s_set[b >> 5], 1u << (b & 31u)) >> (b & 31u)) & 1u)) {
-                        if (x < end) {
-                            atomicOr(&s_first[(x - base) >> 6], 1ull << (x & 63u));
-                        } else {
-                            atomicOr(&first[x >> 6], 1ull << (x & 63u));
-                            const uint32_t hi = (uint32_t)(key & mask);
-                            if (ubins) atomicAdd(&s_hist[hi >> ushift], 1u);
-                            if (uatomics) atomicAdd(&deg[hi], 1u);
-                            const uint32_t l = (uint32_t)(key >> nb);
-                            if (beyond && l != lo) {
-                                atomicAdd(&deg[lo], beyond);
-                                beyond = 0;
-                            }
-                            lo = l;
-                            ++beyond;
-                            ++found;
+                    win = !((atomicOr(&s_set[b >> 5], 1u << (b & 31u)) >> (b & 31u)) & 1u);
+                    if (win && x >= end) {
+                        const uint32_t hi = (uint32_t)(key & mask);
+                        if (a.ubins) atomicAdd(&s_hist[hi >> a.ushift], 1u);
+                        if (a.uatomics) atomicAdd(&a.deg[hi], 1u);
+                        const uint32_t l = (uint32_t)(key >> nb);
+                        if (beyond && l != lo) {
+                            atomicAdd(&a.deg[lo], beyond);
+                            beyond = 0;
                         }
+                        lo = l;
+                        ++beyond;
+                        ++found;
                     }
                 }
-                if (!__syncthreads_and(in)) break;
+                const unsigned long long f = __ballot(win);  // (x of lane 0 is a multiple of 64, as is end)
+                if (lane == 0 && f) {
+                    if (x < end) s_first[(x - base) >> 6] |= f;
+                    else atomicOr(&a.first[x >> 6], f);
+                }
+                if (!__syncthreads_and(in || x < base + p1)) break;
             }
             // lower-id degrees of the keys past the tile (one id, or few where the group holds several)
             const uint32_t lead = __builtin_amdgcn_readfirstlane(lo);
             const unsigned long long differ = __ballot(beyond && lo != lead);
             if (!differ) {
                 const uint32_t t = wave_sum(beyond);
-                if (lane == 0 && t) atomicAdd(&deg[lead], t);
+                if (lane == 0 && t) atomicAdd(&a.deg[lead], t);
             } else if (beyond) {
-                atomicAdd(&deg[lo], beyond);
+                atomicAdd(&a.deg[lo], beyond);
             }
         }
         // bits, lower-id degrees and the upper digit histogram of this tile's distinct edges
-        uint32_t clo = 0xFFFFFFFFu, cc = 0;  // carried group (uniform)
-#pragma unroll
-        for (int i = 0; i < (int)kDedupItems; ++i) {
-            const uint32_t word = wave * kDedupItems + i;
+        if (lane < kDedupItems) {
+            const uint32_t word = wave * kDedupItems + lane;
             const unsigned long long F = s_first[word];
-            if (lane == 0) {
-                if (word * 64u >= p0) {
-                    if (base + word * 64u < cap) first[(base >> 6) + word] = F;
-                } else if (F) {
-                    atomicOr(&first[(base >> 6) + word], F);
-                }
-                found += (unsigned long long)__popcll(F);
+            if (word * 64u >= p0) {
+                if (base + word * 64u < cap) a.first[(base >> 6) + word] = F;
+            } else if (F) {
+                atomicOr(&a.first[(base >> 6) + word], F);
             }
-            const uint32_t lo = (uint32_t)(k[i] >> nb);
-            const bool mine = (F >> lane) & 1ull;
-            if (mine) {
-                const uint32_t hi = (uint32_t)(k[i] & mask);
-                if (ubins) atomicAdd(&s_hist[hi >> ushift], 1u);
-                if (uatomics) atomicAdd(&deg[hi], 1u);
-            }
-            const uint32_t lo_prev = (uint32_t)__shfl_up((int)lo, 1, 64);
-            const unsigned long long H = __ballot(lane == 0 || lo != lo_prev);  // group starts
-            const uint32_t s = 63u - (uint32_t)__builtin_clzll(H & upto);      // this lane's group start
-            const uint32_t c = (uint32_t)__popcll((F & upto) >> s);            // its firsts up to this lane
-            const bool merge = __builtin_amdgcn_readfirstlane(lo) == clo;     // first group continues the carry
-            const uint32_t tail = 63u - (uint32_t)__builtin_clzll(H);          // start of lane 63's group
-            if (lane != 63 && ((H >> (lane + 1)) & 1ull)) {                    // last lane of an inner group
-                const uint32_t cnt = c + ((s == 0 && merge) ? cc : 0u);
-                if (cnt) atomicAdd(&deg[lo], cnt);
-            }
-            const uint32_t c63 = (uint32_t)__builtin_amdgcn_readlane((int)c, 63);
-            const uint32_t lo63 = (uint32_t)__builtin_amdgcn_readlane((int)lo, 63);
-            if (tail == 0 && merge) {
-                cc += c63;
-            } else {
-                if (!merge && cc && lane == 0) atomicAdd(&deg[clo], cc);
-                clo = lo63;
-                cc = c63;
-            }
+            found += (unsigned long long)__popcll(F);
         }
-        if (cc && lane == 0) atomicAdd(&deg[clo], cc);
+        count_firsts(a, k, s_first, s_hist, wave, lane);
         __syncthreads();  // the LDS is reused by the next tile
     }
     if (found) atomicAdd(&s_m, found);
     __syncthreads();
-    if (tid == 0 && s_m) atomicAdd(&meta->m, s_m);
-    for (uint32_t i = tid; i < ubins; i += kDedupThreads)
-        if (s_hist[i]) atomicAdd(&uhist[i], s_hist[i]);
+    if (threadIdx.x == 0 && s_m) atomicAdd(&a.meta->m, s_m);
+    for (uint32_t i = threadIdx.x; i < a.ubins; i += kDedupThreads)
+        if (s_hist[i]) atomicAdd(&a.uhist[i], s_hist[i]);
+}
+
+// The first of the boundaries (first keys of tiles) of group `top`, of which boundary t is one.
+__device__ __forceinline__ uint32_t first_boundary(const unsigned long long* keys, uint32_t low, unsigned long long top,
+                                                   uint32_t t, uint32_t lane) {
+    uint32_t lo = 0, hi = t;  // boundaries below lo are not in the group, hi is
+    uint32_t from = t > 64 ? t - 64 : 0u;  // most groups begin near
+    while (lo < hi) {
+        const uint32_t step = (hi - from + 63) / 64, b = from + lane * step;
+        const unsigned long long in =
+            __ballot(b < hi && (keys[(uint64_t)(b < hi ? b : hi) * kDedupTile] >> low) == top);
+        if (!in) {
+            lo = from + (hi - from - 1) / step * step + 1;  // past the last one looked at
+        } else {
+            const uint32_t i = (uint32_t)__builtin_ctzll(in);
+            hi = from + i * step;
+            if (i) lo = from + (i - 1) * step + 1;
+            else if (from <= lo) lo = hi;
+        }
+        from = lo;
+    }
+    return hi;
+}
+
+// The long groups, tile by tile (see above).
+__global__ void __launch_bounds__(kDedupThreads) k_dedup_long(Dedup a) {
+    __shared__ uint32_t s_set[1u << (kGroupBits - 5)];
+    __shared__ unsigned long long s_first[kDedupWords];
+    __shared__ uint32_t s_hist[1024];
+    __shared__ unsigned long long s_m;
+    if (!*a.any_long) return;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t low_mask = (1u << a.low) - 1u, set_words = long_words(a.low);
+    for (uint32_t i = tid; i < a.ubins; i += kDedupThreads) s_hist[i] = 0;
+    if (tid == 0) s_m = 0;
+    unsigned long long found = 0;
+    for (uint64_t base = blockIdx.x * (uint64_t)kDedupTile; base < a.cap; base += (uint64_t)gridDim.x * kDedupTile) {
+        const uint32_t len = a.cap - base < kDedupTile ? (uint32_t)(a.cap - base) : kDedupTile;
+        const uint32_t longs = long_groups(a, base, lane);
+        if (!longs) continue;  // uniform in the workgroup
+        unsigned long long k[kDedupItems];
+        unsigned long long F[kDedupItems];
+        const unsigned long long head = a.keys[base] >> a.low;
+        const unsigned long long next = base + len < a.cap ? a.keys[base + len] >> a.low : ~0ull;
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const uint64_t x = base + wave * (64u * kDedupItems) + i * 64u + lane;
+            k[i] = x < a.cap ? a.keys[x] : ~0ull;
+            F[i] = 0;
+        }
+        // the group of the tile's first key, then the one that is cut at its end
+        for (uint32_t part = 0; part < 2; ++part) {
+            if (!(longs & (1u << part)) || (part == 1 && next == head)) continue;
+            const unsigned long long top = part ? next : head;
+            const uint32_t tile = (uint32_t)(base / kDedupTile);
+            const uint32_t name = part ? tile + 1 : tile ? first_boundary(a.keys, a.low, top, tile, lane) : 0u;
+            uint32_t* const set = a.bits + (uint64_t)(name / kLongTiles) * set_words;
+            __syncthreads();
+            for (uint32_t i = tid; i < set_words; i += kDedupThreads) s_set[i] = 0;
+            __syncthreads();
+            uint32_t mine = 0;  // keys that set their bit in this tile's set
+#pragma unroll
+            for (int i = 0; i < (int)kDedupItems; ++i) {
+                const uint64_t x = base + wave * (64u * kDedupItems) + i * 64u + lane;
+                if (x >= a.cap || (k[i] >> a.low) != top || k[i] == a.sentinel) continue;
+                const uint32_t b = (uint32_t)k[i] & low_mask, bit = 1u << (b & 31u);
+                if (__hip_atomic_load(&s_set[b >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) continue;
+                if (!(atomicOr(&s_set[b >> 5], bit) & bit)) mine |= 1u << i;
+            }
+            __syncthreads();
+            for (uint32_t i = tid; i < set_words; i += kDedupThreads) {
+                const uint32_t v = s_set[i];
+                if (!v) continue;
+                uint32_t old = __hip_atomic_load(&set[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (v & ~old) old = atomicOr(&set[i], v);
+                s_set[i] = v & ~old;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < (int)kDedupItems; ++i) {
+                const uint32_t b = (uint32_t)k[i] & low_mask;
+                F[i] |= __ballot(((mine >> i) & 1u) && ((s_set[b >> 5] >> (b & 31u)) & 1u));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < (int)kDedupItems; ++i) {
+            const uint32_t word = wave * kDedupItems + i;
+            if (lane == 0) {
+                s_first[word] = F[i];
+                if (F[i]) a.first[(base >> 6) + word] |= F[i];
+                found += (unsigned long long)__popcll(F[i]);
+            }
+        }
+        wave_sync();  // a wavefront reads its own words
+        count_firsts(a, k, s_first, s_hist, wave, lane);
+    }
+    __syncthreads();
+    if (found) atomicAdd(&s_m, found);
+    __syncthreads();
+    if (tid == 0 && s_m) atomicAdd(&a.meta->m, s_m);
+    for (uint32_t i = tid; i < a.ubins; i += kDedupThreads)
+        if (s_hist[i]) atomicAdd(&a.uhist[i], s_hist[i]);
 }
 
 // Upper ids' degrees.  The ids are partitioned by hi >> sub (bins partitions, sizes in uhist; with one
@@ -1290,6 +1452,7 @@ PrepZero prep_zero(uint32_t n, uint64_t m_in) {
     size_t w = kTicketWords + kHistWords;
     z.deg = w;     w += ((size_t)n + 1 + 3) & ~(size_t)3;
     z.first = w;   w += 2 * (((size_t)m_in + 63) / 64 + 1);
+    z.bits = w;    w += (size_t)long_set_words(canon_low(nb), m_in);
     w = (w + 3) & ~(size_t)3;
     z.status = w;
     const uint64_t tm = pass_tiles(m_in, 8), tu = pass_tiles(m_in, 4), tn = pass_tiles(n, 8);
@@ -1425,10 +1588,15 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
     {
         const uint32_t ud = upper_digit(nb), sub = ud ? nb - ud : nb;
         const uint64_t tiles = (m_in + kDedupTile - 1) / kDedupTile;
-        hipLaunchKernelGGL(k_dedup, dim3((uint32_t)std::min<uint64_t>(tiles, 2 * (uint64_t)cu_count)), dim3(kDedupThreads), 0, stream,
-                           t.keys_b, nb, low, m_in, sentinel, t.first, t.deg, uhist, ud ? 1u << ud : 0u, sub,
-                           upper_atomics(nb), g.meta);
+        const uint32_t grid = (uint32_t)std::min<uint64_t>(tiles, 2 * (uint64_t)cu_count);
+        const Dedup d{t.keys_b, m_in, sentinel, t.first, t.bits, t.deg, uhist, g.meta, t.zero + kTicketWords - 1, nb, low,
+                      ud ? 1u << ud : 0u, sub, upper_atomics(nb)};
+        hipLaunchKernelGGL(k_dedup, dim3(grid), dim3(kDedupThreads), 0, stream, d);
         TC_TRY(hipGetLastError());
+        if (tiles >= kLongTiles) {
+            hipLaunchKernelGGL(k_dedup_long, dim3(grid), dim3(kDedupThreads), 0, stream, d);
+            TC_TRY(hipGetLastError());
+        }
         const LoadUpper upper{t.keys_b, t.first, mask};
         uint32_t* ids = nullptr;
         if (ud) {

@@ -101,3 +101,53 @@ def test_build_upper_partitions(n, m):
     ids = np.concatenate([at + np.arange(2000), [n - 1, 0, 1]]).astype(np.uint32)
     s, d = ids[rng.integers(0, len(ids), m)], ids[rng.integers(0, len(ids), m)]
     _check(gg.EdgeList(n, s, d, f"narrow{n}_{m}"))
+
+
+@pytest.mark.parametrize("n,spread", [(60, 8), (700, 300), (4096, 4000), (70000, 4000), (70000, 1), (1 << 20, 8000),
+                                      ((1 << 24) + 1, 16000)])
+def test_build_long_groups(n, spread):
+    """Groups of equal top bits that hold the first keys of three, four or more tiles of 4096, begin or end at a
+    tile, or follow one another within one, of few or many distinct pairs (`spread` upper ids)."""
+    sizes = [1000, 3096, 16384, 12288, 12289, 16383, 16385, 20000, 100, 3, 20001, 4095, 8200, 40000, 28671, 2]
+    rng = np.random.default_rng(n + spread)
+    s, d = [], []
+    for i, size in enumerate(sizes):
+        s.append(np.full(size, i, np.uint32))
+        d.append((i + 1 + rng.integers(0, min(spread, n - i - 1), size)).astype(np.uint32))
+    s, d = np.concatenate(s), np.concatenate(d)
+    order = rng.permutation(len(s))
+    flip = rng.random(len(s)) < 0.5
+    s, d = s[order], d[order]
+    _check(gg.EdgeList(n, np.where(flip, d, s), np.where(flip, s, d), f"groups{n}_{spread}"))
+
+
+@pytest.mark.parametrize("n", [4, 700, 4096, 1 << 20])
+@pytest.mark.parametrize("pairs", [1, 4])
+def test_build_repeated_samples_are_not_read_by_one_workgroup(n, pairs):
+    """2^24 samples of few pairs, a third of them self-loops, are built in the time of distinct ones (0.5-0.9 ms);
+    read to their end by one workgroup they took 13-26."""
+    import time
+
+    import torch
+
+    from paper_2103_08053_amd import Context
+    rng = np.random.default_rng(n + pairs)
+    m = 1 << 24
+    e = rng.choice(n, (2, pairs)).astype(np.uint32)
+    e[:, 0] = 0, n - 1
+    at = rng.integers(0, pairs, m)
+    s, d = e[0][at], e[1][at]
+    s[: m // 3] = d[: m // 3]
+    print(f"[gpu] build repeats n={n} m={m} pairs={pairs}", flush=True)
+    ctx = Context(0)
+    s, d = (torch.as_tensor(x.astype(np.int32)).to("cuda") for x in (s, d))
+    ms = []
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        gr = ctx.build(s, d, n)
+        torch.cuda.synchronize()
+        ms.append((time.perf_counter() - t0) * 1e3)
+    want = {(min(int(a), int(b)), max(int(a), int(b))) for a, b in e.T if a != b}
+    assert gr.info().m == len(want)
+    assert min(ms) < 5, ms
