@@ -80,7 +80,8 @@ typedef struct tc_params {
  * (degree, id) one).  Default: the (degree, id) rank.  At most one of: */
 #define TC_F_ORDER_INDEGREE   0x40u  /* continuous ids by oriented in-degree, largest first */
 #define TC_F_ORDER_COLLECTIVE 0x80u  /* vertices by collective degree W(u), largest first, give their
-                                        not-yet-numbered out-neighbours the next ids in list order */
+                                        not-yet-numbered out-neighbours the next ids in the order
+                                        of those' input ids */
 /* Intra-vertex work assignment of the probe (paper Section 4.2).  Default: virtual combination.
  * At most one of (the build is the same; counts use the parameters the graph was built with): */
 #define TC_F_SUBWAVE_8   0x100u  /* groups of 8 lanes, one out-neighbour list per group */

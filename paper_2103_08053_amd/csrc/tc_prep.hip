@@ -1333,18 +1333,23 @@ __global__ void k_key_collective(const unsigned long long* __restrict__ work, ui
 }
 
 // Greedy numbering of the collective order, in parallel: vertices taken in W order hand the next ids
-// to their not-yet-numbered out-neighbours in list order, so v's id follows its first claim, the
-// smallest (position of u in W order, position of v in u's list) over its in-edges u -> v.
-// One wavefront per row.
+// to their not-yet-numbered out-neighbours in the order of those' input ids, so v's id follows its first
+// claim, the smallest (position of u in W order, input id of v) over its in-edges u -> v.  (Not the place
+// in u's list, which differs from build to build.)  order: degree << 32 | input id of every rank.  One
+// wavefront per row.
 __global__ void k_claim(const int64_t* __restrict__ off, const uint32_t* __restrict__ col,
-                        const uint32_t* __restrict__ posw, uint32_t n, unsigned long long* __restrict__ claim) {
+                        const uint32_t* __restrict__ posw, const unsigned long long* __restrict__ order, uint32_t n,
+                        unsigned long long* __restrict__ claim) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t nwv = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < n; r += nwv) {
         const int64_t b = off[r];
         const uint32_t d = (uint32_t)(off[r + 1] - b);
         const unsigned long long hi = (unsigned long long)posw[r] << 32;
-        for (uint32_t j = lane; j < d; j += 64) atomicMin(&claim[col[b + j]], hi | j);
+        for (uint32_t j = lane; j < d; j += 64) {
+            const uint32_t v = col[b + j];
+            atomicMin(&claim[v], hi | (uint32_t)order[v]);
+        }
     }
 }
 
@@ -1496,7 +1501,8 @@ hipError_t relabel(uint32_t n, const GraphDev& g, const BuildTemp& t, const Batc
         hipLaunchKernelGGL(k_rank, dim3(grid_for(n)), dim3(kThreads), 0, stream, t.order, n, posw);
         TC_TRY(hipGetLastError());
         TC_TRY(fill_u32(t.rk_a, 0xFFFFFFFFu, 2 * (size_t)n, stream));
-        hipLaunchKernelGGL(k_claim, dim3(wave_grid), dim3(kThreads), 0, stream, g.off, g.col, posw, n, t.rk_a);
+        hipLaunchKernelGGL(k_claim, dim3(wave_grid), dim3(kThreads), 0, stream, g.off, g.col, posw, t.skey_a, n,
+                           t.rk_a);
         TC_TRY(hipGetLastError());
         hipLaunchKernelGGL(k_key_claimed, dim3(grid_for(n)), dim3(kThreads), 0, stream, n, t.rk_a);
         TC_TRY(hipGetLastError());

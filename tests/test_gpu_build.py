@@ -151,3 +151,21 @@ def test_build_repeated_samples_are_not_read_by_one_workgroup(n, pairs):
     want = {(min(int(a), int(b)), max(int(a), int(b))) for a, b in e.T if a != b}
     assert gr.info().m == len(want)
     assert min(ms) < 5, ms
+
+
+@pytest.mark.parametrize("flags", [0x80, 0x80 | 0x8, 0x40, 0])
+def test_build_order_does_not_depend_on_the_samples_order(flags):
+    """Hash ids are the graph's own: builds from reordered, repeated and flipped samples get tables of the same
+    collisions, also where ids are handed out neighbour by neighbour (0x80)."""
+    from paper_2103_08053_amd import Context, Params
+    g = gg.rmat(15, 12, seed=21)
+    ctx = Context(0, Params(flags=flags))
+    rng = np.random.default_rng(4)
+    seen = []
+    for i in range(4):
+        at = rng.permutation(np.concatenate([np.arange(g.m_in), rng.integers(0, g.m_in, 1000 * i)]))
+        flip = rng.random(len(at)) < 0.5
+        s, d = np.where(flip, g.dst[at], g.src[at]), np.where(flip, g.src[at], g.dst[at])
+        print(f"[gpu] build order flags {flags:#x} m={len(at)}", flush=True)
+        seen.append(ctx.build(s, d, g.n).collisions())
+    assert all(x == seen[0] for x in seen), seen
