@@ -32,7 +32,8 @@ struct GraphMeta {
     unsigned long long m;           // oriented edges
     unsigned long long wplus;       // W+ = sum over oriented (u, v) of d+(v)
     unsigned int big_full;          // bin-1 vertices whose tables need more than half a CU's LDS (first in bin 1)
-    unsigned int max_dplus, pad1;
+    unsigned int max_dplus;
+    unsigned int hub_span;          // ranks from the first one whose out-degree no LDS table holds (0: none)
     // vertex counts: global-memory tables, large LDS tables (one workgroup per CU), workgroup LDS
     // tables, wavefront LDS slices, light vertices packed several per wavefront, skipped (d+ < 2 or
     // no 2-hop work)
