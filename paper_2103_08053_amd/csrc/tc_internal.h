@@ -217,7 +217,7 @@ struct GraphDev {
     uint2* elist;       // [m_in] light graphs: list {start, length} of every edge's head, edges in row order
                         // (starts as the count reads lists: in col, or in rec); null where the rows are not
                         // in rank order (relabelled and counting-sort builds)
-    // core path only, else null
+    // core path only, else null (in elist's memory: used where light_on does not hold)
     uint4* blk;         // [core_start(m_in, n)] block words of every list
     uint2* bl;          // [n] {first quad, quads} of each list's block words
     uint32_t* rend;     // [n] end of each list's ids outside the core (they come first)

@@ -96,3 +96,16 @@ def test_core_path_shards_replay_static_and_small_grids(g):
         c1 = Context(0, Params(grid_wgs=grid))
         t1, p1 = c1.build(g.src, g.dst, g.n).count(per_vertex=True)
         assert t1 == want.total and (p1.cpu().numpy() == ref).all()
+
+
+@pytest.mark.parametrize("n,m", [(1 << 22, 1 << 26), (1 << 20, 16_777_003), (70_000, 1 << 18)])
+def test_core_path_shares_the_edge_list_bounds_memory(n, m):
+    """A graph uses the list bounds per edge or the core path's layout, so its storage holds the larger of them."""
+    import ctypes
+
+    from paper_2103_08053_amd import Context
+    ctx = Context(0)
+    storage, temp = ctypes.c_uint64(), ctypes.c_uint64()
+    assert ctx.lib.tc_graph_footprint(ctx.h, n, m, ctypes.byref(storage), ctypes.byref(temp)) == 0
+    csr = 8 * (n + 1) + 4 * (n + 1) + 4 * m + 4 * n + 4 * n
+    assert storage.value <= csr + max(8 * m, 4 * m + 28 * n) + 4096
