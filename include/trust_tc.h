@@ -19,8 +19,8 @@
  *     tc_graph_count_static, whose scratch is a static buffer that every
  *     device holds for the life of the process).  Host
  *     memory is allocated only for the opaque handles and pinned buffers: a
- *     context's staging (tc_count_graphs) and 64 bytes for the answer of its
- *     one-shot counts.
+ *     context's staging (tc_count_graphs) and a page that the one-shot counts
+ *     of the process read their answers from.
  *   - Ids: vertex ids are uint32 in [0, n), n <= 2^32 - 1.  Edge samples may
  *     repeat, appear in both directions or be self-loops; all are accepted and
  *     cleaned.  n = 0 or m_in = 0 gives a count of 0.

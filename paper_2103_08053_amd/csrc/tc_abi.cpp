@@ -54,7 +54,6 @@ struct tc_context {
         hipGraphExec_t exec;
     };
     std::vector<MultiCapture> mcap;
-    void* answer = nullptr;          // 64 bytes of pinned host memory: a one-shot count's total and error flag
     void* static_scratch = nullptr;  // this device's copy of the library-owned count scratch
     std::vector<Occ> occ;  // resident workgroups per CU, by kernel variant and launch shape
 };
@@ -81,35 +80,40 @@ hipError_t static_scratch(int device, void** out) {
     return hipSuccess;
 }
 
-// Pinned host memory of the contexts' one-shot answers: 64 bytes per context, cut from one page that is
-// kept once allocated (an allocation of its own made creating a context 75 us slower).  Contexts beyond
-// the page's 64 take an allocation each.
+// Pinned host memory that one-shot counts read their answers from: 64 bytes per call that is running, cut from
+// one page that is kept once allocated (an allocation of its own made creating a context 75 us slower).  Calls
+// beyond the page's 64 take an allocation each.
 constexpr size_t kAnswerBytes = 64;
 std::mutex g_answer_mutex;
 char* g_answer_page = nullptr;
 uint64_t g_answer_used = 0;  // a bit per slot
 
-hipError_t take_answer(void** out) {
-    std::lock_guard<std::mutex> lock(g_answer_mutex);
-    if (~g_answer_used) {
-        if (!g_answer_page)
-            if (hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g_answer_page), 64 * kAnswerBytes,
-                                             hipHostMallocPortable); e != hipSuccess) return e;
-        const int slot = __builtin_ctzll(~g_answer_used);
-        g_answer_used |= 1ull << slot;
-        *out = g_answer_page + slot * kAnswerBytes;
-        return hipSuccess;
+struct Answer {
+    void* host = nullptr;
+    hipError_t take() {
+        std::lock_guard<std::mutex> lock(g_answer_mutex);
+        if (~g_answer_used) {
+            if (!g_answer_page)
+                if (hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g_answer_page), 64 * kAnswerBytes,
+                                                 hipHostMallocPortable); e != hipSuccess) return e;
+            const int slot = __builtin_ctzll(~g_answer_used);
+            g_answer_used |= 1ull << slot;
+            host = g_answer_page + slot * kAnswerBytes;
+            return hipSuccess;
+        }
+        return hipHostMalloc(&host, kAnswerBytes, hipHostMallocPortable);
     }
-    return hipHostMalloc(out, kAnswerBytes, hipHostMallocPortable);
-}
-
-void give_answer(void* p) {
-    if (!p) return;
-    std::lock_guard<std::mutex> lock(g_answer_mutex);
-    const uintptr_t at = reinterpret_cast<uintptr_t>(p) - reinterpret_cast<uintptr_t>(g_answer_page);
-    if (g_answer_page && at < 64 * kAnswerBytes) g_answer_used &= ~(1ull << (at / kAnswerBytes));
-    else (void)hipHostFree(p);
-}
+    ~Answer() {
+        if (!host) return;
+        std::lock_guard<std::mutex> lock(g_answer_mutex);
+        const uintptr_t at = reinterpret_cast<uintptr_t>(host) - reinterpret_cast<uintptr_t>(g_answer_page);
+        if (g_answer_page && at < 64 * kAnswerBytes) g_answer_used &= ~(1ull << (at / kAnswerBytes));
+        else (void)hipHostFree(host);
+    }
+    Answer() = default;
+    Answer(const Answer&) = delete;
+    Answer& operator=(const Answer&) = delete;
+};
 
 }  // namespace
 
@@ -855,7 +859,7 @@ tc_status tc_create(int hip_device, const tc_params* p, tc_context** out) {
             return TC_E_DEVICE;
         }
     }
-    if (take_answer(&c->answer) != hipSuccess) {
+    if (Answer().take() != hipSuccess) {  // the page, before the first count needs it
         delete c;
         return TC_E_DEVICE;
     }
@@ -880,7 +884,6 @@ tc_status tc_destroy(tc_context* ctx) {
         if (st.host) (void)hipHostFree(st.host);
     }
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
-    give_answer(ctx->answer);
     delete ctx;
     return TC_OK;
 }
@@ -978,9 +981,19 @@ namespace {
 // the total and the range flag back (synchronises the stream).
 tc_status count_one_shot(tc_context* ctx, uint32_t n, uint64_t m_in, const uint32_t* d_src, const uint32_t* d_dst,
                          uint64_t* d_per_vertex, void* d_ws, const Layout& L, hipStream_t st, uint64_t* h_total) {
-    // pinned: the copies of the total and the flag go to the host without a staging copy
-    tc::SmallResult* const host = static_cast<tc::SmallResult*>(ctx->answer);
+    // pinned: the copy of the total and the flag goes to the host without a staging copy
+    Answer answer;
+    HIP_TRY(ctx, answer.take());
+    tc::SmallResult* const host = static_cast<tc::SmallResult*>(answer.host);
     *host = tc::SmallResult{0ull, 0u, 0u};
+    auto fetch = [&](const void* d) -> tc_status {  // (a slot whose copy may still be under way is not given back)
+        HIP_TRY(ctx, hipMemcpyAsync(host, d, sizeof(*host), hipMemcpyDeviceToHost, st));
+        if (const hipError_t e = hipStreamSynchronize(st); e != hipSuccess) {
+            answer.host = nullptr;
+            return hip_fail(ctx, e, "hipStreamSynchronize");
+        }
+        return TC_OK;
+    };
     if (small_path(ctx, n, m_in)) {
         char* ws = scratch_base(d_ws);
         const tc::SmallLayout S = tc::small_layout(n, m_in);
@@ -999,8 +1012,7 @@ tc_status count_one_shot(tc_context* ctx, uint32_t n, uint64_t m_in, const uint3
             HIP_TRY(ctx, hipEventRecord(ctx->ev[3], st));
             ctx->have_build = ctx->have_count = true;
         }
-        HIP_TRY(ctx, hipMemcpyAsync(host, a.result, sizeof(*host), hipMemcpyDeviceToHost, st));
-        HIP_TRY(ctx, hipStreamSynchronize(st));
+        if (tc_status s = fetch(a.result)) return s;
         if (host->err & 1u) return fail(ctx, TC_E_RANGE, "an input vertex id is >= n = %u", n);
         *h_total = host->total;
         return TC_OK;
@@ -1012,12 +1024,10 @@ tc_status count_one_shot(tc_context* ctx, uint32_t n, uint64_t m_in, const uint3
     uint64_t* d_total = g.empty ? reinterpret_cast<uint64_t*>(scratch_base(d_scr) + L.c_total)
                                 : reinterpret_cast<uint64_t*>(&g.dev.meta->total);
     if (tc_status s = count_into(ctx, &g, d_total, d_per_vertex, d_scr, L, st)) return s;
-    if (!g.empty) {
-        static_assert(sizeof(tc::SmallResult) == sizeof(tc::GraphMeta) - offsetof(tc::GraphMeta, total) &&
-                      offsetof(tc::SmallResult, err) == 8, "total and flag in one copy");
-        HIP_TRY(ctx, hipMemcpyAsync(host, d_total, sizeof(*host), hipMemcpyDeviceToHost, st));
-    }
-    HIP_TRY(ctx, hipStreamSynchronize(st));
+    static_assert(sizeof(tc::SmallResult) == sizeof(tc::GraphMeta) - offsetof(tc::GraphMeta, total) &&
+                  offsetof(tc::SmallResult, err) == 8, "total and flag in one copy");
+    if (g.empty) HIP_TRY(ctx, hipStreamSynchronize(st));
+    else if (tc_status s = fetch(d_total)) return s;
     const unsigned int err = host->err;
     if (err & 1u) return fail(ctx, TC_E_RANGE, "an input vertex id is >= n = %u", n);
     *h_total = host->total;

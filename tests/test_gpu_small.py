@@ -128,3 +128,40 @@ def test_small_repeated_samples_are_not_bound_by_their_atomics(n, pairs):
         ctx.count(s, d, n, workspace=ws)
         ms.append((time.perf_counter() - t0) * 1e3)
     assert min(ms) < 5, ms
+
+
+def test_small_answers_of_calls_at_the_same_time():
+    """One-shot counts that run at the same time, in threads of their own, each get their own answer: on contexts of
+    their own, and through one context that has been warmed up."""
+    import threading
+
+    import torch
+
+    from paper_2103_08053_amd import Context
+    shared = Context(0)
+    graphs = [gg.complete(20 + 7 * i) for i in range(8)] + [gg.with_isolated(gg.complete(30 + i), 9000) for i in range(8)]
+    wrong, ready = [], threading.Barrier(len(graphs))
+
+    def work(i, ctx):
+        g, k = graphs[i], [20 + 7 * i, 30 + i - 8][i >= 8]
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            s, d = (torch.as_tensor(x.astype(np.int32)).to("cuda") for x in (g.src, g.dst))
+            ws = torch.empty(ctx.workspace_bytes(g.n, g.m_in), dtype=torch.uint8, device="cuda")
+            stream.synchronize()
+            ready.wait()
+            for _ in range(200):
+                total, _ = ctx.count(s, d, g.n, workspace=ws, stream=stream)
+                if total != k * (k - 1) * (k - 2) // 6:
+                    wrong.append((i, k, total))
+
+    for g in graphs:
+        shared.count(g.src, g.dst, g.n)
+    for ctxs in ([Context(0) for _ in graphs], [shared] * len(graphs)):
+        print(f"[gpu] small {len(graphs)} threads", flush=True)
+        threads = [threading.Thread(target=work, args=(i, c)) for i, c in enumerate(ctxs)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong, wrong[:5]
