@@ -165,3 +165,20 @@ def test_small_answers_of_calls_at_the_same_time():
         for t in threads:
             t.join()
         assert not wrong, wrong[:5]
+
+
+@pytest.mark.parametrize("g", [gg.complete(3), gg.complete(150), gg.star(2000), gg.rmat(8, 8, seed=1), gg.rmat(12, 16, seed=2),
+                               gg.erdos_renyi(500, 3000, seed=3), gg.erdos_renyi(8000, 20_000, seed=4)],
+                         ids=lambda g: g.name)
+def test_general_one_shot_path_on_small_graphs(g):
+    """The default one-shot count of the same graphs with isolated vertices beyond the bit matrix's 8192: the build
+    and the hash kernels, total and per vertex."""
+    from paper_2103_08053_amd import Context
+    d = gg.dirty(gg.with_isolated(g, 8200), seed=5)
+    print(f"[gpu] one-shot {d.name} n={d.n} m_in={d.m_in}", flush=True)
+    assert d.n > 8192
+    want = oracle.count(d.n, d.src, d.dst, per_vertex=True)
+    ctx = Context(0)
+    total, pv = ctx.count(d.src, d.dst, d.n, per_vertex=True)
+    assert total == want.total and (pv.cpu().numpy().astype(np.uint64) == want.per_vertex).all()
+    assert ctx.count(d.src, d.dst, d.n)[0] == want.total

@@ -147,3 +147,12 @@ def test_measured_traffic_needs_matching_source_workload_and_mode(tmp_path, monk
     assert bench.measured_traffic(True, "rmat22") is None
     summary("0" * 40, True, "er25")
     assert bench.measured_traffic(True, "er25") is None
+
+
+def test_smoke_covers_both_routes_of_a_one_shot_count():
+    """Up to 8192 vertices a default one-shot count runs none of the build, hash and core kernels; the core path
+    begins at 2^17 samples."""
+    import __graft_entry__ as entry
+    graphs = entry.smoke_graphs()
+    assert any(g.n <= 8192 for g in graphs)
+    assert any(g.n > 8192 and g.m_in >= 1 << 17 for g in graphs)
