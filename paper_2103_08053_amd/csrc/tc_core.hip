@@ -738,11 +738,6 @@ __global__ void __launch_bounds__(64 * NW) tc_core_kernel(CoreArgs a) {
 typedef void (*CoreFn)(CoreArgs);
 constexpr uint32_t kCoreDcap[3] = {128, 1024, 4096};
 
-// Wavefronts per owner.  Part 0: two (R-MAT 22, 8 KB tables: 3.0 ms against 3.2 with four, per-vertex 3.65
-// against 4.3), but four beside a 16 KB table, of which a CU holds few (R-MAT 26 per-vertex 94.8 ms against 98.0).  Part 1:
-// eight (2.7 ms; per-vertex 4.8 against 5.7 with four and 8.0 with sixteen).
-int core_waves(int part, uint32_t S) { return part == 0 ? (S > 20 ? 2 : 4) : part == 1 ? 8 : 16; }
-
 CoreFn pick_core(int part, bool pv, uint32_t S) {
     switch (part) {
         case 0:
@@ -764,6 +759,11 @@ uint32_t core_lds(int part, bool pv, uint32_t S) {
     } while (0)
 
 }  // namespace
+
+// Wavefronts per owner.  Part 0: two (R-MAT 22, 8 KB tables: 3.0 ms against 3.2 with four, per-vertex 3.65
+// against 4.3), but four beside a 16 KB table, of which a CU holds few (R-MAT 26 per-vertex 94.8 ms against 98.0).  Part 1:
+// eight (2.7 ms; per-vertex 4.8 against 5.7 with four and 8.0 with sixteen).
+uint32_t core_waves(int part, uint32_t S) { return part == 0 ? (S > 20 ? 2u : 4u) : part == 1 ? 8u : 16u; }
 
 hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream) {
     const uint32_t lds = 4u << (32 - a.S);

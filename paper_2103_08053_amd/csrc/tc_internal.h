@@ -439,6 +439,7 @@ struct CoreArgs {
 };
 inline uint32_t core_magic(uint32_t S) { return (uint32_t)(((1ull << 32) + S - 1) / S); }  // x / S = umulhi(x, magic), x < 2^26
 hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream);
+uint32_t core_waves(int part, uint32_t S);  // wavefronts of a workgroup of that part's launch
 hipError_t core_info(int part, bool pv, uint32_t S, int* blocks_per_cu);
 hipError_t core_launch(int part, bool pv, uint32_t grid, CoreArgs a, hipStream_t stream);
 
