@@ -251,7 +251,7 @@ __global__ void k_place_write(const uint32_t* __restrict__ off32, uint32_t n,
 // (the ids the count handles are record ids), in rank order.
 __global__ void k_clear_record_starts(unsigned long long* __restrict__ tv, const uint32_t* __restrict__ place,
                                       uint32_t n) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x)
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x)
         tv[rec_id(place[2 * (uint64_t)r])] = 0ull;
 }
 
@@ -1255,7 +1255,7 @@ __global__ void __launch_bounds__(1024) k_schedule(const uint32_t* __restrict__ 
     unsigned long long hw = 0, ce = 0;
     uint32_t h3 = 0;
     for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < n; base += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t r = (uint32_t)base + threadIdx.x;
+        const uint64_t r = base + threadIdx.x;
         const bool act = r < n;
         const uint32_t d = act ? off[r + 1] - off[r] : 0u;
         const unsigned long long w = act ? work[r] : 0ull;
@@ -1346,7 +1346,7 @@ __global__ void __launch_bounds__(1024) k_schedule(const uint32_t* __restrict__ 
 }
 
 __global__ void k_rank(const uint32_t* __restrict__ order, uint32_t n, uint32_t* __restrict__ rank) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x)
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x)
         rank[order[r]] = r;
 }
 
@@ -1361,7 +1361,7 @@ __global__ void k_dplus(const uint32_t* __restrict__ off, uint32_t n, uint32_t* 
 // In-degree order: larger oriented in-degree d-(r) = deg(r) - d+(r) first, ties by rank.
 __global__ void k_key_indegree(const unsigned long long* __restrict__ order, const uint32_t* __restrict__ dplus,
                                uint32_t n, unsigned long long* __restrict__ key) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t din = (uint32_t)(order[r] >> 32) - dplus[r];  // order[r] = degree << 32 | id
         key[r] = ((unsigned long long)(0xFFFFFFFFu - din) << 32) | r;
     }
@@ -1370,7 +1370,7 @@ __global__ void k_key_indegree(const unsigned long long* __restrict__ order, con
 // Collective degree W(r), larger first, ties by rank.
 __global__ void k_key_collective(const unsigned long long* __restrict__ work, uint32_t n,
                                  unsigned long long* __restrict__ key) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
         const unsigned long long w = work[r] > 0xFFFFFFFFull ? 0xFFFFFFFFull : work[r];
         key[r] = ((0xFFFFFFFFull - w) << 32) | r;
     }
@@ -1386,7 +1386,7 @@ __global__ void k_claim(const int64_t* __restrict__ off, const uint32_t* __restr
                         unsigned long long* __restrict__ claim) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t nwv = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < n; r += nwv) {
+    for (uint64_t r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < n; r += nwv) {
         const int64_t b = off[r];
         const uint32_t d = (uint32_t)(off[r + 1] - b);
         const unsigned long long hi = (unsigned long long)posw[r] << 32;
@@ -1399,13 +1399,13 @@ __global__ void k_claim(const int64_t* __restrict__ off, const uint32_t* __restr
 
 // Unclaimed vertices (no in-edges) follow every claimed one, by rank.
 __global__ void k_key_claimed(uint32_t n, unsigned long long* __restrict__ claim) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x)
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x)
         if (claim[r] == ~0ull) claim[r] = (0xFFFFFFFFull << 32) | r;
 }
 
 __global__ void k_perm_dplus(const uint32_t* __restrict__ dplus, const uint32_t* __restrict__ pi, uint32_t n,
                              uint32_t* __restrict__ nd) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
         nd[pi[r]] = dplus[r];
         if (r == 0) nd[n] = 0;
     }
@@ -1417,7 +1417,7 @@ __global__ void k_relabel_rows(const int64_t* __restrict__ off, const uint32_t* 
                                uint32_t* __restrict__ col2) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t nwv = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < n; r += nwv) {
+    for (uint64_t r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < n; r += nwv) {
         const int64_t b = off[r];
         const uint32_t d = (uint32_t)(off[r + 1] - b);
         const int64_t b2 = off2[pi[r]];
@@ -1426,17 +1426,17 @@ __global__ void k_relabel_rows(const int64_t* __restrict__ off, const uint32_t* 
 }
 
 __global__ void k_compose(uint32_t* __restrict__ rank, const uint32_t* __restrict__ pi, uint32_t n) {
-    for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) rank[x] = pi[rank[x]];
+    for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < n; x += (uint64_t)gridDim.x * blockDim.x) rank[x] = pi[rank[x]];
 }
 
 __global__ void k_scatter_u32(const uint32_t* __restrict__ in, const uint32_t* __restrict__ pi, uint32_t n,
                               uint32_t* __restrict__ out) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) out[pi[r]] = in[r];
+    for (uint64_t r = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) out[pi[r]] = in[r];
 }
 
 __global__ void k_gather(const unsigned long long* __restrict__ tv, const uint32_t* __restrict__ rank, uint32_t n,
                          const uint32_t* __restrict__ place, unsigned long long* __restrict__ out) {
-    for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
+    for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < n; x += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t r = rank[x];
         out[x] = tv[place ? rec_id(place[2 * (uint64_t)r]) : r];
     }

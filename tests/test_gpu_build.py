@@ -204,3 +204,26 @@ def test_build_dense_rows_in_rank_order():
         ms.append(best * 1e3)
         assert total == k * (k - 1) * (k - 2) // 6 and bool((pv == each).all())
     assert ms[1] < 1.15 * ms[0], ms
+
+
+def test_build_largest_id_range():
+    """2^32 - 1 vertices, the most that ids allow: loops over vertices end, and every vertex is scheduled once."""
+    import torch
+
+    from paper_2103_08053_amd import Context
+    n = (1 << 32) - 1
+    ids = np.array([0, 1, 2, 77, 1 << 16, 1 << 31, n - 1025, n - 1024, n - 3, n - 2, n - 1], np.uint32)
+    i, j = np.triu_indices(len(ids), 1)
+    ctx = Context(0)
+    torch.cuda.empty_cache()
+    need = ctx.workspace_bytes(n, len(i))
+    if torch.cuda.mem_get_info()[0] < need + (2 << 30):
+        pytest.skip(f"{need >> 30} GiB of device memory needed")
+    print(f"[gpu] build n={n} workspace {need >> 30} GiB", flush=True)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    try:
+        k = len(ids)
+        assert ctx.count(ids[i].astype(np.int64), ids[j].astype(np.int64), n, workspace=ws)[0] == k * (k - 1) * (k - 2) // 6
+    finally:
+        del ws
+        torch.cuda.empty_cache()
