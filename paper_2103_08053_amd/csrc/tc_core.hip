@@ -3,7 +3,7 @@
 // Ranks follow degree, so on skewed graphs nearly every 2-hop id is one of the last K ranks (the core;
 // R-MAT scale 22: 99% of the probes end in the last 43,008 of 4.2 M ranks), and a list's core ids crowd
 // together.  Each list's core ids are stored as block words: block index << S | S-bit mask of the
-// block's ids, S = 20..22 (CoreShape), one word per block that holds any (R-MAT 22: 2.8 ids per word;
+// block's ids, S = 20..22 (core_shape), one word per block that holds any (R-MAT 22: 2.8 ids per word;
 // every list padded to whole 16-byte quads).  An owner u keeps its own words in an LDS table indexed by
 // the block (2^(32-S) words: no hashing, no chains, no filter), and a probe is
 //     hits += popcount(table[word >> S] & word),
@@ -18,7 +18,7 @@
 // less fixed work per owner.
 //
 // Whether a graph takes this path is decided on the device (core_on): the owners with enough work must
-// hold at least half of W+, and a quarter of the edges must end in the core.
+// hold at least half of W+, and the path must find enough 2-hop ids per edge in the core.
 #include <algorithm>
 
 #include "tc_fetch.h"
@@ -761,8 +761,10 @@ uint32_t core_lds(int part, bool pv, uint32_t S) {
 }  // namespace
 
 // Wavefronts per owner.  Part 0: two (R-MAT 22, 8 KB tables: 3.0 ms against 3.2 with four, per-vertex 3.65
-// against 4.3), but four beside a 16 KB table, of which a CU holds few (R-MAT 26 per-vertex 94.8 ms against 98.0).  Part 1:
-// eight (2.7 ms; per-vertex 4.8 against 5.7 with four and 8.0 with sixteen).
+// against 4.3), but four beside a 16 KB table, of which a CU holds few (R-MAT 26 per-vertex 94.8 ms against 98.0;
+// whole counts, total / per-vertex, of 80,000 vertices of degree 200: uniform 0.56 / 0.70 ms against 0.59 / 0.76,
+// power law 0.21 / 0.34 against 0.24 / 0.36).  Part 1: eight (2.7 ms; per-vertex 4.8 against 5.7 with four and
+// 8.0 with sixteen).
 uint32_t core_waves(int part, uint32_t S) { return part == 0 ? (S > 20 ? 2u : 4u) : part == 1 ? 8u : 16u; }
 
 hipError_t core_build(const CoreBuild& a, int cu_count, hipStream_t stream) {

@@ -61,13 +61,28 @@ constexpr uint32_t kCoreMinBits = 20;
 constexpr uint32_t kRestClasses = 5 * 32;  // schedule classes of the cut lists: five groups of bins by 32 powers of two
 constexpr uint64_t kCoreMinWork = 1024;
 // Graphs of little work per owner (mean W(u) at most this) get their edges' list bounds (GraphDev::elist):
-// where lists are short, finding them costs the count as much as reading them.
+// where lists are short, finding them costs the count as much as reading them.  Total / per-vertex counts
+// with the bounds and without, by mean W(u): uniform graphs of 2^21 vertices at 176 0.91 / 1.04 ms and
+// 1.24 / 1.25, at 393 1.78 / 2.02 and 1.97 / 2.11, at 533 2.29 / 2.52 and 2.53 / 2.69; R-MAT 20 at 199
+// 0.20 / 0.45 and 0.20 / 0.46, at 494 0.28 / 0.87 and 0.36 / 0.53, at 1266 0.50 / 1.47 and 0.45 / 0.68.
+// Skewed graphs, whose work is in few long lists, lose per vertex from about here on; uniform ones would
+// gain beyond it, but nothing known before the W(u) tells the two apart.
 constexpr uint64_t kLightMeanWork = 512;
 __host__ __device__ inline bool light_on(const GraphMeta& m) {
     return m.pre_owners > 0 && m.pre_work <= kLightMeanWork * m.pre_owners;
 }
+// The core path counts where its owners hold half of W+ and where it takes enough 2-hop ids per edge: each
+// owner is visited twice (block words, cut lists), and only ids in the core go faster.  That number is
+// about (edges into the core / m) * (W+ / m), and the line lies where both ways are even.  Resident totals /
+// per-vertex counts with the path and without, by that number: 15 (uniform, 2^18 vertices of degree 128)
+// 1.20 / 1.32 ms and 0.85 / 0.92; 16 (R-MAT 22, a = 0.45) 5.35 / 5.99 and 4.23 / 4.76; 28 (2^18, degree 256)
+// 3.58 / 4.18 and 2.93 / 3.27; 32 (R-MAT 18, a = 0.45) 0.45 / 0.53 and 0.40 / 0.62; 37 (power law, 50,000
+// vertices of degree 80) 0.18 / 0.29 and 0.22 / 0.61; 49 (2^17, degree 256) 1.54 / 1.84 and 1.50 / 1.68;
+// 78 (R-MAT 22, a = 0.5) 6.82 / 8.00 and 6.95 / 8.17; 370 (R-MAT 22, a = 0.57) 6.9 / 9.8 and 14.9 / 17.8.
+constexpr double kCoreMinIds = 30;
 __host__ __device__ inline bool core_on(const GraphMeta& m) {
-    return !light_on(m) && m.heavy_work > 0 && 2 * m.heavy_work >= m.wplus && 4 * m.core_edges >= m.m;
+    return !light_on(m) && m.heavy_work > 0 && 2 * m.heavy_work >= m.wplus &&
+           (double)m.core_edges * (double)m.wplus >= kCoreMinIds * (double)m.m * (double)m.m;
 }
 // First quad (16 bytes) of row r's block words when its list starts at col[off]: rows in order, each
 // with room for one word per id padded to whole quads (ceil4(d) <= d + 3).

@@ -136,3 +136,43 @@ def test_core_path_keeps_a_grid_of_the_callers():
         seen.append((total, pv))
     assert seen[0][0] == seen[1][0] and bool((seen[0][1] == seen[1][1]).all())
     assert ms[0] < 1.1 * ms[1], ms
+
+
+def test_core_path_is_off_where_few_ids_per_edge_are_in_the_core():
+    """Uniform, 2^18 vertices of degree 128: a third of the edges end in the core, 43 probes per edge; counting
+    there took 1.4 times as long as the bucket kernels."""
+    import time
+
+    import torch
+
+    from paper_2103_08053_amd import Context, Params
+    n, m = 1 << 18, 1 << 24
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    src, dst = (torch.randint(0, n, (m,), generator=gen, device="cuda", dtype=torch.int32) for _ in range(2))
+    print(f"[gpu] core uniform n={n} m_in={m}", flush=True)
+    ms, seen = [], []
+    for flags in (0, TC_F_NO_MID):
+        gr = Context(0, Params(flags=flags)).build(src, dst, n)
+        best = 1e9
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            total, _ = gr.count()
+            best = min(best, time.perf_counter() - t0)
+        ms.append(best * 1e3)
+        seen.append(total)
+    assert seen[0] == seen[1]
+    assert ms[0] < 1.2 * ms[1], ms
+
+
+@pytest.mark.parametrize("k,size", [(330, 130), (150, 600)])
+def test_core_path_on_cliques(k, size):
+    """Cliques inside the core (out-degrees around 128) and half outside it, with enough ids per edge for the path."""
+    from math import comb
+
+    from paper_2103_08053_amd import Context
+    g = _cliques(k, size)
+    print(f"[gpu] core {g.name}", flush=True)
+    total, pv = Context(0).build(g.src, g.dst, g.n).count(per_vertex=True)
+    assert total == k * comb(size, 3)
+    assert (pv.cpu().numpy() == comb(size - 1, 2)).all()
