@@ -69,11 +69,15 @@ typedef struct tc_params {
     uint32_t flags;             /* TC_F_* below */
 } tc_params;
 
+/* Flags ask for a bin, probe, layout or order of their own: with any of them a graph takes neither the core path
+ * (lists' ids among the last ranks 20-22 to a word, for skewed single graphs of 2^17 samples and more) nor, in
+ * one-shot counts of up to 8192 vertices, the adjacency bit matrix.  Lists' order within a vertex is unspecified
+ * and may differ between builds of the same samples. */
 #define TC_F_NO_LPT     0x1u    /* keep rank order instead of largest-work-first within each bin */
 #define TC_F_FORCE_WG   0x2u    /* every vertex goes to the workgroup bin (tests) */
 #define TC_F_FORCE_HUB  0x4u    /* every vertex goes to the global-memory table bin (tests) */
-#define TC_F_SCATTER_CSR 0x8u   /* build the CSR by an atomic counting sort (list order unspecified) instead
-                                   of the default radix passes of the oriented edges by row */
+#define TC_F_SCATTER_CSR 0x8u   /* build the CSR by an atomic counting sort instead of the default radix passes
+                                   of the oriented edges by row */
 #define TC_F_WIDE_ADDR  0x10u   /* 64-bit list addressing even below 2^30 edges (tests) */
 #define TC_F_FORCE_BIG  0x20u   /* every vertex goes to the large-LDS-table bin (tests) */
 /* Vertex order used as the hash ids (paper Section 4.1, reordering; the orientation stays the
@@ -107,7 +111,9 @@ typedef struct tc_params {
                                     reaches 2^31; the
                                     graph's storage grows by 4 R + 8 (n + 1) bytes, the build's
                                     temporaries by 16 (ceil(n / 64) + 1) and a per-vertex count's
-                                    scratch by 8 (R - n) bytes */
+                                    scratch by 8 (R - n) bytes.  On light graphs (mean W(u) of the owners at
+                                    most 512) the default layout keeps the bounds of every edge's list
+                                    beside the edge and spares the same load */
 
 /* Opaque handles. */
 typedef struct tc_context tc_context;
@@ -184,10 +190,11 @@ tc_status tc_graph_build(tc_context* ctx, uint32_t n, uint64_t m_in, const uint3
 tc_status tc_count_scratch_bytes(const tc_context* ctx, uint32_t n, uint64_t m_in, uint64_t* bytes);
 
 /* Count the triangles of a built graph.  Asynchronous: the total is written
- * to d_total (device uint64); d_per_vertex as in tc_count.  This call is one
- * persistent kernel launch (preceded, when some out-degree may exceed the
- * workgroup bin's limit, by one launch for the large-vertex bins) plus, with
- * d_per_vertex, one gather launch. */
+ * to d_total (device uint64); d_per_vertex as in tc_count.  A fixed sequence of
+ * launches: clears, on graphs laid out for it the core path's (by out-degree),
+ * the large-vertex bins' when some out-degree may exceed the workgroup bin's
+ * limit, the main one, those two again for lists cut before the core, and with
+ * d_per_vertex a gather. */
 tc_status tc_graph_count(tc_context* ctx, const tc_graph* g, uint64_t* d_total,
                          uint64_t* d_per_vertex, void* d_scratch, uint64_t scratch_bytes,
                          void* stream);

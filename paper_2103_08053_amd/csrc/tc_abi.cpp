@@ -278,12 +278,13 @@ bool records_on(const tc_params& p, uint32_t n, uint64_t m_in) {
 
 // Layout of the core path (tc_core.hip) for a graph of n vertices and m_in samples built with p.  Ids per
 // block word: the most whose 2^(32 - S) blocks hold every rank; where n is larger, 21 (an 8 KB table in the
-// count's and the build's LDS; R-MAT 22: blocks built in 1.1 ms against 2.0 ms with 20 and 16 KB, and the
-// same count), but 20 from 2^24 vertices on, where a core of 43,008 ranks leaves too many probes to the
-// bucket kernels (R-MAT 26 per-vertex count 388 ms against 397).  A word's index must also be able
-// to name every member of the list of an owner that the path takes.  For default flags (each of them asks
-// for a bin, a probe or an order of its own), single graphs, and enough samples that the few launches more
-// do not show.
+// count's and the build's LDS), but 20 from 2^24 vertices on, where a core of 43,008 ranks leaves too many
+// probes to the bucket kernels.  Counts (total / per-vertex) with 20 and with 21, R-MAT: scale 22 6.94 / 10.4 ms
+// and 7.19 / 9.9, 23 18.3 / 24.6 and 18.0 / 23.5, 24 47.8 / 60.0 and 47.5 / 58.0, 25 125 / 154 and 129 / 155,
+// 26 per-vertex 388 and 397; builds are equal.  A word's index must also be able to name every member of the
+// list of an owner that the path takes.  For default flags (each of them asks for a bin, a probe or an order
+// of its own), single graphs, and from 2^17 samples on: the few launches more cost 2 to 5 us, which show below
+// (R-MAT 10, 2^13 samples: 49 us a count with them, 44 without), where few graphs have owners for the path.
 void core_shape(const tc_context* ctx, const tc_params& p, const tc::BinCaps& caps, uint32_t n, uint64_t m_in,
                 bool batch, Layout& L) {
     L.core_bits = L.core_first = 0;

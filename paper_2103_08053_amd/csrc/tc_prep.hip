@@ -6,9 +6,9 @@
 //     removed, directed pairs read as undirected); single graphs form the
 //     keys as the first sort pass reads its input;
 //  2. radix passes (tc_sort.h) over the top bits of the keys: all but at most 16 low bits of the upper
-//     id, so that equal keys meet in groups of equal top bits; k_dedup finds the first of each distinct
-//     key in its group (a bit per sample; duplicates stay in place and are skipped downstream) and
-//     counts the degrees of the lower ids (runs of equal ids);
+//     id, so that equal keys meet in groups of equal top bits; k_dedup and, for groups of many tiles,
+//     k_dedup_long find the first of each distinct key in its group (a bit per sample; duplicates stay in
+//     place and are skipped downstream) and count the degrees of the lower ids (runs of equal ids);
 //  3. degrees of the upper ids: one partition pass by their top bits, then counters in LDS (k_upper_count);
 //     the rank in (degree, id) order from a radix sort of (degree, id);
 //  4. orientation by rank-by-degree (Section 2.2): the edge runs from the
@@ -16,7 +16,10 @@
 //     its rank, so out-neighbour lists hold ranks and hashing the low bits of
 //     a rank spreads neighbours of similar degree over consecutive buckets
 //     (the reordering idea of Section 4.1; other orders are optional);
-//  5. CSR: stable radix passes of the oriented keys by row; lists and offsets from the runs of equal rows;
+//  5. CSR: radix passes of the oriented keys by row; lists and offsets from the runs of equal rows.  A list's
+//     order is unspecified and differs between builds of the same samples (the keys of a group are in no
+//     order, and the first row pass and the partition by upper id do not keep any); the rows that
+//     global-memory tables probe are put in rank order (k_sort_rows);
 //  5c (optional): the record layout: rank r's record at p(r) holds d+(r) and then the record id
 //     rec_id(p(v)) of each out-neighbour v; records go in rank order, a short one moved to the next
 //     128-byte line where it would straddle one (placed first, written by k_work, which reads d+(v)
@@ -997,10 +1000,11 @@ __global__ void __launch_bounds__(256) k_csr(const unsigned long long* __restric
 // Collective work W(r) = sum of d+(v) over r's out-neighbours v, from the oriented keys sorted by row.  A
 // wavefront walks a range of consecutive edges, 256 at a time with their gathers (v's offsets) issued
 // together, and sums the runs of equal rows: runs that begin and end inside are stored, the first and the
-// last are added to work (cleared beforehand; with ranges of 256 edges those atomics cost 2 of 13 ms).  Bound by the gathers: one 128-byte line per edge at 2^25 vertices (11.8 ms for 537 M
-// edges), 0.51 ms for the 64 M of R-MAT 22, 0.09 ms for the 16 M of R-MAT 20 (16 lanes per row took 0.47
-// and 0.39, waiting for the longest rows).  Record layout: d+(v) comes with v's placement {p(v), d+(v)}, and edge e writes v's record id
-// into its row's record; the row's first edge also writes the header d+(r).  On light graphs the bounds of
+// last are added to work (cleared beforehand; with ranges of 256 edges those atomics cost 2 of 13 ms).  Bound
+// by the gathers: one 128-byte line per edge at 2^25 vertices (10.6 ms for 537 M edges), 0.36 ms for the 64 M of
+// R-MAT 22, 0.09 ms for the 16 M of R-MAT 20 (16 lanes per row took 0.47 and 0.39, waiting for the longest
+// rows).  Record layout: d+(v) comes with v's placement {p(v), d+(v)}, and edge e writes v's record id into its
+// row's record; the row's first edge also writes the header d+(r).  On light graphs the bounds of
 // v's list are kept per edge as well: 8 coalesced bytes that spare the count its own gather of them.
 constexpr uint32_t kWorkItems = 4;
 
@@ -1702,9 +1706,8 @@ hipError_t prep_build(uint32_t n, uint64_t m_in, const uint32_t* src, const uint
     // 4-5: orientation and CSR in rank space.
     unsigned long long* const osorted = reinterpret_cast<unsigned long long*>(t.aux);
     if (!caps.scatter_csr) {
-        // Sort the oriented keys by row only (the high nb bits; the passes are stable, so each list keeps
-        // the order of the canonical keys; lists need no order for hashing): rows come out contiguous, in
-        // aux.
+        // Sort the oriented keys by row only (the high nb bits; lists need no order for hashing, so the first
+        // pass keeps none): rows come out contiguous, in aux.
         const uint32_t passes = row_passes(nb);
         auto buf = [&](uint32_t writes_left) { return writes_left % 2 ? osorted : t.keys_a; };
         uint32_t* hist = take_hist(512 * passes);

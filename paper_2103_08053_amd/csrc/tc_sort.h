@@ -5,7 +5,9 @@
 // the same digit in earlier tiles comes from a decoupled look-back over the tiles' published counts, and
 // the tile is written out from LDS, digit after digit, so that the elements of a digit leave in runs.
 // The digits' totals (`hist`) are counted beforehand, by whichever kernel makes the elements.
-//
+// (The published method is single-pass radix sorting: A. Adinets and D. Merrill, "Onesweep: A Faster Least
+// Significant Digit Radix Sort for GPUs", on the look-back of D. Merrill and M. Garland, "Single-pass Parallel
+// Prefix Scan with Decoupled Look-back".)
 #pragma once
 
 #include <hip/hip_runtime.h>

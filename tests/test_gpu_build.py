@@ -1,6 +1,6 @@
 """The build (canonical sort, distinct edges, degrees, rank, CSR, schedule) against the oracle.
 
-Sizes sit at the edges of its tiles (2048 keys of the distinct-edge pass, 2048, 4096 and 18432 elements of a
+Sizes sit at the edges of its tiles (4096 keys of the distinct-edge pass, 2048, 4096 and 18432 elements of a
 sort pass, 28672 of the upper-id partition), at the id widths where the number of passes or the
 treatment of the upper ids changes (2^9, 2^12, 2^15, 2^16, 2^24, 2^25 ids), and at inputs made of
 duplicates or of self-loops, whose groups of equal keys run over many tiles.
