@@ -617,9 +617,12 @@ def main():
                      "traffic_kind": "bytes between the L2 and the memory fabric per launch, from request counters "
                                      "resolved by size (32/64/128-byte reads, 32/64-byte writes); Infinity Cache "
                                      "hits included, so not DRAM bytes",
-                     "achieved_kind": "algorithmic bytes / kernel time (no cache reuse assumed: re-reads served "
-                                      "by the L2 or the Infinity Cache count as if they came from HBM)",
-                     "kernel": "tc_count_kernel (after tc_hub_kernel, both inside the events)",
+                     "achieved_kind": "algorithmic bytes / kernel time (every 2-hop id as 4 bytes, no cache reuse: "
+                                      "re-reads served by the L2 or the Infinity Cache count as if they came from "
+                                      "HBM, and so do the ids that share a core-path block word, so the rate may "
+                                      "exceed the peak)",
+                     "kernel": "tc_hub_kernel, tc_count_kernel and, where the graph takes the core path, "
+                               "tc_core_kernel (all inside the events)",
                      "algorithmic_bytes": b_alg,
                      "measured_copy_gbs": copy_gbs, "frac_of_measured_copy": achieved / copy_gbs,
                      "issue": issue_ceiling(per_vertex, args.workload, kernel_ms) if not args.flags else None,
